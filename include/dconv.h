@@ -21,7 +21,9 @@
  *     fp32 accumulation; the order of additions is unspecified, so results
  *     agree with an exact sum to within rounding of an fp32 sum of C*F*F
  *     terms, and are bit-exact whenever all partial sums are exactly
- *     representable.
+ *     representable.  (Large layers of dconv_general take the products apart
+ *     into exact ones of 8-bit parts on the bf16 matrix cores; their sums are
+ *     fp32 too and closer to the exact ones.)
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).
  *     Work is enqueued on it and the call returns without synchronising.
  *     The launch happens on the device that is current in the calling thread;
@@ -253,14 +255,17 @@ int dconv_tile_choice(int single_channel, int N, int C, int H, int W, int K, int
  * and replayed.  The one exception is the workspace of dconv_general described
  * below: the first call that needs it on a stream allocates and clears it,
  * which is not allowed while that stream is capturing.  Run the calls once on
- * the stream before capturing on it.
+ * the stream before capturing on it.  (Layers whose products are taken apart
+ * need the workspace for that alone; captured, they run on the fp32 matrix
+ * cores instead, in dconv_general_noalloc as they do otherwise.)
  */
 
 /*
  * dconv_general keeps one device workspace per (device, stream) it has been
  * called on: when the tiles of a shape do not spread evenly over the chip, a
  * tile is summed over channels by several workgroups and their partial sums
- * meet there.  The first call that needs it on a stream allocates, with
+ * meet there; large layers also keep their split filters there between two
+ * kernels of one call.  The first call that needs it on a stream allocates, with
  * hipMalloc, what the largest launch on that device can need (256 KiB of
  * partial sums and four counters per compute unit: 64 MiB + 4 KiB on a 256-CU
  * chip) and clears the counters on that stream; no other entry point
@@ -286,7 +291,7 @@ int dconv_release_workspace(void);
  * the same kernels in the same launch configuration) and same errors as
  * dconv_general_v, but it never calls hipMalloc, hipFree or any allocating
  * routine: where dconv_general_v would use its workspace, the partial sums and
- * arrival counters of shared tiles go to a static device array that is part of
+ * arrival counters of shared tiles and the split filters go to a static device array that is part of
  * the library's code object -- 64 MiB + 16 KiB on every GPU the library runs on,
  * held until the process ends.  That is room for 512 workgroups with two 64 x 256
  * partial tiles each and 4096 counters, i.e. for every launch configuration on

@@ -21,6 +21,7 @@ SOURCES = [("api.hip", [], "api"), ("simple.hip", [], "simple"), ("single.hip", 
            ("general.hip", [], "general"), ("general_fewfilters.hip", [], "general_fewfilters")] + \
           [("general_few_inst.hip", [f"-DDCONV_F={f}"], f"general_few_f{f}") for f in range(1, 8)] + \
           [("general_inst.hip", [f"-DDCONV_F={f}"], f"general_f{f}") for f in range(1, 33)] + \
+          [("split_inst.hip", [f"-DDCONV_F={f}"], f"split_f{f}") for f in range(2, 8)] + \
           [("half.hip", [], "half")] + \
           [("half_inst.hip", [f"-DDCONV_F={f}"], f"half_f{f}") for f in range(1, 33)]
 

@@ -1,10 +1,12 @@
 // General-case direct convolution: dispatch over filter side, tile shape and schedule, and
 // the workspace that shared tiles are summed through.  The kernel is in general_kernel.h.
+#include <cmath>
 #include <map>
 #include <mutex>
 #include <utility>
 #include <vector>
 #include "general_kernel.h"
+#include "split_kernel.h"
 
 namespace dconv {
 
@@ -39,6 +41,23 @@ std::map<std::pair<int, hipStream_t>, WsEntry> g_ws;
 
 }  // namespace
 
+std::mutex& gen_launch_mutex()
+{
+    static std::mutex m;
+    return m;
+}
+
+int gen_cus()
+{
+    static std::atomic<int> seen[64] = {};       // per device
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return 0;
+    if (dev >= 0 && dev < 64 && (cus = seen[dev].load(std::memory_order_relaxed)) > 0) return cus;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return 0;
+    if (dev >= 0 && dev < 64) seen[dev].store(cus, std::memory_order_relaxed);
+    return cus;
+}
+
 GenWorkspace gen_workspace(hipStream_t st, size_t part_floats, size_t ncnt)
 {
     int dev = 0, cus = 0;
@@ -49,7 +68,7 @@ GenWorkspace gen_workspace(hipStream_t st, size_t part_floats, size_t ncnt)
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
         return {nullptr, nullptr};
     if (e.part_floats < part_floats) {
-        const size_t want = std::max(part_floats, kPartFloatsPerCu * (size_t)cus);
+        const size_t want = std::max(part_floats, std::max(kPartFloatsPerCu * (size_t)cus, kGenWorkspaceFloats));
         float* fresh = nullptr;
         if (hipMalloc((void**)&fresh, want * sizeof(float)) != hipSuccess) {
             (void)hipGetLastError();
@@ -99,7 +118,7 @@ void release_general_workspaces()
 namespace {
 
 constexpr size_t kScratchCounters = 4096;               // ints: 16 KiB, then the partial sums
-constexpr size_t kScratchPartFloats = (size_t)16 << 20; // 64 MiB: 512 workgroups x 2 x (64 x 256)
+constexpr size_t kScratchPartFloats = kGenWorkspaceFloats; // 64 MiB: 512 workgroups x 2 x (64 x 256)
 constexpr size_t kScratchBytes = 4 * (kScratchCounters + kScratchPartFloats);
 constexpr int kMaxDevices = 64;
 
@@ -136,6 +155,7 @@ int gen_static_workspace(hipStream_t st, size_t part_floats, size_t ncnt, GenWor
     }
     ws->cnt = (int*)base;
     ws->part = (float*)(base + 4 * kScratchCounters);
+    if (ncnt == 0) return DCONV_OK;
     begin_launch();
     hipLaunchKernelGGL(clear_counters_kernel, dim3((unsigned)((ncnt + kThreads - 1) / kThreads)),
                        dim3(kThreads), 0, st, ws->cnt, (int)ncnt);
@@ -295,6 +315,74 @@ bool general_tiled_supports(const Shape& s)
     return whole_batch_supported(s) || per_image_supported(s, &one);
 }
 
+namespace {
+
+int launch_split(const float* in, const float* filt, float* out, const Shape& s, hipStream_t st, const GenSched& sched, bool dry)
+{
+    switch (s.F) {
+    case 2: return split_launch_for_F<2>(in, filt, out, s, st, sched, dry);
+    case 3: return split_launch_for_F<3>(in, filt, out, s, st, sched, dry);
+    case 4: return split_launch_for_F<4>(in, filt, out, s, st, sched, dry);
+    case 5: return split_launch_for_F<5>(in, filt, out, s, st, sched, dry);
+    case 6: return split_launch_for_F<6>(in, filt, out, s, st, sched, dry);
+    case 7: return split_launch_for_F<7>(in, filt, out, s, st, sched, dry);
+    default: return DCONV_UNSUPPORTED;
+    }
+}
+
+// When the split-operand kernel goes before the fp32 one, and whether its tiles are shared: by
+// estimates of the three kernel times, fitted to 1170 layers drawn at random (8 to 512 channels,
+// 17 to 512 filters of 2x2 to 7x7, 7 x 7 to 128 x 256 maps, 1 to 64 images, 0.05 to 60 GFLOP; rms
+// 6 % whole tiles, 12 % shared, 15 % the fp32 kernel).  Split, per round of tiles over the CUs:
+// 0.33 us a matrix-core step of a workgroup, 1.4 us a unit, 5 us a tile; 6.7 us for the launch with
+// the small kernel in front.  Shared tiles cost 0.45 us a step and the parts of a tile meet at
+// about 1 us each.  fp32: 118 TFLOP/s of what a block of 32 or 64 filters computes and 12 us.
+// It has to promise an eighth: over those layers the chosen ones are 1.35 times faster on average.
+// (0: no, 1: whole tiles, 2: shared)
+int split_mode(const Shape& s)
+{
+    if (s.F < 2 || s.F > 7 || s.K < 17) return 0;
+    const SplitPlan pl = make_split_plan(s, split_image_rows(s.F), 256, split_most_pixels(s.F));
+    if (!pl.ok) return 0;
+    constexpr int cus = 256;
+    const double tiles = ((double)(pl.nstrips - 1) * pl.pt_full + pl.pt_last) * ((s.K + 63) / 64);
+    const double nun = (double)((s.C + 15) / 16) * (s.F / split_image_rows(s.F));
+    const double steps = (double)split_image_rows(s.F) * s.F;
+    const double rounds = std::ceil(tiles / cus);
+    const double whole = 6.7 + rounds * (nun * (0.326 * steps + 1.42) + 5.0) + (nun == 1 ? 2.5 : 0.0);
+    const double units = std::ceil(tiles * nun / cus);
+    const double parts = tiles < cus ? std::min<double>(cus, tiles * nun) / tiles : 1.0;
+    // (a few tiles of many parts each: the workgroup that adds them takes longer than the estimate)
+    const double shared = tiles >= 24 && nun > 1 ? 10.3 + units * (0.447 * steps + 1.70) + 2.0 * rounds + 1.06 * parts : 1e30;
+    const int k64 = (s.K + 63) / 64 * 64, k32 = (s.K + 31) / 32 * 32;
+    const double taps = (double)s.C * s.F * s.F, px = (double)s.N * s.Ho * s.Wo;
+    const double mflop = 2e-6 * px * taps * (s.K <= 32 || s.F >= 3 ? k32 : k64);
+    const double fp32 = 12.3 + 0.00847 * mflop + 0.0417 * std::sqrt(mflop) + 0.128e-6 * px * s.K + 0.0033 * taps;
+    if (std::min(whole, shared) > 0.88 * fp32) return 0;
+    return whole <= shared ? 1 : 2;
+}
+
+// Runs the layer on the split-operand kernel if it is the better choice; DCONV_UNSUPPORTED if the
+// fp32 kernel has to.  A call that is being captured into a graph stays on the fp32 kernel unless
+// its scratch memory is the static array: the workspace may have to be allocated, which a capture
+// does not allow, and two graphs captured on one stream would share the split filters in it.
+int try_split(const float* in, const float* filt, float* out, const Shape& s, hipStream_t st, bool static_ws)
+{
+    const int mode = split_mode(s);
+    if (mode == 0) return DCONV_UNSUPPORTED;
+    if (!static_ws) {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(st, &cap) != hipSuccess) {
+            (void)hipGetLastError();
+            return DCONV_UNSUPPORTED;
+        }
+        if (cap != hipStreamCaptureStatusNone) return DCONV_UNSUPPORTED;
+    }
+    return launch_split(in, filt, out, s, st, GenSched{mode, 0, false, static_ws, 0}, false);
+}
+
+}  // namespace
+
 int launch_general_tiled(const float* in, const float* filt, float* out, const Shape& s,
                          hipStream_t st, int cfg, bool static_ws)
 {
@@ -308,6 +396,11 @@ int launch_general_tiled(const float* in, const float* filt, float* out, const S
             if (rc != DCONV_OK) return rc;
         }
         return DCONV_OK;
+    }
+    // (a forced configuration that is what the shape's own choice names runs the same way)
+    if (cfg < 0 || (cfg < kShapes && cfg == shape_for(s))) {
+        const int rc = try_split(in, filt, out, s, st, static_ws);
+        if (rc != DCONV_UNSUPPORTED) return rc;
     }
     if (cfg < 0) {
         const GenSched sched{0, 0, false, static_ws, 0};

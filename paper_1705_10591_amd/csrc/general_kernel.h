@@ -42,6 +42,7 @@
 //    the result does not depend on the order of arrival.
 #pragma once
 #include <algorithm>
+#include <mutex>
 #include "common.h"
 #include "../../include/dconv.h"
 
@@ -727,6 +728,12 @@ struct GenWorkspace {
 // Returns a workspace with room for `part_floats` floats of partial sums and `ncnt` counters,
 // or nullptr members on allocation failure.
 GenWorkspace gen_workspace(hipStream_t st, size_t part_floats, size_t ncnt);
+// floats every workspace has room for (and the static array): the largest launch's partial sums
+constexpr size_t kGenWorkspaceFloats = (size_t)16 << 20;
+// Held while a call that uses a workspace enqueues its kernels: calls from several threads on one
+// stream share its workspace, and a call of two kernels must not be cut in two.
+std::mutex& gen_launch_mutex();
+int gen_cus();            // CUs of the current device, 0 on an error
 // The same room inside the static device array of the current device, its counters cleared on
 // `st` by a small kernel.  Allocates nothing.  Returns a dconv_status: DCONV_SCRATCH_EXCEEDED if
 // the array is too small for the request.
@@ -869,6 +876,8 @@ int gen_try_launch(const float* in, const float* filt, float* out, const Shape& 
         else { split = 0; U = tiles; G = (int)tiles; }
     }
 
+    std::unique_lock<std::mutex> lock(gen_launch_mutex(), std::defer_lock);
+    if (split) lock.lock();
     GenWorkspace ws{nullptr, nullptr};
     if (split && sched.static_ws) {
         const int rc = gen_static_workspace(st, (size_t)G * 2 * MT * NT, (size_t)G, &ws);

@@ -1,0 +1,157 @@
+"""The split-operand kernel of the general case: fp32 layers on the bf16 matrix cores, each value as
+three bf16 parts.  The library picks it by size (3x3 and neighbouring filters, enough work), so the
+shapes here are ones it is picked for: a call that ran on it differs in its last bits from the
+fp32 matrix-core kernel, forced, and is closer to the exact sums.
+"""
+import ctypes
+import threading
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import workloads as wl
+import paper_1705_10591_amd as dconv
+from helpers import assert_within_bound
+
+pytestmark = pytest.mark.gpu
+
+# (N, C, H, W, K, F): every compiled filter side; channels off multiples of sixteen (zero channels in
+# the last chunk), filters off multiples of 64, column strips, pixel tiles that end anywhere in a
+# row, whole tiles and tiles shared between workgroups
+SHAPES = [(11, 154, 63, 63, 39, 2), (4, 96, 55, 55, 179, 3), (20, 61, 65, 65, 64, 3), (1, 100, 60, 300, 96, 3),
+          (1, 64, 224, 224, 64, 3), (14, 48, 66, 66, 64, 4), (5, 40, 75, 67, 100, 5), (6, 48, 40, 44, 100, 6),
+          (3, 40, 60, 62, 120, 7), (8, 97, 25, 25, 250, 7)]
+ids = lambda s: "x".join(map(str, s))
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to("cuda")
+
+
+def call(x, f, variant=dconv.VARIANT_AUTO, noalloc=False):
+    print(f"general {tuple(x.shape)} K,F={f.shape[0]},{f.shape[-1]} variant={variant:#x}", flush=True)
+    out = dconv.dconv_general(dev(x), dev(f), variant=variant, noalloc=noalloc)
+    torch.cuda.synchronize()
+    return out.cpu().numpy()
+
+
+def fp32_variant(N, C, H, W, K, F):
+    """The fp32 kernel with the shape's own tile, whole tiles only."""
+    return dconv.VARIANT_TILED_CFG0 + 3 + dconv.tile_choice(False, N, C, H, W, K, F)
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=ids)
+def test_within_the_bound_and_closer_than_the_fp32_kernel(shape):
+    N, C, H, W, K, F = shape
+    x, f = wl.random_case(8000 + C + F, N, C, H, W, K, F, "u01", "he")
+    acc, mag, _ = oracle.general(x, f)
+    got, fp32 = call(x, f), call(x, f, fp32_variant(*shape))
+    assert not np.array_equal(got, fp32), "the split-operand kernel is expected to run here"
+    assert_within_bound(got, acc, mag, f"split {shape}")
+    err = np.linalg.norm(got - acc), np.linalg.norm(fp32 - acc)
+    assert err[0] <= err[1], err
+    # the same bits every time, through every entry point and variant that names this choice
+    assert np.array_equal(call(x, f), got) and np.array_equal(call(x, f, noalloc=True), got)
+    assert np.array_equal(call(x, f, dconv.VARIANT_TILED_CFG0 + dconv.tile_choice(False, *shape)), got)
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=ids)
+def test_integer_inputs_exact_between_guard_bands(shape):
+    N, C, H, W, K, F = shape
+    x, f = wl.integer_case(8100 + C + F, N, C, H, W, K, F)
+    want = oracle.general(x, f)[0].astype(np.float32)
+    buf = torch.full((want.size + 2048,), float("nan"), device="cuda")
+    out = buf[1001:1001 + want.size].view(want.shape)
+    xb = torch.empty(x.size + 1, device="cuda")[1:].view(x.shape)      # images need no alignment beyond a float's
+    xb.copy_(dev(x))
+    print(f"integers {shape}", flush=True)
+    dconv.dconv_general(xb, dev(f), out=out)
+    torch.cuda.synchronize()
+    assert np.array_equal(out.cpu().numpy(), want)
+    assert torch.isnan(buf[:1001]).all() and torch.isnan(buf[1001 + want.size:]).all()
+
+
+@pytest.mark.parametrize("shape", [(4, 96, 55, 55, 179, 3), (14, 48, 66, 66, 64, 4), (3, 40, 60, 62, 120, 7)], ids=ids)
+def test_values_the_parts_cannot_carry(shape):
+    """Infinities, NaN, values next to the largest float, subnormal values and products of tiny and huge
+    ones: the outputs they reach are what fp32 gives, the others are untouched."""
+    N, C, H, W, K, F = shape
+    x, f = wl.random_case(8200 + F, N, C, H, W, K, F)
+    rng = np.random.default_rng(F)
+    xb, fb = x.copy(), f.copy()
+    for bad in (np.nan, np.inf, -np.inf, 3.4e38, -3.39e38):
+        xb[rng.integers(N), rng.integers(C), rng.integers(H), rng.integers(W)] = bad
+    fb[K - 1, C - 1, 0, 0], fb[5, 0, F - 1, 0] = np.inf, np.nan
+    with np.errstate(all="ignore"):
+        acc, mag, _ = oracle.general(xb, fb)
+        got = call(xb, fb)
+    fits = np.abs(acc) < 3.3e38
+    assert np.array_equal(np.isnan(got), np.isnan(acc))
+    assert np.array_equal(got[np.isinf(acc)], acc[np.isinf(acc)])
+    assert fits.any() and np.all(np.abs(got[fits] - acc[fits]) <= 1e-5 * mag[fits])
+    # (the reference result of a subnormal product may be off by half the smallest float a term)
+    for sx, sf in ((2.0**-120, 1.0), (2.0**-128, 2.0**20), (1.0, 2.0**-118), (2.0**-115, 2.0**60), (2.0**70, 2.0**-130)):
+        xs, fs = (x * np.float32(sx)).astype(np.float32), (f * np.float32(sf)).astype(np.float32)
+        acc, mag, _ = oracle.general(xs, fs)
+        got = call(xs, fs)
+        assert np.all(np.abs(got - acc) <= 1e-5 * mag + C * F * F * 2.0**-150), (sx, sf)
+    # half of the images far below the other half
+    xs = x.copy()
+    xs[::2] *= np.float32(2.0**-122)
+    acc, mag, _ = oracle.general(xs, f)
+    got = call(xs, f)
+    assert np.all(np.abs(got - acc) <= 1e-5 * mag + C * F * F * 2.0**-150)
+
+
+def test_two_threads_on_one_stream():
+    """The filters are split into the stream's workspace by a kernel of its own: two threads that call
+    on one stream must not come between each other's two kernels."""
+    lib, stream = dconv.load_library(), torch.cuda.Stream()
+    vp, cases = ctypes.c_void_p, []
+    for shape in ((14, 48, 66, 66, 64, 4), (6, 48, 40, 44, 100, 6)):
+        N, C, H, W, K, F = shape
+        x, f = wl.random_case(8300 + F, *shape)
+        xd, fd = dev(x), dev(f)
+        cases.append((shape, xd, fd, dconv.dconv_general(xd, fd), [torch.empty(N, K, H - F + 1, W - F + 1, device="cuda")
+                                                                  for _ in range(20)]))
+    torch.cuda.synchronize()
+
+    def work(case):
+        (N, C, H, W, K, F), xd, fd, _, outs = case
+        for o in outs:
+            assert lib.dconv_general(vp(xd.data_ptr()), N, C, H, W, vp(fd.data_ptr()), K, F, vp(o.data_ptr()),
+                                     vp(stream.cuda_stream)) == dconv.STATUS_OK
+
+    threads = [threading.Thread(target=work, args=(c,)) for c in cases]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    stream.synchronize()
+    for _, _, _, want, outs in cases:
+        assert all(torch.equal(o, want) for o in outs)
+
+
+def test_a_first_call_on_a_stream_can_be_captured():
+    """A capture may not allocate: such a call runs on the fp32 kernel, as it did without a workspace."""
+    shape = (1, 64, 224, 224, 64, 3)            # (whole tiles on the fp32 kernel: no workspace there)
+    N, C, H, W, K, F = shape
+    x, f = wl.random_case(8400, *shape)
+    acc, mag, _ = oracle.general(x, f)
+    xd, fd = dev(x), dev(f)
+    out = torch.empty(acc.shape, device="cuda")
+    warm = dconv.dconv_general(xd, fd, variant=fp32_variant(*shape))      # (loads the kernel; no workspace)
+    torch.cuda.synchronize()
+    g, s = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    print("capturing a first call", flush=True)
+    with torch.cuda.graph(g, stream=s):
+        dconv.dconv_general(xd, fd, out=out)
+    for rep in range(3):
+        out.fill_(float("nan"))
+        eager = dconv.dconv_general(xd, fd)
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, warm), f"replay {rep}"
+        assert_within_bound(eager.cpu().numpy(), acc, mag, "eager call between replays")

@@ -84,6 +84,9 @@ bool general_tiled_supports(const Shape& s);
 void release_general_workspaces();
 // Short data types (dtype: DCONV_DTYPE_*, layout: DCONV_LAYOUT_*); variant: AUTO, SIMPLE, TILED
 // or TILED_CFG0 + i.  `out` receives fp32 values, or int32 bit patterns for 8-bit integer inputs.
+// ... and their 1x1 layers where it is the better choice (half_1x1.hip); DCONV_UNSUPPORTED elsewhere
+int launch_general_point(const void* in, const void* filt, float* out, const Shape& s, hipStream_t st,
+                         int dtype, bool blocked);
 int launch_general_half(const void* in, const void* filt, float* out, const Shape& s, hipStream_t st,
                         int dtype, int layout, int variant);
 

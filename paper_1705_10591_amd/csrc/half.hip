@@ -118,8 +118,10 @@ int launch_general_half(const void* in, const void* filt, float* out, const Shap
     if (variant >= DCONV_VARIANT_TILED_CFG0 && variant < DCONV_VARIANT_TILED_CFG0 + kHalfConfigs)
         return launch_tiled(in, filt, out, s, st, dtype, variant - DCONV_VARIANT_TILED_CFG0, blocked, false);
     if (variant != DCONV_VARIANT_AUTO && variant != DCONV_VARIANT_TILED) return DCONV_UNSUPPORTED;
+    int rc = launch_general_point(in, filt, out, s, st, dtype, blocked);
+    if (rc != DCONV_UNSUPPORTED) return rc;
     const int cfg = preferred_config(s, dtype, blocked);
-    int rc = launch_tiled(in, filt, out, s, st, dtype, cfg, blocked, false);
+    rc = launch_tiled(in, filt, out, s, st, dtype, cfg, blocked, false);
     // (the small tiles hold every shape the large one does, and the register-staged one the most)
     if (rc == DCONV_UNSUPPORTED && cfg != 0) rc = launch_tiled(in, filt, out, s, st, dtype, 0, blocked, false);
     if (rc == DCONV_UNSUPPORTED && variant == DCONV_VARIANT_AUTO)

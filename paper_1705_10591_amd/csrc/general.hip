@@ -58,6 +58,14 @@ int gen_cus()
     return cus;
 }
 
+bool gen_capturing(hipStream_t st)
+{
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cap) == hipSuccess) return cap != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
 GenWorkspace gen_workspace(hipStream_t st, size_t part_floats, size_t ncnt)
 {
     int dev = 0, cus = 0;
@@ -331,13 +339,14 @@ int launch_split(const float* in, const float* filt, float* out, const Shape& s,
 }
 
 // When the split-operand kernel goes before the fp32 one, and whether its tiles are shared: by
-// estimates of the three kernel times, fitted to 1170 layers drawn at random (8 to 512 channels,
-// 17 to 512 filters of 2x2 to 7x7, 7 x 7 to 128 x 256 maps, 1 to 64 images, 0.05 to 60 GFLOP; rms
-// 6 % whole tiles, 12 % shared, 15 % the fp32 kernel).  Split, per round of tiles over the CUs:
-// 0.33 us a matrix-core step of a workgroup, 1.4 us a unit, 5 us a tile; 6.7 us for the launch with
-// the small kernel in front.  Shared tiles cost 0.45 us a step and the parts of a tile meet at
-// about 1 us each.  fp32: 118 TFLOP/s of what a block of 32 or 64 filters computes and 12 us.
-// It has to promise an eighth: over those layers the chosen ones are 1.35 times faster on average.
+// estimates of the three kernel times, fitted to 1000 layers drawn at random (8 to 512 channels,
+// 17 to 512 filters of 2x2 to 7x7, 7 x 7 to 128 x 256 maps, 1 to 64 images, 0.3 to 60 GFLOP; rms
+// 5 % whole tiles, 8 % shared, 15 % the fp32 kernel).  Split, per round of tiles over the CUs:
+// 0.32 us a matrix-core step of a workgroup, 1.4 us a unit, 4.8 us a tile; 7.6 us for the launch with
+// the small kernel in front.  Shared tiles cost 0.41 us a step and the parts of a tile meet at
+// about 1.1 us each.  fp32: 133 TFLOP/s of what a block of 32 or 64 filters computes and 8 us, more on
+// layers that do not fill the chip.  It has to promise a seventh: over those layers the chosen ones
+// are 1.4 times faster on average and 6 of 1000 slower by 3 to 12 %.
 // (0: no, 1: whole tiles, 2: shared)
 int split_mode(const Shape& s)
 {
@@ -349,16 +358,18 @@ int split_mode(const Shape& s)
     const double nun = (double)((s.C + 15) / 16) * (s.F / split_image_rows(s.F));
     const double steps = (double)split_image_rows(s.F) * s.F;
     const double rounds = std::ceil(tiles / cus);
-    const double whole = 6.7 + rounds * (nun * (0.326 * steps + 1.42) + 5.0) + (nun == 1 ? 2.5 : 0.0);
+    const double taps = (double)s.C * s.F * s.F, px = (double)s.N * s.Ho * s.Wo;
+    // (layers of one unit a tile and few taps are bound by their stores, in which the fp32 kernel is better)
+    const double stores = nun == 1 && taps <= 160 ? 1.2 : 1.0;
+    const double whole = stores * (7.6 + rounds * (nun * (0.319 * steps + 1.41) + 4.8));
     const double units = std::ceil(tiles * nun / cus);
     const double parts = tiles < cus ? std::min<double>(cus, tiles * nun) / tiles : 1.0;
     // (a few tiles of many parts each: the workgroup that adds them takes longer than the estimate)
-    const double shared = tiles >= 24 && nun > 1 ? 10.3 + units * (0.447 * steps + 1.70) + 2.0 * rounds + 1.06 * parts : 1e30;
+    const double shared = tiles >= 24 && nun > 1 ? 15.2 + units * (0.413 * steps + 1.36) + 1.9 * rounds + 1.1 * parts : 1e30;
     const int k64 = (s.K + 63) / 64 * 64, k32 = (s.K + 31) / 32 * 32;
-    const double taps = (double)s.C * s.F * s.F, px = (double)s.N * s.Ho * s.Wo;
     const double mflop = 2e-6 * px * taps * (s.K <= 32 || s.F >= 3 ? k32 : k64);
-    const double fp32 = 12.3 + 0.00847 * mflop + 0.0417 * std::sqrt(mflop) + 0.128e-6 * px * s.K + 0.0033 * taps;
-    if (std::min(whole, shared) > 0.88 * fp32) return 0;
+    const double fp32 = 8.3 + 0.0075 * mflop + 0.278 * std::sqrt(mflop) - 0.33e-6 * px * s.K;
+    if (std::min(whole, shared) > 0.86 * fp32) return 0;
     return whole <= shared ? 1 : 2;
 }
 
@@ -370,14 +381,7 @@ int try_split(const float* in, const float* filt, float* out, const Shape& s, hi
 {
     const int mode = split_mode(s);
     if (mode == 0) return DCONV_UNSUPPORTED;
-    if (!static_ws) {
-        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-        if (hipStreamIsCapturing(st, &cap) != hipSuccess) {
-            (void)hipGetLastError();
-            return DCONV_UNSUPPORTED;
-        }
-        if (cap != hipStreamCaptureStatusNone) return DCONV_UNSUPPORTED;
-    }
+    if (!static_ws && gen_capturing(st)) return DCONV_UNSUPPORTED;
     return launch_split(in, filt, out, s, st, GenSched{mode, 0, false, static_ws, 0}, false);
 }
 

@@ -86,7 +86,8 @@ struct GenParams {
     int nch;         // channel chunks per tile
     int tiles;       // all tiles: ((nstrips - 1) * pt_full + pt_last) * KB
     int G;           // workgroups launched
-    int split;       // 1: ranges are cut in units (tiles may be shared), 0: in whole tiles
+    int split;       // 1: ranges are cut in units (tiles may be shared), 0: in whole tiles; 2: in units, and
+                     // every workgroup leaves its sums in the workspace for gen_sum_parts_kernel
     int aligned;     // 1: tiles are written back through LDS in whole 128-byte lines
     int pad_words;   // LDS words added to every slot so that it can hold a tile on its way out
     FastDiv d_strip; // by pt_full * KB
@@ -525,7 +526,7 @@ general_tiled_kernel(GenParams p)
             if (p.aligned) store_out_aligned(tile, r0, r1);
             else store_out();
         };
-        if (whole) { emit(); return; }
+        if (whole && p.split != 2) { emit(); return; }
         const int t0u = tile * nch;
         const int first = unit_owner(t0u, U, G), last = unit_owner(t0u + nch - 1, U, G);
         const int m = last - first + 1;
@@ -538,6 +539,7 @@ general_tiled_kernel(GenParams p)
                 for (int r = 0; r < 16; ++r)
                     __hip_atomic_store(mine + ((mt * NW + nt) * 16 + r) * kWave, acc[mt][nt][r],
                                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (p.split == 2) return;
         // Every store of this workgroup has to be acknowledged (performed at device scope)
         // before its arrival is counted.  A workgroup-scope fence does not wait for that and a
         // device-scope one would write back the whole L2: each wave waits for its own stores
@@ -676,6 +678,45 @@ general_tiled_kernel(GenParams p)
     }
 }
 
+// The second kernel of a launch whose tiles are shared by many workgroups each (split == 2).  A
+// workgroup that adds the parts of its tile one after the other needs about 1 us a part; here every
+// word of every tile has a thread of its own, which adds its parts in the order of the
+// workgroups (the loads of eight parts at a time are independent) and writes the output.
+template <int MW, int NW>
+__global__ void __launch_bounds__(256)
+gen_sum_parts_kernel(GenParams p)
+{
+    constexpr int MT = 32 * MW, NT = 128 * NW, BPT = MT * NT / 256;      // blocks per tile
+    const int tile = blockIdx.x / BPT;
+    const int e = (blockIdx.x % BPT) * 256 + threadIdx.x;
+    const int lane = e & 63, r = (e >> 6) & 15, blk = (e >> 10) % (MW * NW), w = (e >> 10) / (MW * NW);
+    const int nch = p.nch, U = p.tiles * nch, G = p.G, t0u = tile * nch;
+    const int first = unit_owner(t0u, U, G), last = unit_owner(t0u + nch - 1, U, G);
+    auto part = [&](int i) __attribute__((always_inline)) {
+        return p.part[(int64_t)(2 * i + (range_start(i, U, G) >= t0u ? 0 : 1)) * (MT * NT) + e];
+    };
+    // (only a tile's first workgroup can have begun before it)
+    float sum = part(first);
+    for (int i = first + 1; i <= last; i += 8) {
+        float v[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v[q] = i + q <= last ? p.part[(int64_t)(2 * (i + q)) * (MT * NT) + e] : 0.f;
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+            if (i + q <= last) sum += v[q];
+    }
+    const int per_strip = p.pt_full * p.KB;
+    const int strip = min(fdiv(tile, p.d_strip), p.nstrips - 1);
+    const int rem = tile - strip * per_strip;
+    const int ptile = fdiv(rem, p.d_kb), kb = rem - ptile * p.KB;
+    const int x0 = strip * p.bw, ws = min(p.bw, p.Wo - x0);
+    const int pp = ptile * NT + (w * NW + blk % NW) * 32 + (lane & 31);
+    const int k = kb * MT + (blk / NW) * 32 + 8 * (r / 4) + 4 * (lane >> 5) + r % 4;
+    if (pp >= p.N * p.Ho * ws || k >= p.K) return;
+    const int Q = pp / ws, xl = pp - Q * ws, n = fdiv(Q, p.d_ho), y = Q - n * p.Ho;
+    p.out[(((int64_t)n * p.K + k) * p.Ho + y) * p.Wo + x0 + xl] = sum;
+}
+
 // ---- host side: one instantiation -------------------------------------------------------------
 
 struct GenPlan {
@@ -713,7 +754,7 @@ inline GenPlan make_gen_plan(const Shape& s, int NT, int CSH, int imax, int rg, 
 
 // How a launch cuts the work; filled in by the dispatcher.
 struct GenSched {
-    int mode;          // 0: decide by shape, 1: whole tiles only, 2: cut inside tiles
+    int mode;          // 0: decide by shape, 1: whole tiles only, 2: cut inside tiles, 3: cut, parts added by a second kernel
     int force_G;       // > 0: this many workgroups (tests), 0: what the chip holds
     bool widest_only;  // refuse shapes whose image block needs narrower column strips
     bool static_ws;    // shared tiles meet in the library's static device array: nothing is allocated
@@ -734,6 +775,7 @@ constexpr size_t kGenWorkspaceFloats = (size_t)16 << 20;
 // stream share its workspace, and a call of two kernels must not be cut in two.
 std::mutex& gen_launch_mutex();
 int gen_cus();            // CUs of the current device, 0 on an error
+bool gen_capturing(hipStream_t st);   // the stream is being captured into a graph (or cannot be asked)
 // The same room inside the static device array of the current device, its counters cleared on
 // `st` by a small kernel.  Allocates nothing.  Returns a dconv_status: DCONV_SCRATCH_EXCEEDED if
 // the array is too small for the request.
@@ -816,9 +858,9 @@ int gen_try_launch(const float* in, const float* filt, float* out, const Shape& 
     const int cus = chip / (int)(((uint32_t)seen >> 24) & 0xFFu);
 
     // Whole tiles when they spread evenly enough, otherwise cut inside tiles.
-    int G, split;
+    int G, split, alone_G = 0, alone_split = 0;      // (alone_: the choice without a second kernel)
     if (sched.mode == 1) split = 0;
-    else if (sched.mode == 2) split = 1;
+    else if (sched.mode >= 2) split = sched.mode - 1;
     else {
         // ... when a last round would leave much of the chip idle and a tile is long enough
         // (about 60 us with the workgroups of a CU sharing its matrix cores) for the saving to
@@ -874,17 +916,48 @@ int gen_try_launch(const float* in, const float* filt, float* out, const Shape& 
         // promises 4.5 us or more, sharing is 25-85 % faster)
         if (best < 0.9 * whole && whole - best >= 3.0) { split = 1; U = tiles * nch; G = (int)best_g; }
         else { split = 0; U = tiles; G = (int)tiles; }
+        // ... or all parts are added by a second kernel, which costs 7 us with its launch but next to
+        // nothing a part, so that a workgroup per CU pays however few the tiles are.  Its time is
+        // fitted to 260 small layers (1 to 8 images of 7 x 7 to 60 x 60, 16 to 1024 channels, 1x1, 3x3
+        // and 5x5 filters; rms 7 %), the time of the choice above to the same (19 %); where the
+        // first promises a tenth less (and 2.5 us: below, the launch decides) the layers are 1.6 times
+        // faster on average (one image of 256 x 14 x 14, 256 3x3 filters: 25.4 -> 14.3 us; 512 x 7 x
+        // 7, 512: 32.3 -> 18.3 us; 96 x 20 x 20, 32: 18.3 -> 10.0 us), none slower by more than 4 %.
+        alone_G = G;
+        alone_split = split;
+        const double now_us = 6.52 + 1.044 * (split ? best : whole);
+        double sum_us = 1e30;
+        int sum_G = 0;
+        for (int g : {64, 96, 128, 160, 192, 224, 256, 384, 512}) {
+            if (g <= tiles || g > chip || now_us < 10.0) continue;
+            const int64_t units = (tiles * nch + g - 1) / g;
+            const double t = 7.0 + 0.0315 * (double)(units * Gm::S * (MW * NW)) * ((g + cus - 1) / cus) + 0.344 * (double)units +
+                             0.048 * (double)g / (double)tiles + 0.0146 * g;
+            if (t < sum_us) { sum_us = t; sum_G = g; }
+        }
+        // (a layer that needed no workspace needs none under capture: it could not be allocated there)
+        if (sum_us < 0.9 * now_us && now_us - sum_us >= 2.5 && !(split == 0 && !sched.static_ws && gen_capturing(st))) {
+            split = 2;
+            U = tiles * nch;
+            G = sum_G < U ? sum_G : (int)U;
+        }
     }
 
     std::unique_lock<std::mutex> lock(gen_launch_mutex(), std::defer_lock);
     if (split) lock.lock();
     GenWorkspace ws{nullptr, nullptr};
-    if (split && sched.static_ws) {
-        const int rc = gen_static_workspace(st, (size_t)G * 2 * MT * NT, (size_t)G, &ws);
-        if (rc != DCONV_OK) return rc;
-    } else if (split) {
-        ws = gen_workspace(st, (size_t)G * 2 * MT * NT, (size_t)G);
-        if (!ws.part || !ws.cnt) return DCONV_LAUNCH_FAILED;
+    for (;;) {
+        int rc = DCONV_OK;
+        const size_t floats = (size_t)G * 2 * MT * NT, counters = split == 1 ? (size_t)G : 0;
+        if (split && sched.static_ws) rc = gen_static_workspace(st, floats, counters, &ws);
+        else if (split) {
+            ws = gen_workspace(st, floats, counters);
+            if (!ws.part || (counters && !ws.cnt)) rc = DCONV_LAUNCH_FAILED;
+        }
+        if (rc == DCONV_OK) break;
+        if (split != 2 || sched.mode == 3) return rc;
+        split = alone_split;                          // no room for the parts: as without a second kernel
+        G = alone_G;
     }
     GenParams p{in, filt, out, ws.part, ws.cnt, s.N, s.C, s.H, s.W, s.K, s.Ho, s.Wo,
                 pl.bw, pl.nstrips, pl.LS, pl.RS, pl.pt_full, KB, nch, (int)tiles, G, split, aligned, (int)pad_words,
@@ -893,6 +966,11 @@ int gen_try_launch(const float* in, const float* filt, float* out, const Shape& 
                 make_fastdiv(nch), s.Ho + RG - 1};
     begin_launch();
     hipLaunchKernelGGL(kern, dim3((unsigned)G), dim3(kThreads), (size_t)lds_bytes, st, p);
+    if (split == 2) {
+        static_assert(WM == 1 && WN == 4, "gen_sum_parts_kernel's order of words");
+        if (const int rc = launch_status(); rc != DCONV_OK) return rc;
+        hipLaunchKernelGGL((gen_sum_parts_kernel<MW, NW>), dim3((unsigned)(tiles * (MT * NT / 256))), dim3(256), 0, st, p);
+    }
     return launch_status();
 }
 

@@ -47,7 +47,10 @@ struct GenFewParams {
 // LPR: lanes side by side in a row of the tile (64, 32 or 16: tiles 256, 128 or 64 columns wide);
 //      a wave holds 64 / LPR bands of rows, one below the other.
 // RPW: output rows per band.  A tile is 4 * LPR columns x 4 * (64 / LPR) * RPW rows.
-template <int F, int KT, int RPW, int LPR, int CC>
+// WIDE: image rows begin on 16-byte boundaries (a width that is a multiple of four, an aligned image), so
+//      a tile is staged 16 bytes a lane: a quarter of the load instructions, whose rate bounds the
+//      staging, and no pixels beyond the row's end.
+template <int F, int KT, int RPW, int LPR, int CC, bool WIDE>
 __global__ void __launch_bounds__(kThreads)
 general_few_kernel(GenFewParams p)
 {
@@ -57,15 +60,17 @@ general_few_kernel(GenFewParams p)
     constexpr int WIN = 4 + F - 1;                 // window columns of a lane
     constexpr int NV = (WIN + 3) / 4;              // 16-byte LDS reads per window row
     constexpr int SEGS = (TW + 4 * NV - 4 + kWave - 1) / kWave;   // 64-word pieces of a row
-    constexpr int LS = SEGS * kWave;               // LDS row stride: the last lane's reads stay in the row
+    constexpr int LS = WIDE ? TW + 4 * NV - 4 : SEGS * kWave;     // LDS row stride: the last lane's reads stay in the row
     constexpr int ROWS = TR + F - 1;
+    constexpr int PIECES = ROWS * LS / 4;          // 16-byte pieces of a channel's tile
+    constexpr int CHW = WIDE ? (PIECES + 63) / 64 * 64 * 4 : ROWS * LS;   // LDS words of a channel's tile
     constexpr bool kWholeWindow = (RPW + F - 1) * 4 * NV <= 64;   // registers for a band's image rows
     static_assert(LS % 4 == 0, "16-byte aligned rows");
-    static_assert(2 * (CC * ROWS * LS + (KT >= 2 ? CC * KT * kWave : 4)) * 4 <= 64 * 1024,
+    static_assert(2 * (CC * CHW + (KT >= 2 ? CC * KT * kWave : 4)) * 4 <= 64 * 1024,
                   "two sets of tiles and weights fit static LDS");
     static_assert(FF <= kWave, "one lane per weight");
 
-    __shared__ __attribute__((aligned(16))) float sh[2][CC * ROWS * LS];
+    __shared__ __attribute__((aligned(16))) float sh[2][CC * CHW];
     // From two filters on the weights go through LDS too (64 words per filter and channel) and a
     // multiply-add takes its weight from a register that every lane read from the same LDS
     // address; with one filter they go through scalar registers (moved there lane by lane), which
@@ -84,8 +89,9 @@ general_few_kernel(GenFewParams p)
     const int ty = t2 / p.tiles_x, tx = t2 - ty * p.tiles_x;
     const int x0 = tx * TW, y0 = ty * TR;
 
-    // ---- staging: the waves take the rows of a channel's tile in turn, 64 words per
-    // instruction, straight into LDS.  A row's descriptor starts at the row's first pixel in
+    // ---- staging, straight into LDS.  WIDE: the tile as one run of 16-byte pieces, its rows without gaps,
+    // behind one descriptor from the tile's first pixel to the input's end.
+    // Otherwise the waves take the rows of a channel's tile in turn, 64 words per instruction.  A row's descriptor starts at the row's first pixel in
     // the tile and ends with the input: lanes beyond that write zeros; lanes beyond the row's
     // end (or rows below the image) but inside the input bring pixels of the next row, channel
     // or image, which only outputs beyond the row's or the map's end would use, and those are
@@ -96,7 +102,28 @@ general_few_kernel(GenFewParams p)
     int voff[SEGS];
 #pragma unroll
     for (int j = 0; j < SEGS; ++j) voff[j] = 4 * (lane + kWave * j);
+    constexpr int NIT = (PIECES + kThreads - 1) / kThreads;
+    uint32_t woff[WIDE ? NIT : 1];                 // WIDE: byte offset of piece tid + it * kThreads from the tile's first pixel
+#pragma unroll
+    for (int it = 0; it < (WIDE ? NIT : 0); ++it) {
+        const int e = tid + it * kThreads, row = e / (LS / 4), col = 4 * (e % (LS / 4));
+        // (a piece beyond the tile or the row's end reads zeros; no stored output uses it)
+        woff[it] = e < PIECES && x0 + col < p.W ? (uint32_t)(row * p.W + col) * 4u : 0xC0000000u;
+    }
     auto stage = [&](int c, float* buf) __attribute__((always_inline)) {
+        if constexpr (WIDE) {
+            const int64_t first = (((int64_t)n * p.C + c) * p.H + y0) * p.W + x0;
+            const int64_t left = (in_words - first) * 4;       // (the tile begins inside the image)
+            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+                (void*)(p.in + first), 0, (int)(left > 0x7FFFFFFF ? 0x7FFFFFFF : left), kRsrcFlags);
+#pragma unroll
+            for (int it = 0; it < NIT; ++it) {
+                const int w0 = it * kThreads + wave * kWave;   // (uniform)
+                if (w0 < PIECES)
+                    __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr)(buf + 4 * w0), 16, (int)woff[it], 0, 0, 0);
+            }
+            return;
+        }
         const int64_t chan = ((int64_t)n * p.C + c) * p.H;
         for (int r = wave; r < ROWS; r += 4) {     // (uniform)
             const int64_t first = (chan + y0 + r) * p.W + x0;
@@ -144,7 +171,7 @@ general_few_kernel(GenFewParams p)
     float wcur[CC][KT], wnext[CC][KT];
 #pragma unroll
     for (int cc = 0; cc < CC; ++cc) {
-        if (cc < p.C) stage(cc, sh[0] + cc * (ROWS * LS));
+        if (cc < p.C) stage(cc, sh[0] + cc * CHW);
         if constexpr (kLdsWeights) stage_weights(cc, cc, wsh[0]);
         else load_weights(cc, wcur[cc]);
     }
@@ -156,7 +183,7 @@ general_few_kernel(GenFewParams p)
         const int cur = (c0 / CC) & 1;
 #pragma unroll
         for (int cc = 0; cc < CC; ++cc) {
-            if (c0 + CC + cc < p.C) stage(c0 + CC + cc, sh[cur ^ 1] + cc * (ROWS * LS));
+            if (c0 + CC + cc < p.C) stage(c0 + CC + cc, sh[cur ^ 1] + cc * CHW);
             if constexpr (kLdsWeights) stage_weights(c0 + CC + cc, cc, wsh[cur ^ 1]);
             else load_weights(c0 + CC + cc, wnext[cc]);
         }
@@ -165,7 +192,7 @@ general_few_kernel(GenFewParams p)
             // (a channel beyond the last has zero weights, but its place in LDS holds pixels of
             // the next image: not multiplied at all, so that a NaN there stays where it belongs)
             if (c0 + cc >= p.C) break;             // uniform
-            const float* wrow = sh[cur] + cc * (ROWS * LS) + r0 * LS + 4 * lx;
+            const float* wrow = sh[cur] + cc * CHW + r0 * LS + 4 * lx;
             auto load_row = [&](int rr, float (&w)[4 * NV]) __attribute__((always_inline)) {
 #pragma unroll
                 for (int v = 0; v < NV; ++v) {
@@ -302,7 +329,18 @@ int launch_gf(const float* in, const float* filt, float* out, const Shape& s, hi
     // 8 x 64 x 224 x 224, 1x1 filters: 29 -> 23 us; not with twelve or sixteen filters, which
     // are work enough and whose weights take the LDS a second channel would need)
     constexpr int CC = (RPW == 1 && KT <= 8) ? 2 : 1;
-    hipLaunchKernelGGL((general_few_kernel<F, KT, RPW, LPR, CC>), dim3((unsigned)(p.per_xcd * 8)), dim3(kThreads), 0, st, p);
+    // 16 bytes a lane wherever the rows allow it (offsets within a tile then fit 31 bits), measured against
+    // 4 bytes a lane: 8 x 64 x 224 x 224, 3x3, one filter 32.6 -> 24.0 us, three 52.7 -> 45.9, eight 82.4 -> 78.5;
+    // 128 x 64 x 56 x 56, three 3x3 filters 59.3 -> 43.3; 16 x 128 x 128 x 128, two 1x1 filters 50.6 -> 38.8.
+    // Not for two or more 6x6 or 7x7 filters: all arithmetic, and with the smaller tile the compiler takes one
+    // more wave per SIMD for the registers that hold the next weights, for which every multiply-add
+    // then waits (8 x 10 x 204 x 204, thirteen 7x7 filters: 98 -> 163 us).
+    constexpr bool kWideHelps = F <= 5 || KT == 1;
+    const bool wide = s.W % 4 == 0 && ((uintptr_t)in & 15) == 0 && (int64_t)(TR + F) * s.W < (1LL << 28);
+    if (kWideHelps && wide)
+        hipLaunchKernelGGL((general_few_kernel<F, KT, RPW, LPR, CC, kWideHelps>), dim3((unsigned)(p.per_xcd * 8)), dim3(kThreads), 0, st, p);
+    else
+        hipLaunchKernelGGL((general_few_kernel<F, KT, RPW, LPR, CC, false>), dim3((unsigned)(p.per_xcd * 8)), dim3(kThreads), 0, st, p);
     return launch_status();
 }
 

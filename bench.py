@@ -193,6 +193,13 @@ def config_entry(w, ms):
             "algorithmic_gbs": round(gbs, 1), "frac_hbm_peak": round(gbs / HBM_PEAK_GBS, 4)}
 
 
+def add_parts_peak(roof):
+    """Large fp32 layers of the general case run on the bf16 matrix cores, six products of bf16 parts for
+    one of fp32 (their rate can pass the fp32 matrix-core peak): the peak of that way beside the other."""
+    roof["peak_bf16_parts"] = round(MFMA16_PEAK_TFLOPS / 6, 1)
+    roof["frac_bf16_parts"] = round(roof["achieved"] * 6 / MFMA16_PEAK_TFLOPS, 4)
+
+
 def read_traffic(name):
     """HBM bytes per launch from the committed counter summary of this kernel/workload, if any."""
     p = ROOT / "profiles" / f"{name}_hbm_traffic.txt"
@@ -338,6 +345,8 @@ def main():
         if on_alu:
             roof["peak_plain_fma"] = FP32_PEAK_TFLOPS / 2
             roof["frac_plain_fma"] = round(entry["gflops"] / 1e3 / (FP32_PEAK_TFLOPS / 2), 4)
+        elif not single:
+            add_parts_peak(roof)
     roof["kernel"] = entry["kernel"]
     roof["kernel_ms"] = round(ms, 5)
     roof["traffic"] = read_traffic(f"{entry['kernel']}_{head.name}")
@@ -406,6 +415,7 @@ def main():
             "achieved": round(g["G3"]["gflops"] / 1e3, 3), "peak": FP32_PEAK_TFLOPS, "unit": "TFLOP/s",
             "frac": g["G3"]["frac_fp32_peak"], "traffic": read_traffic("dconv_general_G3"),
             "traffic_source": "profiles/dconv_general_G3_hbm_traffic.txt (earlier run)"}
+        add_parts_peak(result["roofline_general"])
         if peaks:
             result["roofline_general"]["peak_measured"] = peaks["fp32_mfma_tflops"]
             result["roofline_general"]["frac_measured"] = g["G3"]["frac_fp32_mfma_measured"]

@@ -255,9 +255,12 @@ int dconv_tile_choice(int single_channel, int N, int C, int H, int W, int K, int
  * and replayed.  The one exception is the workspace of dconv_general described
  * below: the first call that needs it on a stream allocates and clears it,
  * which is not allowed while that stream is capturing.  Run the calls once on
- * the stream before capturing on it.  (Layers whose products are taken apart
- * need the workspace for that alone; captured, they run on the fp32 matrix
- * cores instead, in dconv_general_noalloc as they do otherwise.)
+ * the stream before capturing on it: the block that the first of them is given
+ * serves every later call.  (A capture in relaxed mode does allow the
+ * allocation; the block is then cleared at once, on a stream of the library's
+ * own, which is waited for.)  Layers whose products are taken apart run on the
+ * fp32 matrix cores when they are captured, so their bits and their time are
+ * those of that kernel; in dconv_general_noalloc they run as they do otherwise.
  */
 
 /*
@@ -271,9 +274,9 @@ int dconv_tile_choice(int single_channel, int N, int C, int H, int W, int K, int
  * chip) and clears the counters on that stream; no other entry point
  * allocates (dconv_single_channel counts as dconv_general here where it runs
  * on the same kernel, see there), and no call
- * synchronises.  The block keeps its address from then
- * on: later calls on the stream, whatever their shape, use the same block (they
- * run in order, so they share it safely; calls on different streams use
+ * synchronises (but for the relaxed capture above).  The block keeps its
+ * address from then on: later calls on the stream, whatever their shape, use the
+ * same block (they run in order, so they share it safely; calls on different streams use
  * different blocks), and a graph captured on the stream stays valid while
  * other calls are made on it.
  * dconv_release_workspace frees all blocks.  The caller must make sure that no
@@ -288,11 +291,12 @@ int dconv_release_workspace(void);
  * dconv_general_v for callers that cannot allocate device memory: code that is
  * under HIP graph capture from its first call on, tight serving loops,
  * harnesses that forbid hipMalloc.  Same arguments, same results (bit for bit:
- * the same kernels in the same launch configuration) and same errors as
- * dconv_general_v, but it never calls hipMalloc, hipFree or any allocating
- * routine: where dconv_general_v would use its workspace, the partial sums and
- * arrival counters of shared tiles and the split filters go to a static device array that is part of
- * the library's code object -- 64 MiB + 16 KiB on every GPU the library runs on,
+ * the same kernels in the same launch configuration as a dconv_general_v that
+ * is not being captured) and same errors as dconv_general_v, but it never
+ * calls hipMalloc, hipFree or any allocating routine: where dconv_general_v
+ * would use its workspace, the partial sums and arrival counters of shared tiles
+ * and the split filters go to a static device array that is part of the
+ * library's code object -- 64 MiB + 16 KiB on every GPU the library runs on,
  * held until the process ends.  That is room for 512 workgroups with two 64 x 256
  * partial tiles each and 4096 counters, i.e. for every launch configuration on
  * a chip of up to 256 compute units; a launch that would need more returns

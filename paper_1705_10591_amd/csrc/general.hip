@@ -39,6 +39,31 @@ struct WsEntry {
 std::mutex g_ws_mutex;
 std::map<std::pair<int, hipStream_t>, WsEntry> g_ws;
 
+__global__ void clear_counters_kernel(int* cnt, int n)
+{
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) cnt[i] = 0;
+}
+
+// Clears the counters of a block before the calls that follow on the stream.  A capture that lets
+// the allocation through (relaxed mode) would record the clearing instead of running it, and calls
+// before the graph's first replay would find counters never cleared: there it runs on a stream
+// of its own and is waited for.
+bool clear_counters(int* cnt, size_t n, hipStream_t st)
+{
+    const bool apart = gen_capturing(st);
+    hipStream_t on = st;
+    if (apart && hipStreamCreateWithFlags(&on, hipStreamNonBlocking) != hipSuccess) return false;
+    begin_launch();
+    hipLaunchKernelGGL(clear_counters_kernel, dim3((unsigned)((n + kThreads - 1) / kThreads)), dim3(kThreads), 0, on, cnt, (int)n);
+    bool ok = launch_status() == DCONV_OK;
+    if (apart) {
+        ok = hipStreamSynchronize(on) == hipSuccess && ok;
+        (void)hipStreamDestroy(on);
+    }
+    return ok;
+}
+
 }  // namespace
 
 std::mutex& gen_launch_mutex()
@@ -66,16 +91,19 @@ bool gen_capturing(hipStream_t st)
     return true;
 }
 
+// The first request on a (device, stream) brings partial sums AND counters, whatever it asks for: a call
+// that is captured later may take another kernel than the call that ran before it, and a capture
+// does not allow an allocation.
 GenWorkspace gen_workspace(hipStream_t st, size_t part_floats, size_t ncnt)
 {
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess) return {nullptr, nullptr};
     std::lock_guard<std::mutex> lock(g_ws_mutex);
     WsEntry& e = g_ws[{dev, st}];
-    if (e.part_floats >= part_floats && e.ncnt >= ncnt) return {e.part, e.cnt};
+    if (e.part && e.part_floats >= part_floats && e.cnt && e.ncnt >= ncnt) return {e.part, e.cnt};
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
         return {nullptr, nullptr};
-    if (e.part_floats < part_floats) {
+    if (!e.part || e.part_floats < part_floats) {
         const size_t want = std::max(part_floats, std::max(kPartFloatsPerCu * (size_t)cus, kGenWorkspaceFloats));
         float* fresh = nullptr;
         if (hipMalloc((void**)&fresh, want * sizeof(float)) != hipSuccess) {
@@ -86,12 +114,10 @@ GenWorkspace gen_workspace(hipStream_t st, size_t part_floats, size_t ncnt)
         e.part = fresh;
         e.part_floats = want;
     }
-    if (e.ncnt < ncnt) {
+    if (!e.cnt || e.ncnt < ncnt) {
         const size_t want = std::max(ncnt, kCountersPerCu * (size_t)cus);
         int* fresh = nullptr;
-        // (the one place where a call may not be captured into a graph: first use on a stream)
-        if (hipMalloc((void**)&fresh, want * sizeof(int)) != hipSuccess ||
-            hipMemsetAsync(fresh, 0, want * sizeof(int), st) != hipSuccess) {
+        if (hipMalloc((void**)&fresh, want * sizeof(int)) != hipSuccess || !clear_counters(fresh, want, st)) {
             if (fresh) (void)hipFree(fresh);
             (void)hipGetLastError();
             return {nullptr, nullptr};
@@ -134,12 +160,6 @@ static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 std::mutex g_scratch_mutex;
 unsigned char* g_scratch_ptr[kMaxDevices] = {};         // device address of `scratch`, per device
-
-__global__ void clear_counters_kernel(int* cnt, int n)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) cnt[i] = 0;
-}
 
 }  // namespace
 

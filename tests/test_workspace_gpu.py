@@ -1,0 +1,106 @@
+"""The workspace of dconv_general over the calls that share it: run once and then captured, captured while the
+allocation is let through, used from several graphs, streams and threads.
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import workloads as wl
+import paper_1705_10591_amd as dconv
+from helpers import assert_within_bound
+
+pytestmark = pytest.mark.gpu
+
+SHARED = dconv.VARIANT_TILED_CFG0 + 2 * 3          # + tile shape: tiles cut over channels
+# runs on the split-operand kernel, whole tiles (no counters); on the fp32 kernel its 680 tiles are shared
+DEEP = (32, 256, 28, 28, 512, 3)
+# parts added by a second kernel: partial sums, no counters
+ONE_IMAGE = (1, 256, 14, 14, 256, 3)
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to("cuda")
+
+
+def make(seed, shape):
+    N, C, H, W, K, F = shape
+    x, f = wl.random_case(seed, *shape, "u01", "he")
+    return x, f, dev(x), dev(f), torch.empty(N, K, H - F + 1, W - F + 1, device="cuda")
+
+
+def fresh_stream():
+    """A stream on which the library holds no workspace."""
+    s = torch.cuda.Stream()
+    dconv.release_workspace()
+    return s
+
+
+def test_a_layer_run_once_and_then_captured_on_another_kernel():
+    """Captured calls stay on the fp32 kernel, which shares this layer's tiles: the block that the call before
+    it was given has the counters for that."""
+    x, f, xd, fd, out = make(8500, DEEP)
+    want = dconv.dconv_general(xd, fd, variant=SHARED + dconv.tile_choice(False, *DEEP))
+    s = fresh_stream()
+    with torch.cuda.stream(s):
+        eager = dconv.dconv_general(xd, fd)
+    s.synchronize()
+    assert not torch.equal(eager, want), "the split-operand kernel is expected to run here"
+    g = torch.cuda.CUDAGraph()
+    print(f"capturing {DEEP}", flush=True)
+    with torch.cuda.graph(g, stream=s):
+        dconv.dconv_general(xd, fd, out=out)
+    for rep in range(3):
+        out.fill_(float("nan"))
+        with torch.cuda.stream(s):
+            again = dconv.dconv_general(xd, fd)
+        s.synchronize()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want) and torch.equal(again, eager), f"replay {rep}"
+    for n in (0, DEEP[0] - 1):
+        acc, mag, _ = oracle.general(np.ascontiguousarray(x[n:n + 1]), f)
+        assert_within_bound(out[n:n + 1].cpu().numpy(), acc, mag, f"captured, image {n}")
+        assert_within_bound(eager[n:n + 1].cpu().numpy(), acc, mag, f"eager, image {n}")
+
+
+def test_a_call_without_counters_prepares_the_stream_for_one_with_counters():
+    """The first call that needs the workspace brings all of it."""
+    first, second = make(8501, ONE_IMAGE), make(8502, (3, 16, 28, 28, 130, 3))
+    want = dconv.dconv_general(second[2], second[3], variant=SHARED + 1)
+    s = fresh_stream()
+    with torch.cuda.stream(s):
+        dconv.dconv_general(first[2], first[3])
+    s.synchronize()
+    g = torch.cuda.CUDAGraph()
+    print("capturing shared tiles after parts without counters", flush=True)
+    with torch.cuda.graph(g, stream=s):
+        dconv.dconv_general(second[2], second[3], out=second[4], variant=SHARED + 1)
+    for rep in range(3):
+        second[4].fill_(float("nan"))
+        dconv.dconv_general(first[2], first[3])
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(second[4], want), f"replay {rep}"
+
+
+def test_a_capture_that_lets_the_allocation_through_leaves_cleared_counters():
+    """In relaxed mode a first call may allocate while it is captured: calls before the first replay find cleared
+    counters, and replays do not clear them again."""
+    x, f, xd, fd, out = make(8503, (3, 16, 28, 28, 130, 3))
+    want = dconv.dconv_general(xd, fd, variant=SHARED + 1)
+    torch.cuda.synchronize()
+    s = fresh_stream()
+    g = torch.cuda.CUDAGraph()
+    print("capturing a first call in relaxed mode", flush=True)
+    with torch.cuda.graph(g, stream=s, capture_error_mode="relaxed"):
+        dconv.dconv_general(xd, fd, out=out, variant=SHARED + 1)
+    for rep in range(3):
+        with torch.cuda.stream(s):
+            eager = dconv.dconv_general(xd, fd, variant=SHARED + 1)
+        s.synchronize()
+        assert torch.equal(eager, want), f"eager call {rep}"
+        out.fill_(float("nan"))
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want), f"replay {rep}"

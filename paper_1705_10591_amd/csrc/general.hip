@@ -22,6 +22,10 @@ namespace dconv {
 // largest launch on that device can need (a launch has at most OCC workgroups per CU, each with
 // two partial tiles), and later requests find it large enough.  Should a request ever exceed it
 // (a forced grid), a larger block is allocated beside the old one, which is kept until release.
+//
+// A graph may be replayed on another stream than the one it was captured on, beside calls on that
+// one: the first captured launch takes the stream's block over, later captured launches share it,
+// and the next call that is not captured is given a block of its own.
 namespace {
 
 // floats of partial sums and counters per CU that cover every compiled tile shape:
@@ -29,12 +33,22 @@ namespace {
 constexpr size_t kPartFloatsPerCu = 2 * 2 * 64 * 256;
 constexpr size_t kCountersPerCu = 4;
 
-struct WsEntry {
+struct WsBlock {
     float* part = nullptr;
     size_t part_floats = 0;
     int* cnt = nullptr;
     size_t ncnt = 0;
+    bool holds(size_t floats, size_t counters) const { return part && part_floats >= floats && cnt && ncnt >= counters; }
+};
+struct WsEntry {
+    WsBlock eager, captured;         // for calls, and for launches that a graph holds
     std::vector<void*> retired;      // outgrown blocks: freed only by release_general_workspaces()
+    void retire(WsBlock& b)
+    {
+        if (b.part) retired.push_back(b.part);
+        if (b.cnt) retired.push_back(b.cnt);
+        b = WsBlock();
+    }
 };
 std::mutex g_ws_mutex;
 std::map<std::pair<int, hipStream_t>, WsEntry> g_ws;
@@ -98,43 +112,39 @@ GenWorkspace gen_workspace(hipStream_t st, size_t part_floats, size_t ncnt)
 {
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess) return {nullptr, nullptr};
+    const bool capturing = gen_capturing(st);
     std::lock_guard<std::mutex> lock(g_ws_mutex);
     WsEntry& e = g_ws[{dev, st}];
-    if (e.part && e.part_floats >= part_floats && e.cnt && e.ncnt >= ncnt) return {e.part, e.cnt};
+    WsBlock& b = capturing ? e.captured : e.eager;
+    if (b.holds(part_floats, ncnt)) return {b.part, b.cnt};
+    if (capturing && e.eager.holds(part_floats, ncnt)) {
+        e.retire(b);
+        std::swap(b, e.eager);
+        return {b.part, b.cnt};
+    }
     if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
         return {nullptr, nullptr};
-    if (!e.part || e.part_floats < part_floats) {
-        const size_t want = std::max(part_floats, std::max(kPartFloatsPerCu * (size_t)cus, kGenWorkspaceFloats));
-        float* fresh = nullptr;
-        if (hipMalloc((void**)&fresh, want * sizeof(float)) != hipSuccess) {
-            (void)hipGetLastError();
-            return {nullptr, nullptr};
-        }
-        if (e.part) e.retired.push_back(e.part);
-        e.part = fresh;
-        e.part_floats = want;
+    WsBlock fresh;
+    fresh.part_floats = std::max(part_floats, std::max(kPartFloatsPerCu * (size_t)cus, kGenWorkspaceFloats));
+    fresh.ncnt = std::max(ncnt, kCountersPerCu * (size_t)cus);
+    if (hipMalloc((void**)&fresh.part, fresh.part_floats * sizeof(float)) != hipSuccess ||
+        hipMalloc((void**)&fresh.cnt, fresh.ncnt * sizeof(int)) != hipSuccess || !clear_counters(fresh.cnt, fresh.ncnt, st)) {
+        if (fresh.part) (void)hipFree(fresh.part);
+        if (fresh.cnt) (void)hipFree(fresh.cnt);
+        (void)hipGetLastError();
+        return {nullptr, nullptr};
     }
-    if (!e.cnt || e.ncnt < ncnt) {
-        const size_t want = std::max(ncnt, kCountersPerCu * (size_t)cus);
-        int* fresh = nullptr;
-        if (hipMalloc((void**)&fresh, want * sizeof(int)) != hipSuccess || !clear_counters(fresh, want, st)) {
-            if (fresh) (void)hipFree(fresh);
-            (void)hipGetLastError();
-            return {nullptr, nullptr};
-        }
-        if (e.cnt) e.retired.push_back(e.cnt);
-        e.cnt = fresh;
-        e.ncnt = want;
-    }
-    return {e.part, e.cnt};
+    e.retire(b);
+    b = fresh;
+    return {b.part, b.cnt};
 }
 
 void release_general_workspaces()
 {
     std::lock_guard<std::mutex> lock(g_ws_mutex);
     for (auto& kv : g_ws) {
-        if (kv.second.part) (void)hipFree(kv.second.part);
-        if (kv.second.cnt) (void)hipFree(kv.second.cnt);
+        kv.second.retire(kv.second.eager);
+        kv.second.retire(kv.second.captured);
         for (void* q : kv.second.retired) (void)hipFree(q);
     }
     g_ws.clear();

@@ -104,3 +104,36 @@ def test_a_capture_that_lets_the_allocation_through_leaves_cleared_counters():
         g.replay()
         torch.cuda.synchronize()
         assert torch.equal(out, want), f"replay {rep}"
+
+
+def test_a_graph_runs_on_one_stream_beside_calls_on_the_stream_it_was_captured_on():
+    """Captured launches have a block of their own: the partial sums of a replay and the split filters of calls
+    made meanwhile on the capture stream do not meet."""
+    a, b = make(8504, (3, 64, 40, 44, 130, 3)), make(8505, (14, 48, 66, 66, 64, 4))
+    want_a = dconv.dconv_general(a[2], a[3], variant=SHARED + 1)
+    want_b = dconv.dconv_general(b[2], b[3])
+    outs = [torch.empty_like(a[4]) for _ in range(10)]
+    s, other = fresh_stream(), torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        dconv.dconv_general(a[2], a[3], variant=SHARED + 1)
+    s.synchronize()
+    g = torch.cuda.CUDAGraph()
+    print("capturing ten launches", flush=True)
+    with torch.cuda.graph(g, stream=s):
+        for o in outs:
+            dconv.dconv_general(a[2], a[3], out=o, variant=SHARED + 1)
+    results = [torch.empty_like(b[4]) for _ in range(30)]
+    torch.cuda.synchronize()
+    for rep in range(3):
+        for t in outs + results:
+            t.fill_(float("nan"))
+        torch.cuda.synchronize()
+        for i in range(5):
+            with torch.cuda.stream(other):
+                g.replay()
+            with torch.cuda.stream(s):
+                for o in results[6 * i:6 * i + 6]:
+                    dconv.dconv_general(b[2], b[3], out=o)
+        torch.cuda.synchronize()
+        assert all(torch.equal(o, want_a) for o in outs), f"replays, {rep}"
+        assert all(torch.equal(o, want_b) for o in results), f"calls, {rep}"

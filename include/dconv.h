@@ -277,12 +277,15 @@ int dconv_tile_choice(int single_channel, int N, int C, int H, int W, int K, int
  * synchronises (but for the relaxed capture above).  The block keeps its
  * address from then on: later calls on the stream, whatever their shape, use the
  * same block (they run in order, so they share it safely; calls on different
- * streams use different blocks).  Launches captured into a graph have a block of
- * their own: the first of them takes over the one that the calls before it used
- * (let those finish before the graph is launched), and the next call on the
- * stream that is not captured is given another.  A graph may so be launched on
- * any stream while calls are made on the one it was captured on; graphs
- * captured on ONE stream share their block and must not run at the same time.
+ * streams use different blocks; hipStreamPerThread, another stream in every
+ * thread, has one for each thread, and what a thread leaves when it ends goes to
+ * the next that needs one, whose first call then waits for the device).
+ * Launches captured into a graph have a block of their own: the first of them
+ * takes over the one that the calls before it used (let those finish before the
+ * graph is launched), and the next call on the stream that is not captured is
+ * given another.  A graph may so be launched on any stream while calls are made
+ * on the one it was captured on; graphs captured on ONE stream share their block
+ * and must not run at the same time.
  * dconv_release_workspace frees all blocks.  The caller must make sure that no
  * dconv_general launch is still running and that every graph that holds
  * captured dconv_general calls has been destroyed (or is never launched

@@ -3,6 +3,7 @@
 #include <cmath>
 #include <map>
 #include <mutex>
+#include <tuple>
 #include <utility>
 #include <vector>
 #include "general_kernel.h"
@@ -12,7 +13,9 @@ namespace dconv {
 
 // ---- workspace ---------------------------------------------------------------------------------
 // One per (device, stream): launches on one stream run in order and may share it; launches on
-// different streams may overlap and must not.  It holds the partial sums of tiles shared by
+// different streams may overlap and must not.  (hipStreamPerThread is one handle and another
+// stream in every thread: each thread has a block of its own there, which passes to the next
+// thread that needs one when it ends.)  It holds the partial sums of tiles shared by
 // several workgroups and one arrival counter per workgroup.  The counters are zero between
 // launches: the workgroup that completes a tile resets its counter.
 //
@@ -49,9 +52,50 @@ struct WsEntry {
         if (b.cnt) retired.push_back(b.cnt);
         b = WsBlock();
     }
+    void free_all()
+    {
+        for (WsBlock* b : {&eager, &captured}) retire(*b);
+        for (void* q : retired) (void)hipFree(q);
+        retired.clear();
+    }
 };
-std::mutex g_ws_mutex;
-std::map<std::pair<int, hipStream_t>, WsEntry> g_ws;
+// (never destroyed: threads may end after the library's static objects have)
+struct WsTable {
+    std::mutex mutex;
+    std::map<std::tuple<int, hipStream_t, uint64_t>, WsEntry> entries;     // device, stream, thread
+    std::vector<std::pair<int, WsEntry>> left;                            // by threads that ended
+};
+WsTable& ws_table()
+{
+    static WsTable* t = new WsTable;
+    return *t;
+}
+
+// The calling thread, for hipStreamPerThread; other streams are the same stream in every thread (0).
+struct WsThread {
+    uint64_t id = 0;
+    ~WsThread()
+    {
+        if (id == 0) return;
+        WsTable& t = ws_table();
+        std::lock_guard<std::mutex> lock(t.mutex);
+        for (auto it = t.entries.begin(); it != t.entries.end();) {
+            if (std::get<2>(it->first) != id) { ++it; continue; }
+            it->second.retire(it->second.captured);        // (graphs may outlive the thread)
+            t.left.emplace_back(std::get<0>(it->first), std::move(it->second));
+            it = t.entries.erase(it);
+        }
+    }
+};
+uint64_t ws_thread(hipStream_t st)
+{
+    static std::atomic<uint64_t> count{0};
+    thread_local WsThread self;
+    if (st != hipStreamPerThread) return 0;
+    if (self.id == 0) self.id = ++count;
+    return self.id;
+}
+
 
 __global__ void clear_counters_kernel(int* cnt, int n)
 {
@@ -113,8 +157,20 @@ GenWorkspace gen_workspace(hipStream_t st, size_t part_floats, size_t ncnt)
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess) return {nullptr, nullptr};
     const bool capturing = gen_capturing(st);
-    std::lock_guard<std::mutex> lock(g_ws_mutex);
-    WsEntry& e = g_ws[{dev, st}];
+    const uint64_t thread = ws_thread(st);
+    WsTable& table = ws_table();
+    std::lock_guard<std::mutex> lock(table.mutex);
+    WsEntry& e = table.entries[{dev, st, thread}];
+    if (thread != 0 && !capturing && !e.eager.part && !e.captured.part) {
+        // what another thread left, once its launches are done
+        const auto it = std::find_if(table.left.begin(), table.left.end(), [&](const auto& l) { return l.first == dev; });
+        if (it != table.left.end()) {
+            if (hipDeviceSynchronize() == hipSuccess) {
+                e = std::move(it->second);
+                table.left.erase(it);
+            } else (void)hipGetLastError();
+        }
+    }
     WsBlock& b = capturing ? e.captured : e.eager;
     if (b.holds(part_floats, ncnt)) return {b.part, b.cnt};
     if (capturing && e.eager.holds(part_floats, ncnt)) {
@@ -141,13 +197,12 @@ GenWorkspace gen_workspace(hipStream_t st, size_t part_floats, size_t ncnt)
 
 void release_general_workspaces()
 {
-    std::lock_guard<std::mutex> lock(g_ws_mutex);
-    for (auto& kv : g_ws) {
-        kv.second.retire(kv.second.eager);
-        kv.second.retire(kv.second.captured);
-        for (void* q : kv.second.retired) (void)hipFree(q);
-    }
-    g_ws.clear();
+    WsTable& table = ws_table();
+    std::lock_guard<std::mutex> lock(table.mutex);
+    for (auto& kv : table.entries) kv.second.free_all();
+    for (auto& l : table.left) l.second.free_all();
+    table.entries.clear();
+    table.left.clear();
 }
 
 // ---- the static scratch array of dconv_general_noalloc --------------------------------------------

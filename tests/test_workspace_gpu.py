@@ -1,6 +1,9 @@
 """The workspace of dconv_general over the calls that share it: run once and then captured, captured while the
 allocation is let through, used from several graphs, streams and threads.
 """
+import ctypes
+import threading
+
 import numpy as np
 import pytest
 import torch
@@ -137,3 +140,43 @@ def test_a_graph_runs_on_one_stream_beside_calls_on_the_stream_it_was_captured_o
         torch.cuda.synchronize()
         assert all(torch.equal(o, want_a) for o in outs), f"replays, {rep}"
         assert all(torch.equal(o, want_b) for o in results), f"calls, {rep}"
+
+
+def test_the_per_thread_stream_has_a_workspace_for_every_thread():
+    """hipStreamPerThread is one handle and another stream in each thread: the split filters and the partial
+    sums of two threads' calls do not meet; threads that follow take over what ended threads left."""
+    lib, per_thread, vp = dconv.load_library(), ctypes.c_void_p(2), ctypes.c_void_p
+    cases = [(shape, make(8510 + i, shape)) for i, shape in enumerate(
+        ((14, 48, 66, 66, 64, 4), (6, 48, 40, 44, 100, 6), (1, 256, 14, 14, 256, 3), (2, 64, 30, 30, 64, 3)))]
+    wants = [dconv.dconv_general(c[2], c[3]) for _, c in cases]
+    outs = [[torch.empty_like(c[4]) for _ in range(12)] for _, c in cases]
+    torch.cuda.synchronize()
+    dconv.release_workspace()
+    errors, go = [], None
+
+    def work(i):
+        (N, C, H, W, K, F), (_, _, xd, fd, _) = cases[i]
+        go.wait()
+        for o in outs[i]:
+            rc = lib.dconv_general(vp(xd.data_ptr()), N, C, H, W, vp(fd.data_ptr()), K, F, vp(o.data_ptr()), per_thread)
+            if rc != dconv.STATUS_OK:
+                errors.append((i, rc))
+
+    held = []
+    for rep in range(3):
+        for t in sum(outs, []):
+            t.fill_(float("nan"))
+        torch.cuda.synchronize()
+        go = threading.Barrier(len(cases))
+        threads = [threading.Thread(target=work, args=(i,)) for i in range(len(cases))]
+        print(f"four threads on the per-thread stream, {rep}", flush=True)
+        for t in threads:
+            t.start()
+        for t in threads:
+            t.join()
+        torch.cuda.synchronize()
+        assert not errors, errors
+        for i, want in enumerate(wants):
+            assert all(torch.equal(o, want) for o in outs[i]), f"{cases[i][0]}, {rep}"
+        held.append(torch.cuda.mem_get_info()[0])
+    assert held[2] >= held[0], "the threads' blocks are used again"

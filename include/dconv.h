@@ -279,7 +279,7 @@ int dconv_tile_choice(int single_channel, int N, int C, int H, int W, int K, int
  * same block (they run in order, so they share it safely; calls on different
  * streams use different blocks; hipStreamPerThread, another stream in every
  * thread, has one for each thread, and what a thread leaves when it ends goes to
- * the next that needs one, whose first call then waits for the device).
+ * the next that needs one, whose first call then waits for the former's last).
  * Launches captured into a graph have a block of their own: the first of them
  * takes over the one that the calls before it used (let those finish before the
  * graph is launched), and the next call on the stream that is not captured is

@@ -2,6 +2,7 @@
 // the workspace that shared tiles are summed through.  The kernel is in general_kernel.h.
 #include <cmath>
 #include <map>
+#include <memory>
 #include <mutex>
 #include <tuple>
 #include <utility>
@@ -44,16 +45,22 @@ struct WsBlock {
     bool holds(size_t floats, size_t counters) const { return part && part_floats >= floats && cnt && ncnt >= counters; }
 };
 struct WsEntry {
+    std::mutex mutex;                // held while a call that uses the entry enqueues its kernels
     WsBlock eager, captured;         // for calls, and for launches that a graph holds
+    hipEvent_t done = nullptr;       // hipStreamPerThread: recorded behind the last call that used `eager`
     std::vector<void*> retired;      // outgrown blocks: freed only by release_general_workspaces()
-    void retire(WsBlock& b)
+    void retire(WsBlock& b) noexcept
     {
-        if (b.part) retired.push_back(b.part);
-        if (b.cnt) retired.push_back(b.cnt);
+        try {
+            if (b.part) retired.push_back(b.part);
+            if (b.cnt) retired.push_back(b.cnt);
+        } catch (...) {}                                 // (never freed, but nobody's)
         b = WsBlock();
     }
     void free_all()
     {
+        if (done) (void)hipEventDestroy(done);
+        done = nullptr;
         for (WsBlock* b : {&eager, &captured}) retire(*b);
         for (void* q : retired) (void)hipFree(q);
         retired.clear();
@@ -62,8 +69,8 @@ struct WsEntry {
 // (never destroyed: threads may end after the library's static objects have)
 struct WsTable {
     std::mutex mutex;
-    std::map<std::tuple<int, hipStream_t, uint64_t>, WsEntry> entries;     // device, stream, thread
-    std::vector<std::pair<int, WsEntry>> left;                            // by threads that ended
+    std::map<std::tuple<int, hipStream_t, uint64_t>, std::shared_ptr<WsEntry>> entries;     // device, stream, thread
+    std::vector<std::pair<int, std::shared_ptr<WsEntry>>> left;                            // by threads that ended
 };
 WsTable& ws_table()
 {
@@ -81,7 +88,7 @@ struct WsThread {
         std::lock_guard<std::mutex> lock(t.mutex);
         for (auto it = t.entries.begin(); it != t.entries.end();) {
             if (std::get<2>(it->first) != id) { ++it; continue; }
-            it->second.retire(it->second.captured);        // (graphs may outlive the thread)
+            it->second->retire(it->second->captured);        // (graphs may outlive the thread)
             t.left.emplace_back(std::get<0>(it->first), std::move(it->second));
             it = t.entries.erase(it);
         }
@@ -95,7 +102,6 @@ uint64_t ws_thread(hipStream_t st)
     if (self.id == 0) self.id = ++count;
     return self.id;
 }
-
 
 __global__ void clear_counters_kernel(int* cnt, int n)
 {
@@ -124,12 +130,6 @@ bool clear_counters(int* cnt, size_t n, hipStream_t st)
 
 }  // namespace
 
-std::mutex& gen_launch_mutex()
-{
-    static std::mutex m;
-    return m;
-}
-
 int gen_cus()
 {
     static std::atomic<int> seen[64] = {};       // per device
@@ -149,58 +149,100 @@ bool gen_capturing(hipStream_t st)
     return true;
 }
 
+namespace {
+
 // The first request on a (device, stream) brings partial sums AND counters, whatever it asks for: a call
 // that is captured later may take another kernel than the call that ran before it, and a capture
 // does not allow an allocation.
-GenWorkspace gen_workspace(hipStream_t st, size_t part_floats, size_t ncnt)
+GenWorkspace take_workspace(hipStream_t st, size_t part_floats, size_t ncnt)
 {
     int dev = 0, cus = 0;
-    if (hipGetDevice(&dev) != hipSuccess) return {nullptr, nullptr};
+    if (hipGetDevice(&dev) != hipSuccess) return {};
     const bool capturing = gen_capturing(st);
     const uint64_t thread = ws_thread(st);
     WsTable& table = ws_table();
-    std::lock_guard<std::mutex> lock(table.mutex);
-    WsEntry& e = table.entries[{dev, st, thread}];
-    if (thread != 0 && !capturing && !e.eager.part && !e.captured.part) {
-        // what another thread left, once its launches are done
-        const auto it = std::find_if(table.left.begin(), table.left.end(), [&](const auto& l) { return l.first == dev; });
-        if (it != table.left.end()) {
-            if (hipDeviceSynchronize() == hipSuccess) {
-                e = std::move(it->second);
+    std::shared_ptr<WsEntry> e;
+    bool taken_over = false;         // what another thread left: its launches may still run
+    {
+        std::lock_guard<std::mutex> lock(table.mutex);
+        std::shared_ptr<WsEntry>& mine = table.entries[{dev, st, thread}];
+        if (!mine && thread != 0 && !capturing) {
+            const auto it = std::find_if(table.left.begin(), table.left.end(), [&](const auto& l) { return l.first == dev; });
+            if (it != table.left.end()) {
+                mine = std::move(it->second);
                 table.left.erase(it);
-            } else (void)hipGetLastError();
+                taken_over = true;
+            }
+        }
+        if (!mine) mine = std::make_shared<WsEntry>();
+        e = mine;
+    }
+    e->mutex.lock();
+    const bool mark = thread != 0 && !capturing;
+    // When the call has enqueued its kernels.  (Measured: a device synchronisation does not wait for the
+    // per-thread stream of a thread that has ended.  An event on it tells when its calls are done.)
+    auto unlock = [e, st, mark](void*) {
+        if (mark && (!e->done || hipEventRecord(e->done, st) != hipSuccess)) {
+            (void)hipGetLastError();
+            e->retire(e->eager);
+        }
+        e->mutex.unlock();
+    };
+    std::shared_ptr<void> use(nullptr, unlock);
+    if (taken_over && (!e->done || hipEventSynchronize(e->done) != hipSuccess)) {
+        (void)hipGetLastError();
+        e->retire(e->eager);
+    }
+    if (mark && !e->done && hipEventCreateWithFlags(&e->done, hipEventDisableTiming) != hipSuccess) {
+        e->done = nullptr;
+        (void)hipGetLastError();
+        return {};
+    }
+    WsBlock& b = capturing ? e->captured : e->eager;
+    if (!b.holds(part_floats, ncnt)) {
+        if (capturing && e->eager.holds(part_floats, ncnt)) {
+            e->retire(b);
+            std::swap(b, e->eager);
+        } else {
+            if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0) return {};
+            WsBlock fresh;
+            fresh.part_floats = std::max(part_floats, std::max(kPartFloatsPerCu * (size_t)cus, kGenWorkspaceFloats));
+            fresh.ncnt = std::max(ncnt, kCountersPerCu * (size_t)cus);
+            if (hipMalloc((void**)&fresh.part, fresh.part_floats * sizeof(float)) != hipSuccess ||
+                hipMalloc((void**)&fresh.cnt, fresh.ncnt * sizeof(int)) != hipSuccess || !clear_counters(fresh.cnt, fresh.ncnt, st)) {
+                if (fresh.part) (void)hipFree(fresh.part);
+                if (fresh.cnt) (void)hipFree(fresh.cnt);
+                (void)hipGetLastError();
+                return {};
+            }
+            e->retire(b);
+            b = fresh;
         }
     }
-    WsBlock& b = capturing ? e.captured : e.eager;
-    if (b.holds(part_floats, ncnt)) return {b.part, b.cnt};
-    if (capturing && e.eager.holds(part_floats, ncnt)) {
-        e.retire(b);
-        std::swap(b, e.eager);
-        return {b.part, b.cnt};
+    return {b.part, b.cnt, std::move(use)};
+}
+
+}  // namespace
+
+GenWorkspace gen_workspace(hipStream_t st, size_t part_floats, size_t ncnt)
+{
+    try {
+        return take_workspace(st, part_floats, ncnt);
+    } catch (...) {                                  // (no memory for the table)
+        return {};
     }
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus <= 0)
-        return {nullptr, nullptr};
-    WsBlock fresh;
-    fresh.part_floats = std::max(part_floats, std::max(kPartFloatsPerCu * (size_t)cus, kGenWorkspaceFloats));
-    fresh.ncnt = std::max(ncnt, kCountersPerCu * (size_t)cus);
-    if (hipMalloc((void**)&fresh.part, fresh.part_floats * sizeof(float)) != hipSuccess ||
-        hipMalloc((void**)&fresh.cnt, fresh.ncnt * sizeof(int)) != hipSuccess || !clear_counters(fresh.cnt, fresh.ncnt, st)) {
-        if (fresh.part) (void)hipFree(fresh.part);
-        if (fresh.cnt) (void)hipFree(fresh.cnt);
-        (void)hipGetLastError();
-        return {nullptr, nullptr};
-    }
-    e.retire(b);
-    b = fresh;
-    return {b.part, b.cnt};
 }
 
 void release_general_workspaces()
 {
     WsTable& table = ws_table();
     std::lock_guard<std::mutex> lock(table.mutex);
-    for (auto& kv : table.entries) kv.second.free_all();
-    for (auto& l : table.left) l.second.free_all();
+    auto free_all = [](WsEntry& e) {
+        std::lock_guard<std::mutex> held(e.mutex);
+        e.free_all();
+    };
+    for (auto& kv : table.entries) free_all(*kv.second);
+    for (auto& l : table.left) free_all(*l.second);
     table.entries.clear();
     table.left.clear();
 }
@@ -223,7 +265,7 @@ constexpr int kMaxDevices = 64;
 
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
-std::mutex g_scratch_mutex;
+std::mutex g_scratch_mutex, g_scratch_use[kMaxDevices];  // (of the table below; of each device's array)
 unsigned char* g_scratch_ptr[kMaxDevices] = {};         // device address of `scratch`, per device
 
 }  // namespace
@@ -245,6 +287,12 @@ int gen_static_workspace(hipStream_t st, size_t part_floats, size_t ncnt, GenWor
             g_scratch_ptr[dev] = (unsigned char*)q;
         }
         base = g_scratch_ptr[dev];
+    }
+    g_scratch_use[dev].lock();
+    try {
+        ws->use = std::shared_ptr<void>(nullptr, [dev](void*) { g_scratch_use[dev].unlock(); });
+    } catch (...) {                                  // (unlocked by the deleter)
+        return DCONV_LAUNCH_FAILED;
     }
     ws->cnt = (int*)base;
     ws->part = (float*)(base + 4 * kScratchCounters);

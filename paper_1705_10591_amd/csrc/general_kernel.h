@@ -42,7 +42,7 @@
 //    the result does not depend on the order of arrival.
 #pragma once
 #include <algorithm>
-#include <mutex>
+#include <memory>
 #include "common.h"
 #include "../../include/dconv.h"
 
@@ -761,19 +761,18 @@ struct GenSched {
     int wb;            // write-back: 0 by shape, 1 straight from the accumulators, 2 in whole lines through LDS
 };
 
-// Workspace of one (device, stream): grown on demand by the dispatcher.
+// The workspace a call uses, its own while `use` lives: calls from several threads on one stream share
+// the stream's workspace, and a call of two kernels must not be cut in two.
 struct GenWorkspace {
-    float* part;
-    int* cnt;
+    float* part = nullptr;
+    int* cnt = nullptr;
+    std::shared_ptr<void> use = nullptr;
 };
 // Returns a workspace with room for `part_floats` floats of partial sums and `ncnt` counters,
 // or nullptr members on allocation failure.
 GenWorkspace gen_workspace(hipStream_t st, size_t part_floats, size_t ncnt);
 // floats every workspace has room for (and the static array): the largest launch's partial sums
 constexpr size_t kGenWorkspaceFloats = (size_t)16 << 20;
-// Held while a call that uses a workspace enqueues its kernels: calls from several threads on one
-// stream share its workspace, and a call of two kernels must not be cut in two.
-std::mutex& gen_launch_mutex();
 int gen_cus();            // CUs of the current device, 0 on an error
 bool gen_capturing(hipStream_t st);   // the stream is being captured into a graph (or cannot be asked)
 // The same room inside the static device array of the current device, its counters cleared on
@@ -943,9 +942,7 @@ int gen_try_launch(const float* in, const float* filt, float* out, const Shape& 
         }
     }
 
-    std::unique_lock<std::mutex> lock(gen_launch_mutex(), std::defer_lock);
-    if (split) lock.lock();
-    GenWorkspace ws{nullptr, nullptr};
+    GenWorkspace ws;
     for (;;) {
         int rc = DCONV_OK;
         const size_t floats = (size_t)G * 2 * MT * NT, counters = split == 1 ? (size_t)G : 0;
@@ -956,6 +953,7 @@ int gen_try_launch(const float* in, const float* filt, float* out, const Shape& 
         }
         if (rc == DCONV_OK) break;
         if (split != 2 || sched.mode == 3) return rc;
+        ws = GenWorkspace();
         split = alone_split;                          // no room for the parts: as without a second kernel
         G = alone_G;
     }

@@ -656,9 +656,7 @@ int split_try_launch(const float* in, const float* filt, float* out, const Shape
     auto kern = general_split_kernel<F, IR, RG>;
     static std::atomic<uint64_t> lds_limit_raised{0};
     if (!raise_lds_limit((const void*)kern, kGenLdsLimit, lds_limit_raised)) return DCONV_LAUNCH_FAILED;
-    // Two kernels and the workspace between them: no other call on the stream may come in between.
-    std::lock_guard<std::mutex> lock(gen_launch_mutex());
-    GenWorkspace ws{nullptr, nullptr};
+    GenWorkspace ws;
     if (sched.static_ws) {
         if (gen_static_workspace(st, floats, split ? (size_t)G : 0, &ws) != DCONV_OK) return DCONV_UNSUPPORTED;
     } else {

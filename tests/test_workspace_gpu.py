@@ -3,6 +3,7 @@ allocation is let through, used from several graphs, streams and threads.
 """
 import ctypes
 import threading
+import time
 
 import numpy as np
 import pytest
@@ -144,7 +145,8 @@ def test_a_graph_runs_on_one_stream_beside_calls_on_the_stream_it_was_captured_o
 
 def test_the_per_thread_stream_has_a_workspace_for_every_thread():
     """hipStreamPerThread is one handle and another stream in each thread: the split filters and the partial
-    sums of two threads' calls do not meet; threads that follow take over what ended threads left."""
+    sums of two threads' calls do not meet.  Threads that follow take over what ended threads left, which
+    may still be at work."""
     lib, per_thread, vp = dconv.load_library(), ctypes.c_void_p(2), ctypes.c_void_p
     cases = [(shape, make(8510 + i, shape)) for i, shape in enumerate(
         ((14, 48, 66, 66, 64, 4), (6, 48, 40, 44, 100, 6), (1, 256, 14, 14, 256, 3), (2, 64, 30, 30, 64, 3)))]
@@ -152,31 +154,47 @@ def test_the_per_thread_stream_has_a_workspace_for_every_thread():
     outs = [[torch.empty_like(c[4]) for _ in range(12)] for _, c in cases]
     torch.cuda.synchronize()
     dconv.release_workspace()
-    errors, go = [], None
+    errors = []
 
-    def work(i):
+    def work(i, go, hold):
         (N, C, H, W, K, F), (_, _, xd, fd, _) = cases[i]
         go.wait()
         for o in outs[i]:
             rc = lib.dconv_general(vp(xd.data_ptr()), N, C, H, W, vp(fd.data_ptr()), K, F, vp(o.data_ptr()), per_thread)
             if rc != dconv.STATUS_OK:
                 errors.append((i, rc))
+        hold.wait()
 
-    held = []
-    for rep in range(3):
+    def run(together):
         for t in sum(outs, []):
             t.fill_(float("nan"))
         torch.cuda.synchronize()
-        go = threading.Barrier(len(cases))
-        threads = [threading.Thread(target=work, args=(i,)) for i in range(len(cases))]
-        print(f"four threads on the per-thread stream, {rep}", flush=True)
+        go, hold = threading.Barrier(len(cases) if together else 1), threading.Event()
+        threads = [threading.Thread(target=work, args=(i, go, hold)) for i in range(len(cases))]
+        if not together:
+            hold.set()
         for t in threads:
             t.start()
+            if not together:
+                t.join()
+        if together:
+            torch.cuda.synchronize()
+        hold.set()
         for t in threads:
             t.join()
-        torch.cuda.synchronize()
+        # (a device synchronisation does not wait for the streams of threads that have ended)
+        deadline = time.time() + 20
+        while any(bool(torch.isnan(o).any()) for o in sum(outs, [])) and time.time() < deadline:
+            time.sleep(0.01)
         assert not errors, errors
         for i, want in enumerate(wants):
-            assert all(torch.equal(o, want) for o in outs[i]), f"{cases[i][0]}, {rep}"
-        held.append(torch.cuda.mem_get_info()[0])
-    assert held[2] >= held[0], "the threads' blocks are used again"
+            assert all(torch.equal(o, want) for o in outs[i]), f"{cases[i][0]}, together={together}"
+        return torch.cuda.mem_get_info()[0]
+
+    left = []
+    for rep in range(3):
+        print(f"four threads on the per-thread stream, one after the other and together, {rep}", flush=True)
+        run(False)
+        left.append(run(True))
+    # 24 threads, at most four at a time: not 24 blocks (a thread may begin while the one before it, joined, ends)
+    assert left[0] - left[2] <= 4 * (65 << 20), "the threads' blocks are used again"

@@ -30,10 +30,16 @@
 //
 // Values a bf16 triple cannot carry are found and their outputs computed again in fp32:
 //  * infinities, NaN and values above the largest bf16: their splits make NaN, so every output
-//    they reach is not finite; such outputs are formed again (redo_output);
+//    they reach is not finite; such outputs are formed again (redo_block);
 //  * values below 2^-103, whose last parts may fall below the smallest bf16 (2^-133): each loses
 //    at most 2^-134; where a tile has staged one, outputs below 2^-60 are formed again (all of
 //    the tile's where values above 2^40 occur beside them).
+// What that costs: a wave that has such an output computes its block of 64 filters x 32 pixels again
+// behind the main loop, at the rate of its SIMD's fp32 matrix cores.  32 x 256 x 28 x 28 with 512 3x3
+// filters, by events around a call: 278 us, one NaN pixel 596, a filter of values near 2^-110 502,
+// nothing but NaN 967 (the fp32 kernel 460-490 for any data; with a lane for each such output, one after
+// the other, 5500, 372 and 7560); 32 x 64 x 56 x 56 with 64: 62, 91, 200, 199 (fp32 83); few
+// tiles of many taps, 8 x 97 x 25 x 25 with 250 7x7 filters: 75, 399, 420, 423 (fp32 100).
 #pragma once
 #include "general_kernel.h"
 
@@ -88,19 +94,59 @@ struct SplitGeom {
     static constexpr int IB = 3 * PS;                 // LDS pieces of an image block
 };
 
-// One output in fp32, channel by channel, for the few that the split cannot form.
-__device__ __attribute__((noinline)) float redo_output(const float* x, const float* w, int C, int F, int W, int64_t HW)
+// A wave's block of 64 filters x 32 pixels in fp32, on the fp32 matrix cores, for the outputs that the
+// split cannot form: those in `again` (bit 16 mt + r: accumulator r of block mt) are written.
+// The two reduction indices of an instruction are two channels.  Operands come straight from memory,
+// a filter row of two channels a time, kAhead rows ahead: a lane brings its pixel's words and the
+// row of two filters, so the filter loads gather.
+template <int F>
+__device__ __forceinline__ void redo_block(const char* ibase, int64_t ileft, uint32_t ipix, const float* w, int wbytes, char* out,
+                                           uint32_t again, int C, int W, int HW, int64_t plane)
 {
-    float total = 0.f;
-    for (int c = 0; c < C; ++c) {
-        float acc = 0.f;
-        for (int i = 0; i < F; ++i)
-            for (int jj = 0; jj < F; ++jj) acc = __builtin_fmaf(x[i * W + jj], w[i * F + jj], acc);
-        total += acc;
-        x += HW;
-        w += F * F;
-    }
-    return total;
+    constexpr int FF = F * F, NA = (F + 3) / 4, kAhead = F <= 4 ? 4 : 2;
+    constexpr uint32_t kNowhere = 0xC0000000u;
+    constexpr int kRsrcFlags = 0x00020000;
+    const int lane = threadIdx.x & 63, h = lane >> 5, l32 = lane & 31;
+    const int rows = (C + 1) / 2 * F;
+    v4f a[kAhead][2][NA];
+    float b[kAhead][F];
+    // (a channel beyond C and filters beyond K read zero)
+    auto fetch = [&](int u, v4f (&a)[2][NA], float (&b)[F]) __attribute__((always_inline)) {
+        u = min(u, rows - 1);
+        const int c0 = u / F * 2, i = u % F;
+        const bool there = c0 + h < C;
+        const int64_t ioff = ((int64_t)c0 * HW + (int64_t)i * W) * 4;
+        const int woff = (c0 * FF + i * F) * 4;
+        const auto irs = __builtin_amdgcn_make_buffer_rsrc((void*)(ibase + ioff), 0, (int)min(ileft - ioff, (int64_t)0x7FFFFFFF), kRsrcFlags);
+        const auto wrs = __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)w + woff), 0, wbytes - woff, kRsrcFlags);
+        const uint32_t iv = there ? ipix + (uint32_t)(h * HW) * 4u : kNowhere;
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt) {
+            const uint32_t wv = there ? (uint32_t)((mt * 32 + l32) * C + h) * (FF * 4u) : kNowhere;
+#pragma unroll
+            for (int q = 0; q < NA; ++q)
+                a[mt][q] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(wrs, wv + 16u * q, 0, 0));
+        }
+#pragma unroll
+        for (int jj = 0; jj < F; ++jj) b[jj] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(irs, iv + 4u * jj, 0, 0));
+    };
+    v16f acc[2] = {};
+#pragma unroll
+    for (int d = 0; d < kAhead; ++d) fetch(d, a[d], b[d]);
+    for (int u0 = 0; u0 < rows; u0 += kAhead)
+#pragma unroll
+        for (int d = 0; d < kAhead; ++d) {
+            if (u0 + d < rows) {                             // uniform
+#pragma unroll
+                for (int jj = 0; jj < F; ++jj)
+#pragma unroll
+                    for (int mt = 0; mt < 2; ++mt) acc[mt] = mfma_32x32x2(a[d][mt][jj / 4][jj % 4], b[d][jj], acc[mt]);
+            }
+            fetch(u0 + d + kAhead, a[d], b[d]);
+        }
+#pragma unroll
+    for (int r = 0; r < 32; ++r)
+        if (again >> r & 1) *reinterpret_cast<float*>(out + (int64_t)((r >> 4) * 32 + mfma_row(r & 15, 0)) * plane * 4) = acc[r >> 4][r & 15];
 }
 
 // What a set of split values is like: the smallest last remainder that is not zero (its bits, less one,
@@ -367,9 +413,21 @@ general_split_kernel(SplitParams p)
             for (int r = 0; r < 16; ++r) acc[mt][r] += hi[mt][r] + lo[mt][r];
     };
 
-    // `least`: finite outputs below it are formed again
-    auto emit = [&](bool any_tiny, bool any_huge) __attribute__((always_inline)) {
-        const float least = any_tiny ? (any_huge ? __builtin_inff() : 0x1p-60f) : -1.f;
+    // Tiles with outputs to be formed again, noted per wave for the pass behind the main loop: one bit for the
+    // workgroup's first tile, one for its last (which another workgroup may have to write), the others
+    // share 62.
+    const int tfirst = fdiv(u0, p.d_nun), tlast = fdiv(u1 - 1, p.d_nun);
+    uint64_t redo = 0;
+    int redo_kind = 0;
+    auto redo_bit = [&](int t) __attribute__((always_inline)) {
+        return 1ull << (t == tfirst ? 0 : t == tlast ? 1 : 2 + (t - tfirst) % 62);
+    };
+    // kind of tile: 0 no tiny values, 1 tiny ones, 2 tiny and huge ones; finite outputs below
+    // redo_below(kind) are formed again
+    auto redo_below = [](int kind) __attribute__((always_inline)) { return kind == 0 ? -1.f : kind == 1 ? 0x1p-60f : __builtin_inff(); };
+    auto emit = [&](int t, bool any_tiny, bool any_huge) __attribute__((always_inline)) {
+        const int kind = any_tiny ? (any_huge ? 2 : 1) : 0;
+        const float least = redo_below(kind);
         bool again = false;
 #pragma unroll
         for (int mt = 0; mt < MW; ++mt)
@@ -381,21 +439,9 @@ general_split_kernel(SplitParams p)
                 again |= !(fabsf(v) < __builtin_inff()) | (fabsf(v) < least);
                 if (valid && kk < kleft) *reinterpret_cast<float*>(ob + oofs) = v;
             }
-        if (again && valid) {
-            const uint32_t o0 = oofs / 4u - (uint32_t)(4 * h) * (uint32_t)plane;     // (n - n_first, 0, y, x)
-            const int dn = (int)((int64_t)o0 / ((int64_t)p.K * plane));
-            const int yx = (int)((int64_t)o0 - (int64_t)dn * p.K * plane);
-            const int y = yx / p.Wo, x = yx - y * p.Wo;
-            const float* px = p.in + (int64_t)(n_first_c + dn) * p.C * HW + (int64_t)y * p.W + x;
-#pragma unroll 1
-            for (int r = 0; r < 32; ++r) {
-                const int kk = (r >> 4) * 32 + 8 * ((r & 15) >> 2) + (r & 3);
-                if (kk >= kleft) continue;
-                float* o = reinterpret_cast<float*>((char*)(obase_t + kk * plane) + oofs);
-                const float v = __hip_atomic_load(o, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if (fabsf(v) < __builtin_inff() && !(fabsf(v) < least)) continue;
-                *o = redo_output(px, p.filt + (int64_t)(ck0 + kk + 4 * h) * CFF, p.C, F, p.W, HW);
-            }
+        if (__any(again && valid)) {
+            redo |= redo_bit(t);
+            redo_kind = max(redo_kind, kind);
         }
     };
     auto part_ptr = [&](int wgi, int which) __attribute__((always_inline)) {
@@ -407,7 +453,7 @@ general_split_kernel(SplitParams p)
     auto finish_tile = [&](int tile, bool whole) __attribute__((always_inline)) {
         const bool any_tiny = s_tiny[tile & 3] != 0, any_huge = s_huge[tile & 3] != 0;
         if (tid == 0) { s_tiny[(tile + 3) & 3] = 0; s_huge[(tile + 3) & 3] = 0; }
-        if (whole) { emit(any_tiny, any_huge); return; }
+        if (whole) { emit(tile, any_tiny, any_huge); return; }
         const int t0u = tile * nun;
         const int first = unit_owner(t0u, U, G), last = unit_owner(t0u + nun - 1, U, G);
         const int m = last - first + 1;
@@ -441,7 +487,7 @@ general_split_kernel(SplitParams p)
                 for (int r = 0; r < 16; ++r) acc[mt][r] += v[r];
             }
         }
-        emit(((now >> 10) & 1023) != 0, (now >> 20) != 0);
+        emit(tile, ((now >> 10) & 1023) != 0, (now >> 20) != 0);
     };
 
     // ---- prologue: the first unit's image block and first filter block go to LDS, the next ones
@@ -582,6 +628,34 @@ general_split_kernel(SplitParams p)
         } else {
             ++unit;
         }
+    }
+
+    // ---- outputs that the split cannot form: a wave's blocks again, in fp32 (nothing else is
+    // kept in registers here, as it would be if the main loop called this)
+    if (redo == 0) return;
+    __builtin_amdgcn_s_waitcnt(0x0F70);                         // this wave's outputs are in memory
+    const float least = redo_below(redo_kind);
+    for (int t = tfirst; t <= tlast; ++t) {
+        if ((redo & redo_bit(t)) == 0) continue;                // uniform
+        setup_compute(t);
+        uint32_t which = 0;
+#pragma unroll
+        for (int r = 0; r < 32; ++r) {
+            const int kk = (r >> 4) * 32 + mfma_row(r & 15, 0);
+            if (valid && kk < kleft) {
+                const float v = __hip_atomic_load(reinterpret_cast<float*>((char*)(obase_t + kk * plane) + oofs), __ATOMIC_RELAXED,
+                                                  __HIP_MEMORY_SCOPE_AGENT);
+                if (!(fabsf(v) < __builtin_inff()) | (fabsf(v) < least)) which |= 1u << r;
+            }
+        }
+        if (!__any(which != 0)) continue;
+        const uint32_t o0 = oofs / 4u - (uint32_t)(4 * h) * (uint32_t)plane;     // (n - n_first, 0, y, x)
+        const int dn = (int)((int64_t)o0 / ((int64_t)p.K * plane));
+        const int yx = (int)((int64_t)o0 - (int64_t)dn * p.K * plane);
+        const int y = yx / p.Wo, x = yx - y * p.Wo;
+        const int64_t ifirst = (int64_t)n_first_c * p.C * HW * 4;
+        redo_block<F>((const char*)p.in + ifirst, in_bytes - ifirst, (uint32_t)(dn * p.C * HW + y * p.W + x) * 4u,
+                      p.filt + (int64_t)ck0 * CFF, (p.K - ck0) * CFF * 4, (char*)obase_t + oofs, which, p.C, p.W, HW, plane);
     }
 }
 

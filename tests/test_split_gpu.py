@@ -105,6 +105,56 @@ def test_values_the_parts_cannot_carry(shape):
     assert np.all(np.abs(got - acc) <= 1e-5 * mag + C * F * F * 2.0**-150)
 
 
+def test_values_the_parts_cannot_carry_among_many_tiles():
+    """Over a hundred tiles a workgroup: the tiles to be formed again are found by their outputs.  Against the
+    fp32 kernel, by the bound that its sums of magnitudes give."""
+    shape = (32, 32, 256, 256, 256, 3)
+    N, C, H, W, K, F = shape
+    g = torch.Generator(device="cuda").manual_seed(82)
+    x = torch.rand((N, C, H, W), generator=g, device="cuda")
+    f = torch.randn((K, C, F, F), generator=g, device="cuda") * 0.1
+    x[1::2] *= 2.0 ** -112
+    mag = dconv.dconv_general(x, f.abs(), variant=fp32_variant(*shape))
+    for n, c, y, xx in ((0, 0, 0, 0), (6, 31, 255, 255), (6, 3, 100, 31), (31, 17, 254, 1)):
+        x[n, c, y, xx] = float("nan")
+    x[13, 2, 40, 40] = float("inf")
+    print(f"general {shape}", flush=True)
+    got, want = dconv.dconv_general(x, f), dconv.dconv_general(x, f, variant=fp32_variant(*shape))
+    torch.cuda.synchronize()
+    fine = torch.isfinite(want)
+    assert 0 < int((~fine).sum()) < 10 * 10 * K
+    assert torch.equal(torch.isnan(got), torch.isnan(want)) and torch.equal(torch.isinf(got), torch.isinf(want))
+    assert not torch.equal(got[0, :, 8:], want[0, :, 8:]), "the split-operand kernel is expected to run here"
+    assert bool(((got - want).abs()[fine] <= 2e-5 * mag[fine]).all())
+
+
+def test_time_does_not_depend_on_the_data_without_bound():
+    """One pixel that is not a number: its outputs are formed again, at a small multiple of the call's time
+    (2.1 times measured; a lane for each output, one after the other, took 20)."""
+    w = wl.G3
+    x, f = map(dev, wl.make_inputs(w))
+    out = torch.empty(w.out_shape(), device="cuda")
+
+    def us():
+        dconv.dconv_general(x, f, out=out)
+        best = float("inf")
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            dconv.dconv_general(x, f, out=out)
+            b.record()
+            b.synchronize()
+            best = min(best, a.elapsed_time(b) * 1e3)
+        return best
+
+    clean = us()
+    x[w.N - 1, w.C // 2, w.H // 2, w.W // 2] = float("nan")
+    marked = us()
+    print(f"{clean:.1f} us, with one NaN {marked:.1f} us", flush=True)
+    assert int(torch.isnan(out).sum()) == w.K * w.F * w.F
+    assert marked < 6 * clean
+
+
 def test_two_threads_on_one_stream():
     """The filters are split into the stream's workspace by a kernel of its own: two threads that call
     on one stream must not come between each other's two kernels."""

@@ -58,7 +58,9 @@ enum {
     DCONV_VARIANT_AUTO = 0,   /* pick by shape (what the plain entry points do)  */
     DCONV_VARIANT_SIMPLE = 1, /* one thread per output element; any shape        */
     DCONV_VARIANT_TILED = 2,  /* LDS-staged, matrix-core tiled kernel, tile
-                                 configuration picked by shape                   */
+                                 configuration picked by shape.  dconv_general_v:
+                                 always the fp32 matrix cores, also for the large
+                                 layers whose products AUTO takes apart         */
     DCONV_VARIANT_FEW_FILTERS = 3,
                               /* F <= 7: vector-ALU kernels with a sliding
                                  register window and wave-uniform weights.
@@ -233,7 +235,10 @@ int dconv_tile_config_count(int single_channel);
  * Returns the tile configuration i (as in DCONV_VARIANT_TILED_CFG0 + i) of that
  * entry point's tiled kernel -- for dconv_general the tile shape only, 0 to 2:
  * how its tiles are shared between workgroups is decided at launch from the
- * device's CU count -- or one of the negative values below.
+ * device's CU count -- or one of the negative values below.  (For the large
+ * layers of dconv_general whose products AUTO takes apart, the answer is the tile
+ * shape of the fp32 kernel, which runs them under DCONV_VARIANT_TILED and when the
+ * call is captured; the kernel that takes products apart has one tile shape.)
  */
 enum dconv_choice {
     DCONV_CHOICE_FEW_FILTERS = -1,  /* the vector-ALU kernel for few filters of that entry point */

@@ -91,7 +91,8 @@ CHOICE_FEW_FILTERS, CHOICE_SPECIAL_CASE, CHOICE_SIMPLE, CHOICE_INVALID, CHOICE_G
 
 
 def tile_choice(single_channel: bool, N: int, C: int, H: int, W: int, K: int, F: int) -> int:
-    """What VARIANT_AUTO picks for a shape: a tile configuration (>= 0) or a CHOICE_* value.
+    """What VARIANT_AUTO picks for a shape: a tile configuration (>= 0) or a CHOICE_* value.  (Large layers
+    whose products AUTO takes apart: the tile configuration of the fp32 kernel, which VARIANT_TILED runs.)
     Host arithmetic only: works without a GPU."""
     return int(load_library().dconv_tile_choice(1 if single_channel else 0, N, C, H, W, K, F))
 

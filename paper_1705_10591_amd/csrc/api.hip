@@ -32,9 +32,10 @@ int dispatch(bool single, const float* in, const float* filt, float* out,
     hipStream_t st = (hipStream_t)stream;
     const bool tiled_ok = single ? dconv::single_tiled_supports(s)
                                  : dconv::general_tiled_supports(s);
+    // (only the automatic choice takes products apart: the variants name the fp32 kernels)
     auto tiled = [&](int cfg) {
         return single ? dconv::launch_single_tiled(in, filt, out, s, st, cfg)
-                      : dconv::launch_general_tiled(in, filt, out, s, st, cfg, static_ws);
+                      : dconv::launch_general_tiled(in, filt, out, s, st, cfg, static_ws, variant == DCONV_VARIANT_AUTO);
     };
     switch (variant) {
     case DCONV_VARIANT_AUTO:
@@ -42,7 +43,7 @@ int dispatch(bool single, const float* in, const float* filt, float* out,
         // (filters beyond the special case's 11 x 11: the general kernel takes one channel too;
         // so do narrow or short images and large filters, where it is the faster one)
         if (single && (!tiled_ok || dconv::single_general_preferred(s)) && dconv::general_tiled_supports(s))
-            return dconv::launch_general_tiled(in, filt, out, s, st, -1, static_ws);
+            return dconv::launch_general_tiled(in, filt, out, s, st, -1, static_ws, true);
         return tiled_ok ? tiled(-1) : dconv::launch_simple(in, filt, out, s, st);
     case DCONV_VARIANT_FEW_FILTERS:
         if (!single) return dconv::launch_general_few(in, filt, out, s, st);   // (refuses what it cannot run)

@@ -59,9 +59,10 @@ int launch_simple(const float* in, const float* filt, float* out, const Shape& s
 int launch_single_tiled(const float* img, const float* filt, float* out, const Shape& s,
                         hipStream_t st, int cfg);
 // static_ws: tiles shared between workgroups meet in the library's static device array instead of
-// an allocated workspace (dconv_general_noalloc)
+// an allocated workspace (dconv_general_noalloc); may_split: large layers may have their products
+// taken apart on the bf16 matrix cores (split_kernel.h), with the shape's own configuration only
 int launch_general_tiled(const float* in, const float* filt, float* out, const Shape& s,
-                         hipStream_t st, int cfg, bool static_ws);
+                         hipStream_t st, int cfg, bool static_ws, bool may_split);
 int single_tile_configs();
 int general_tile_configs();
 // what the dispatchers pick by shape: the special case's tile configuration, the general case's

@@ -521,7 +521,7 @@ int try_split(const float* in, const float* filt, float* out, const Shape& s, hi
 }  // namespace
 
 int launch_general_tiled(const float* in, const float* filt, float* out, const Shape& s,
-                         hipStream_t st, int cfg, bool static_ws)
+                         hipStream_t st, int cfg, bool static_ws, bool may_split)
 {
     if (cfg >= kShapes * kSchedules * kWriteBacks) return DCONV_UNSUPPORTED;
     Shape one;
@@ -529,13 +529,12 @@ int launch_general_tiled(const float* in, const float* filt, float* out, const S
         const int64_t in_image = (int64_t)s.C * s.H * s.W, out_image = (int64_t)s.K * s.Ho * s.Wo;
         for (int n = 0; n < s.N; ++n) {
             const int rc = launch_general_tiled(in + n * in_image, filt, out + n * out_image, one, st, cfg,
-                                                static_ws);
+                                                static_ws, may_split);
             if (rc != DCONV_OK) return rc;
         }
         return DCONV_OK;
     }
-    // (a forced configuration that is what the shape's own choice names runs the same way)
-    if (cfg < 0 || (cfg < kShapes && cfg == shape_for(s))) {
+    if (may_split && cfg < 0) {
         const int rc = try_split(in, filt, out, s, st, static_ws);
         if (rc != DCONV_UNSUPPORTED) return rc;
     }

@@ -1,7 +1,7 @@
 """The split-operand kernel of the general case: fp32 layers on the bf16 matrix cores, each value as
 three bf16 parts.  The library picks it by size (3x3 and neighbouring filters, enough work), so the
 shapes here are ones it is picked for: a call that ran on it differs in its last bits from the
-fp32 matrix-core kernel, forced, and is closer to the exact sums.
+fp32 matrix-core kernel with the library's own schedule (VARIANT_TILED) and is closer to the exact sums.
 """
 import ctypes
 import threading
@@ -20,7 +20,7 @@ pytestmark = pytest.mark.gpu
 # (N, C, H, W, K, F): every compiled filter side; channels off multiples of sixteen (zero channels in
 # the last chunk), filters off multiples of 64, column strips, pixel tiles that end anywhere in a
 # row, whole tiles and tiles shared between workgroups
-SHAPES = [(11, 154, 63, 63, 39, 2), (4, 96, 55, 55, 179, 3), (20, 61, 65, 65, 64, 3), (1, 100, 60, 300, 96, 3),
+SHAPES = [(11, 154, 63, 63, 39, 2), (4, 96, 55, 55, 179, 3), (20, 61, 65, 65, 64, 3), (2, 100, 60, 300, 120, 3),
           (1, 64, 224, 224, 64, 3), (14, 48, 66, 66, 64, 4), (5, 40, 75, 67, 100, 5), (6, 48, 40, 44, 100, 6),
           (3, 40, 60, 62, 120, 7), (8, 97, 25, 25, 250, 7)]
 ids = lambda s: "x".join(map(str, s))
@@ -37,9 +37,8 @@ def call(x, f, variant=dconv.VARIANT_AUTO, noalloc=False):
     return out.cpu().numpy()
 
 
-def fp32_variant(N, C, H, W, K, F):
-    """The fp32 kernel with the shape's own tile, whole tiles only."""
-    return dconv.VARIANT_TILED_CFG0 + 3 + dconv.tile_choice(False, N, C, H, W, K, F)
+# the fp32 kernel with the shape's own tile and schedule
+FP32 = dconv.VARIANT_TILED
 
 
 @pytest.mark.parametrize("shape", SHAPES, ids=ids)
@@ -47,14 +46,14 @@ def test_within_the_bound_and_closer_than_the_fp32_kernel(shape):
     N, C, H, W, K, F = shape
     x, f = wl.random_case(8000 + C + F, N, C, H, W, K, F, "u01", "he")
     acc, mag, _ = oracle.general(x, f)
-    got, fp32 = call(x, f), call(x, f, fp32_variant(*shape))
+    got, fp32 = call(x, f), call(x, f, FP32)
     assert not np.array_equal(got, fp32), "the split-operand kernel is expected to run here"
     assert_within_bound(got, acc, mag, f"split {shape}")
     err = np.linalg.norm(got - acc), np.linalg.norm(fp32 - acc)
     assert err[0] <= err[1], err
-    # the same bits every time, through every entry point and variant that names this choice
+    # the same bits every time and through both entry points; a forced configuration is the fp32 kernel's
     assert np.array_equal(call(x, f), got) and np.array_equal(call(x, f, noalloc=True), got)
-    assert np.array_equal(call(x, f, dconv.VARIANT_TILED_CFG0 + dconv.tile_choice(False, *shape)), got)
+    assert np.array_equal(call(x, f, dconv.VARIANT_TILED_CFG0 + dconv.tile_choice(False, *shape)), fp32)
 
 
 @pytest.mark.parametrize("shape", SHAPES, ids=ids)
@@ -114,12 +113,12 @@ def test_values_the_parts_cannot_carry_among_many_tiles():
     x = torch.rand((N, C, H, W), generator=g, device="cuda")
     f = torch.randn((K, C, F, F), generator=g, device="cuda") * 0.1
     x[1::2] *= 2.0 ** -112
-    mag = dconv.dconv_general(x, f.abs(), variant=fp32_variant(*shape))
+    mag = dconv.dconv_general(x, f.abs(), variant=FP32)
     for n, c, y, xx in ((0, 0, 0, 0), (6, 31, 255, 255), (6, 3, 100, 31), (31, 17, 254, 1)):
         x[n, c, y, xx] = float("nan")
     x[13, 2, 40, 40] = float("inf")
     print(f"general {shape}", flush=True)
-    got, want = dconv.dconv_general(x, f), dconv.dconv_general(x, f, variant=fp32_variant(*shape))
+    got, want = dconv.dconv_general(x, f), dconv.dconv_general(x, f, variant=FP32)
     torch.cuda.synchronize()
     fine = torch.isfinite(want)
     assert 0 < int((~fine).sum()) < 10 * 10 * K
@@ -192,7 +191,7 @@ def test_a_first_call_on_a_stream_can_be_captured():
     acc, mag, _ = oracle.general(x, f)
     xd, fd = dev(x), dev(f)
     out = torch.empty(acc.shape, device="cuda")
-    warm = dconv.dconv_general(xd, fd, variant=fp32_variant(*shape))      # (loads the kernel; no workspace)
+    warm = dconv.dconv_general(xd, fd, variant=FP32)      # (loads the kernel; no workspace)
     torch.cuda.synchronize()
     g, s = torch.cuda.CUDAGraph(), torch.cuda.Stream()
     print("capturing a first call", flush=True)

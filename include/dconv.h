@@ -21,9 +21,20 @@
  *     fp32 accumulation; the order of additions is unspecified, so results
  *     agree with an exact sum to within rounding of an fp32 sum of C*F*F
  *     terms, and are bit-exact whenever all partial sums are exactly
- *     representable.  (Large layers of dconv_general take the products apart
- *     into exact ones of 8-bit parts on the bf16 matrix cores; their sums are
- *     fp32 too and closer to the exact ones.)
+ *     representable.
+ *     DCONV_VARIANT_AUTO of dconv_general takes large layers (filters 2x2 to
+ *     7x7, more than sixteen filters) apart on the bf16 matrix cores: every
+ *     value is the exact sum of three 8-bit parts, x = xh + xm + xl, and of the
+ *     nine products of parts the six largest are summed, in fp32.  Left out are
+ *     xm*wl, xl*wm and xl*wl: a product enters the sum to within 2^-24 of
+ *     itself where an fp32 multiply-add takes it whole.  Sums of many terms come
+ *     out closer to the exact ones than the fp32 instructions' (fewer roundings
+ *     per sum; 4 to 7 times on layers of 64 to 256 channels), a sum of ONE
+ *     term may be off by up to 1 ulp instead of 1/2, and bit-exact sums need a
+ *     bit to spare.  Values below 2^-103 lose what lies below 2^-134 of them
+ *     where an output reaches 2^-60; smaller outputs they may have touched, and
+ *     outputs that are not finite, are computed again in fp32, which takes
+ *     longer.  DCONV_VARIANT_TILED stays on fp32 products.
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).
  *     Work is enqueued on it and the call returns without synchronising.
  *     The launch happens on the device that is current in the calling thread;

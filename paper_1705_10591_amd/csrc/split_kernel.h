@@ -1,14 +1,17 @@
 // General-case direct convolution in fp32 on the bf16 matrix cores of gfx950.
 //
-// v_mfma_f32_32x32x2_f32 forms 64 multiply-adds per lane in 64 cycles, v_mfma_f32_32x32x16_bf16
-// 512 in 32: sixteen times the rate.  A 24-bit fp32 value is the exact sum of three bf16 values,
+// v_mfma_f32_32x32x2_f32 forms 32 multiply-adds per lane in 64 cycles, v_mfma_f32_32x32x16_bf16
+// 256 in 32: sixteen times the rate.  A 24-bit fp32 value is the exact sum of three bf16 values,
 // x = x_h + x_m + x_l (each the rest rounded to the eight bits of bf16), so
-//   x * w = h h' + (h m' + m h') + (m m' + h l' + l h') + terms below 2^-26 |x w|
+//   x * w = h h' + (h m' + m h') + (m m' + h l' + l h') + (m l' + l m' + l l')
+// with |m| <= 2^-8 |x| and |l| <= 2^-17 |x|.  The last three are left out, 2^-24 |x w| at most together,
 // and six bf16 instructions do the work of eight fp32 ones of twice the length: the matrix-core
-// time of a layer falls to 6/16, while the products are exact and the sums stay in fp32.
-// Errors against 64 bits are smaller than those of the fp32 instructions (fewer additions per
-// sum: an instruction adds eight products at a time, large and small products are summed apart,
-// and every block of sixteen channels is summed by itself before it joins the total).
+// time of a layer falls to 6/16.  Products of parts are exact and the sums stay in fp32.
+// Errors of dense sums against 64 bits are smaller than those of the fp32 instructions (fewer
+// additions per sum: an instruction adds eight products at a time, large and small products are
+// summed apart, and every block of sixteen channels is summed by itself before it joins the
+// total): 7.6e-7 -> 1.0e-7 with 256 channels of 3x3, 2.7e-7 -> 0.7e-7 with 64.  A sum of one term,
+// which the fp32 instructions round once, may be off by 1 ulp.
 //
 // What is kept from general_tiled_kernel: Algorithm 2's (filter block) x (pixel block) tiles,
 // pixels numbered along (n, y, x) of a column strip, channel chunks staged in LDS with the next

@@ -104,6 +104,30 @@ def test_values_the_parts_cannot_carry(shape):
     assert np.all(np.abs(got - acc) <= 1e-5 * mag + C * F * F * 2.0**-150)
 
 
+@pytest.mark.parametrize("shape", [(14, 48, 66, 66, 64, 4), (3, 40, 60, 62, 120, 7)], ids=ids)
+def test_a_sum_of_one_term_is_within_one_unit_in_the_last_place(shape):
+    """Filters of one weight: an output is one product.  Its three smallest products of parts, 2^-24 of it at
+    most, are left out and the rest is rounded: at most one unit in the last place.  Weights of eight bits
+    and VARIANT_TILED: the product rounded once."""
+    N, C, H, W, K, F = shape
+    rng = np.random.default_rng(8600 + F)
+    x = rng.standard_normal((N, C, H, W)).astype(np.float32)
+    f, at = np.zeros((K, C, F, F), np.float32), []
+    for k in range(K):
+        at.append((rng.integers(C), rng.integers(F), rng.integers(F)))
+        f[(k, *at[-1])] = rng.standard_normal()
+    want = np.stack([x[:, c, i:i + H - F + 1, j:j + W - F + 1].astype(np.float64) * f[k, c, i, j] for k, (c, i, j) in enumerate(at)], axis=1)
+    got = call(x, f)
+    ulp = np.spacing(np.abs(want).astype(np.float32)).astype(np.float64)
+    off = np.abs(got - want) / ulp
+    print(f"split {shape}: {off.max():.3f} units in the last place, rms {np.sqrt((off ** 2).mean()):.3f}", flush=True)
+    assert not np.array_equal(got, want.astype(np.float32)) and off.max() <= 1.0
+    assert np.array_equal(call(x, f, FP32), want.astype(np.float32))
+    short = (f.view(np.uint32) & np.uint32(0xFFFF0000)).view(np.float32)      # eight bits: h' alone
+    want = np.stack([x[:, c, i:i + H - F + 1, j:j + W - F + 1] * short[k, c, i, j] for k, (c, i, j) in enumerate(at)], axis=1)
+    assert np.abs(call(x, short) - want.astype(np.float64)).max() <= (0.502 * np.spacing(np.abs(want))).max()
+
+
 def test_values_the_parts_cannot_carry_among_many_tiles():
     """Over a hundred tiles a workgroup: the tiles to be formed again are found by their outputs.  Against the
     fp32 kernel, by the bound that its sums of magnitudes give."""

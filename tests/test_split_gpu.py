@@ -128,6 +128,20 @@ def test_a_sum_of_one_term_is_within_one_unit_in_the_last_place(shape):
     assert np.abs(call(x, short) - want.astype(np.float64)).max() <= (0.502 * np.spacing(np.abs(want))).max()
 
 
+@pytest.mark.parametrize("shape", [(4, 96, 55, 55, 179, 3), (14, 48, 66, 66, 64, 4)], ids=ids)
+def test_products_near_and_below_the_smallest_normal_value(shape):
+    """Operands whose parts are all there, products of parts that are subnormal: nothing is formed again, the
+    matrix cores keep subnormal products and sums."""
+    N, C, H, W, K, F = shape
+    x, f = wl.random_case(8700 + F, N, C, H, W, K, F, "u01", "he")
+    for sx, sf in ((-56, -56), (-62, -60), (-70, -50), (-75, -66), (-60, -72)):
+        xs, fs = np.ldexp(x, sx).astype(np.float32), np.ldexp(f, sf).astype(np.float32)
+        assert np.abs(xs[xs != 0]).min() > 2.0 ** -103 and np.abs(fs[fs != 0]).min() > 2.0 ** -103
+        acc, mag, _ = oracle.general(xs, fs)
+        got = call(xs, fs)
+        assert np.all(np.abs(got - acc) <= 1e-5 * mag + C * F * F * 2.0 ** -150), (sx, sf)
+
+
 def test_values_the_parts_cannot_carry_among_many_tiles():
     """Over a hundred tiles a workgroup: the tiles to be formed again are found by their outputs.  Against the
     fp32 kernel, by the bound that its sums of magnitudes give."""

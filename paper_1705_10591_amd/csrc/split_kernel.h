@@ -542,6 +542,8 @@ general_split_kernel(SplitParams p)
         for (int i = 0; i < 8; ++i) n += pair_step(i) / S == ph && pair_step(i) % S < S - 1 ? 2 : 0;
         return n;
     };
+    // (that count holds in the order written: the compiler moves no load across this)
+    auto in_order = []() __attribute__((always_inline)) { asm volatile("" ::: "memory"); };
     auto wait_filter = [](int later) __attribute__((always_inline)) {      // vmcnt(later), other counters left alone
         switch (later) {
         case 0: __builtin_amdgcn_s_waitcnt(0x0F70); break;
@@ -580,8 +582,13 @@ general_split_kernel(SplitParams p)
                     wf |= flags[b_of[0] + ph];
 #pragma unroll
                     for (int k = 0; k < NFI; ++k) fetch_filter(k, b_of[(ph + 1) / NP] + (ph + 1) % NP, fnext);
+                    in_order();
                 }
-                if (s == S - 1) wait_filter(later_loads(ph));
+                if (s == S - 1) {
+                    in_order();
+                    wait_filter(later_loads(ph));
+                    in_order();
+                }
 #pragma unroll
                 for (int i = 0; i < 8; ++i)
                     if (pair_step(i) == t) {

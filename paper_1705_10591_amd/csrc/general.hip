@@ -458,15 +458,15 @@ bool general_tiled_supports(const Shape& s)
 
 namespace {
 
-int launch_split(const float* in, const float* filt, float* out, const Shape& s, hipStream_t st, const GenSched& sched, bool dry)
+int launch_split(const float* in, const float* filt, float* out, const Shape& s, hipStream_t st, const GenSched& sched)
 {
     switch (s.F) {
-    case 2: return split_launch_for_F<2>(in, filt, out, s, st, sched, dry);
-    case 3: return split_launch_for_F<3>(in, filt, out, s, st, sched, dry);
-    case 4: return split_launch_for_F<4>(in, filt, out, s, st, sched, dry);
-    case 5: return split_launch_for_F<5>(in, filt, out, s, st, sched, dry);
-    case 6: return split_launch_for_F<6>(in, filt, out, s, st, sched, dry);
-    case 7: return split_launch_for_F<7>(in, filt, out, s, st, sched, dry);
+    case 2: return split_launch_for_F<2>(in, filt, out, s, st, sched);
+    case 3: return split_launch_for_F<3>(in, filt, out, s, st, sched);
+    case 4: return split_launch_for_F<4>(in, filt, out, s, st, sched);
+    case 5: return split_launch_for_F<5>(in, filt, out, s, st, sched);
+    case 6: return split_launch_for_F<6>(in, filt, out, s, st, sched);
+    case 7: return split_launch_for_F<7>(in, filt, out, s, st, sched);
     default: return DCONV_UNSUPPORTED;
     }
 }
@@ -515,7 +515,7 @@ int try_split(const float* in, const float* filt, float* out, const Shape& s, hi
     const int mode = split_mode(s);
     if (mode == 0) return DCONV_UNSUPPORTED;
     if (!static_ws && gen_capturing(st)) return DCONV_UNSUPPORTED;
-    return launch_split(in, filt, out, s, st, GenSched{mode, 0, false, static_ws, 0}, false);
+    return launch_split(in, filt, out, s, st, GenSched{mode, 0, false, static_ws, 0});
 }
 
 }  // namespace

@@ -754,7 +754,7 @@ inline GenPlan make_gen_plan(const Shape& s, int NT, int CSH, int imax, int rg, 
 
 // How a launch cuts the work; filled in by the dispatcher.
 struct GenSched {
-    int mode;          // 0: decide by shape, 1: whole tiles only, 2: cut inside tiles, 3: cut, parts added by a second kernel
+    int mode;          // 0: decide by shape, 1: whole tiles only, 2: cut inside tiles
     int force_G;       // > 0: this many workgroups (tests), 0: what the chip holds
     bool widest_only;  // refuse shapes whose image block needs narrower column strips
     bool static_ws;    // shared tiles meet in the library's static device array: nothing is allocated
@@ -859,7 +859,7 @@ int gen_try_launch(const float* in, const float* filt, float* out, const Shape& 
     // Whole tiles when they spread evenly enough, otherwise cut inside tiles.
     int G, split, alone_G = 0, alone_split = 0;      // (alone_: the choice without a second kernel)
     if (sched.mode == 1) split = 0;
-    else if (sched.mode >= 2) split = sched.mode - 1;
+    else if (sched.mode == 2) split = 1;
     else {
         // ... when a last round would leave much of the chip idle and a tile is long enough
         // (about 60 us with the workgroups of a CU sharing its matrix cores) for the saving to
@@ -952,7 +952,7 @@ int gen_try_launch(const float* in, const float* filt, float* out, const Shape& 
             if (!ws.part || (counters && !ws.cnt)) rc = DCONV_LAUNCH_FAILED;
         }
         if (rc == DCONV_OK) break;
-        if (split != 2 || sched.mode == 3) return rc;
+        if (split != 2) return rc;
         ws = GenWorkspace();
         split = alone_split;                          // no room for the parts: as without a second kernel
         G = alone_G;

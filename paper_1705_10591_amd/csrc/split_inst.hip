@@ -10,9 +10,9 @@ namespace dconv {
 
 template <>
 int split_launch_for_F<DCONV_F>(const float* in, const float* filt, float* out, const Shape& s,
-                                hipStream_t st, const GenSched& sched, bool dry)
+                                hipStream_t st, const GenSched& sched)
 {
-    return split_try_launch<DCONV_F, split_image_rows(DCONV_F), split_phase_rows(DCONV_F)>(in, filt, out, s, st, sched, dry);
+    return split_try_launch<DCONV_F, split_image_rows(DCONV_F), split_phase_rows(DCONV_F)>(in, filt, out, s, st, sched);
 }
 
 }  // namespace dconv

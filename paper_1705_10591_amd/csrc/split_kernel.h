@@ -700,7 +700,7 @@ inline SplitPlan make_split_plan(const Shape& s, int rg, int NT, int most)
 
 template <int F, int IR, int RG>
 int split_try_launch(const float* in, const float* filt, float* out, const Shape& s, hipStream_t st,
-                     const GenSched& sched, bool dry)
+                     const GenSched& sched)
 {
     using Gm = SplitGeom<F, IR, RG>;
     constexpr int MT = Gm::MT, NT = Gm::NT, THREADS = Gm::THREADS;
@@ -736,7 +736,6 @@ int split_try_launch(const float* in, const float* filt, float* out, const Shape
     const int64_t part_floats = split ? (int64_t)G * 2 * MT * NT : 0;
     const size_t floats = (size_t)(bank_floats + flag_floats + part_floats);
     if (floats > kGenWorkspaceFloats) return DCONV_UNSUPPORTED;
-    if (dry) return DCONV_OK;
     auto kern = general_split_kernel<F, IR, RG>;
     static std::atomic<uint64_t> lds_limit_raised{0};
     if (!raise_lds_limit((const void*)kern, kGenLdsLimit, lds_limit_raised)) return DCONV_LAUNCH_FAILED;
@@ -767,6 +766,6 @@ int split_try_launch(const float* in, const float* filt, float* out, const Shape
 // Implemented once per filter side, each in its own translation unit.
 template <int F>
 int split_launch_for_F(const float* in, const float* filt, float* out, const Shape& s, hipStream_t st,
-                       const GenSched& sched, bool dry);
+                       const GenSched& sched);
 
 }  // namespace dconv

@@ -137,7 +137,7 @@ def graph_replay_ms(fn, launches=20, replays=20):
     return e0.elapsed_time(e1) / (replays * launches)
 
 
-def make_runner(w):
+def make_runner(w, noalloc=False):
     import torch
     import workloads as wl
     import paper_1705_10591_amd as dconv
@@ -146,7 +146,7 @@ def make_runner(w):
     out = torch.empty(w.out_shape(), dtype=torch.float32, device="cuda")
     if w.kind == "single":
         return (lambda: dconv.dconv_single_channel(xd, fd, out=out)), (x, f)
-    return (lambda: dconv.dconv_general(xd, fd, out=out)), (x, f)
+    return (lambda: dconv.dconv_general(xd, fd, out=out, noalloc=noalloc)), (x, f)
 
 
 def make_half_runner(w, kind, blocked=False):
@@ -345,7 +345,7 @@ def main():
         if on_alu:
             roof["peak_plain_fma"] = FP32_PEAK_TFLOPS / 2
             roof["frac_plain_fma"] = round(entry["gflops"] / 1e3 / (FP32_PEAK_TFLOPS / 2), 4)
-        elif not single:
+        elif not single and 2 <= sh["F"] <= 7:
             add_parts_peak(roof)
     roof["kernel"] = entry["kernel"]
     roof["kernel_ms"] = round(ms, 5)
@@ -393,6 +393,11 @@ def main():
             if name in ("S1", "G2"):
                 # the two launch-bound configurations: the same calls replayed from a HIP graph
                 e["ms_graph_replay"] = round(graph_replay_ms(r), 5)
+            if name == "G2":
+                # (captured, dconv_general stays on the fp32 matrix cores where the call timed above takes
+                # its products apart on the bf16 ones; dconv_general_noalloc runs the same kernels either way)
+                e["graph_replay_kernel"] = "fp32 matrix cores; the call, and ms_graph_replay_noalloc: products of bf16 parts"
+                e["ms_graph_replay_noalloc"] = round(graph_replay_ms(make_runner(w, noalloc=True)[0]), 5)
             del r
             torch.cuda.empty_cache()
             if name == "S1":

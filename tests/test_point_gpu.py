@@ -64,3 +64,19 @@ def test_point_layer_non_finite_pixel_and_filter_stay_where_they_belong():
     want[1, :, 3, 4] = True
     want[:, 66] = True
     assert np.array_equal(bad, want)
+
+
+@pytest.mark.parametrize("blocked", [False, True], ids=["last", "blocked"])
+@pytest.mark.parametrize("kind", ["f16", "bf16"])
+@pytest.mark.parametrize("shape", [(5, 192, 7, 7, 65), (2, 320, 13, 17, 129), (6, 832, 80, 81, 128), (5, 512, 64, 65, 127)],
+                         ids=lambda s: "x".join(map(str, s)))
+def test_point_layers_keep_the_bits_of_the_kernel_for_every_filter_side(shape, kind, blocked):
+    """Sums are taken in the same order on both kernels, so rounding is the same too."""
+    N, C, H, W, K = shape
+    dtype, size = TYPES[kind]
+    x, f = wl.random_case(9300 + C + K, N, C, H, W, K, 1)
+    print(f"point {kind} {shape} blocked={blocked}", flush=True)
+    xd, fd = (torch.from_numpy(lay_out(a, blocked, size)).to("cuda").to(dtype) for a in (x, f))
+    got = dconv.dconv_general_half(xd, fd, blocked=blocked)
+    for cfg in (0, 1):
+        assert torch.equal(got, dconv.dconv_general_half(xd, fd, blocked=blocked, variant=dconv.VARIANT_TILED_CFG0 + cfg)), cfg

@@ -22,6 +22,12 @@ that the rules can be checked or re-derived on another chip.
     python -m paper_1705_10591_amd.tune route SEED COUNT          (one image of one channel on shapes drawn at
                                                                    random: the library's choice, the special
                                                                    case's kernel and the general-case kernel)
+    python -m paper_1705_10591_amd.tune rule parts|second|point SEED COUNT
+                                                                  (layers drawn at random, the library's choice
+                                                                   against what it would run without: products
+                                                                   of bf16 parts, the second kernel that adds
+                                                                   the parts of shared tiles, the 1x1 kernel of
+                                                                   the short types)
     python -m paper_1705_10591_amd.tune units                     (special case: 16-byte against 4-byte units
                                                                    on the way out, the width-matching ablation)
     python -m paper_1705_10591_amd.tune writeback                 (general case: stores straight from the
@@ -33,6 +39,7 @@ that the rules can be checked or re-derived on another chip.
 """
 from __future__ import annotations
 
+import math
 import sys
 import time
 
@@ -289,6 +296,114 @@ def route_table(seed: int, count: int) -> None:
           f"({sum(r >= 1.10 for r in general_r)})")
 
 
+def _graph_time(fn, launches: int = 10, replays: int = 15) -> float:
+    """Milliseconds per launch replayed from a graph: short kernels without the host's launch rate."""
+    s = torch.cuda.Stream()
+    with torch.cuda.stream(s):
+        fn()
+    s.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=s):
+        for _ in range(launches):
+            fn()
+    return _time(g.replay, 4.0, replays) / launches
+
+
+def _log(rng, lo, hi):
+    """A whole number between lo and hi, spread over its logarithm."""
+    return max(lo, min(hi, round(math.exp(rng.uniform(math.log(lo), math.log(hi))))))
+
+
+def _rule_case(which: str, rng):
+    """(label, calls: the library's choice first, whether it takes the kernel) of one random layer, or None."""
+    gen = torch.Generator(device="cuda").manual_seed(rng.getrandbits(31))
+    H = _log(rng, 7, {"parts": 128, "second": 60, "point": 128}[which])
+    W = max(7, round(H * rng.choice((1.0, 1.0, rng.uniform(0.5, 2.0)))))
+    if which == "point":
+        kind, blocked = rng.choice(("f16", "bf16", "i8")), rng.random() < 0.5
+        step = 32 if kind == "i8" else 16
+        N, C, K = _log(rng, 1, 64), step * _log(rng, 1, 1024 // step), _log(rng, 16, 1024)
+        if N * H * W * max(C, K) > 3e8:
+            return None
+        shapes = [(A, C // step, h, w, step) if blocked else (A, h, w, C) for A, h, w in ((N, H, W), (K, 1, 1))]
+        if kind == "i8":
+            x, f = (torch.randint(-127, 128, s, device="cuda", generator=gen, dtype=torch.int8) for s in shapes)
+            fn, out = dconv.dconv_general_i8, torch.empty(N, K, H, W, device="cuda", dtype=torch.int32)
+        else:
+            dt = torch.float16 if kind == "f16" else torch.bfloat16
+            x, f = (torch.rand(s, device="cuda", generator=gen).to(dt) for s in shapes)
+            fn, out = dconv.dconv_general_half, torch.empty(N, K, H, W, device="cuda")
+        variants = [dconv.VARIANT_AUTO] + [dconv.VARIANT_TILED_CFG0 + i for i in range(5)]
+        calls = [lambda v=v: fn(x, f, out=out, variant=v, blocked=blocked) for v in variants]
+        return f"{kind}{' blocked' if blocked else ''} {N}x{C}x{H}x{W}x{K}", calls, \
+            4 * N * K * H * W <= 256e6 and C * x.element_size() % 64 == 0
+    F = rng.choice((2, 3, 3, 3, 4, 5, 6, 7) if which == "parts" else (1, 3, 3, 5))
+    N = _log(rng, 1, 64 if which == "parts" else 8)
+    C, K = (_log(rng, 8, 512), _log(rng, 17, 512)) if which == "parts" else (_log(rng, 16, 1024), _log(rng, 17, 512))
+    if F > min(H, W):
+        return None
+    flop = 2.0 * N * C * K * F * F * (H - F + 1) * (W - F + 1)
+    choice = dconv.tile_choice(False, N, C, H, W, K, F)
+    if choice < 0 or flop > 60e9 or (which == "parts" and flop < 0.3e9):
+        return None
+    x = torch.rand(N, C, H, W, device="cuda", generator=gen)
+    f = torch.randn(K, C, F, F, device="cuda", generator=gen) * 0.1
+    out = torch.empty(N, K, H - F + 1, W - F + 1, device="cuda")
+    call = lambda v, o=out: dconv.dconv_general(x, f, out=o, variant=v)
+    label = f"{N}x{C}x{H}x{W}x{K}x{F}"
+    if which == "parts":
+        variants = (dconv.VARIANT_AUTO, dconv.VARIANT_TILED)
+        outs = [call(v, torch.empty_like(out)) for v in variants]
+        return label, [lambda v=v: call(v) for v in variants], not torch.equal(*outs)
+    # the fp32 kernel's own schedule, whole tiles, tiles shared by as many workgroups as the chip holds
+    variants = (dconv.VARIANT_TILED, dconv.VARIANT_TILED_CFG0 + 3 + choice, dconv.VARIANT_TILED_CFG0 + 6 + choice)
+    outs = [call(v, torch.empty_like(out)) for v in variants]
+    return label, [lambda v=v: call(v) for v in variants], not any(torch.equal(outs[0], o) for o in outs[1:])
+
+
+def rule_table(which: str, seed: int, count: int) -> None:
+    """The library's choice on random layers against what it would run without one of its kernels: `parts`
+    against the fp32 matrix cores, `second` against whole tiles and tiles added by their last workgroup,
+    `point` against the tile configurations of the kernel for every filter side (replayed from graphs).  Lists the layers that are 3 %
+    or more slower for it, and a summary over the layers for which the rule takes the kernel."""
+    import random
+    rng = random.Random(seed)
+    print(f"# {which}: {count} random layers (seed {seed}), microseconds per call of the library's choice and of the fastest "
+          "call without the kernel; layers listed where the choice takes it and is 3 % or more slower")
+    taken, everything, done = [], [], 0
+    while done < count:
+        case = _rule_case(which, rng)
+        if case is None:
+            continue
+        label, calls, takes = case
+        ok = []
+        for c in calls:
+            try:
+                c()
+                ok.append(c)
+            except dconv.DconvError as e:
+                if e.status != dconv.STATUS_UNSUPPORTED:
+                    raise
+        t = [1e30] * len(ok)
+        for _ in range(2):                 # alternating: neither gets the warmer chip
+            for i, c in enumerate(ok):
+                t[i] = min(t[i], _graph_time(c) if which == "point" else _time(c, 4.0, 10))
+        ratio = min(t[1:]) / t[0]
+        everything.append(ratio)
+        if takes:
+            taken.append(ratio)
+            if ratio <= 0.97:
+                print(f"{label:36s} {t[0] * 1e3:8.1f} {min(t[1:]) * 1e3:8.1f}  {ratio:5.2f}", flush=True)
+        done += 1
+        if done % 50 == 0:
+            print(f"[{done}]", file=sys.stderr, flush=True)
+    mean = lambda r: math.exp(sum(map(math.log, r)) / len(r)) if r else 1.0
+    taken.sort()
+    print(f"# without the kernel / with it: taken on {len(taken)} of {count} layers, there geometric mean {mean(taken):.3f}, "
+          f"worst {taken[0] if taken else 1.0:.3f}, median {taken[len(taken) // 2] if taken else 1.0:.3f}, best {taken[-1] if taken else 1.0:.2f}, "
+          f"{sum(r <= 0.97 for r in taken)} layers 3 % or more slower; over all layers {mean(everything):.3f}")
+
+
 def writeback_table() -> None:
     """Per shape: the library's choice, the three tile shapes with stores straight from the
     accumulators (configurations 0..2) and with the line-aligned write-back (12..14)."""
@@ -404,6 +519,12 @@ def main(argv):
             print("tune needs a GPU", file=sys.stderr)
             return 2
         random_table(argv[1], int(argv[2]), int(argv[3]))
+        return 0
+    if len(argv) == 4 and argv[0] == "rule" and argv[1] in ("parts", "second", "point"):
+        if not torch.cuda.is_available():
+            print("tune needs a GPU", file=sys.stderr)
+            return 2
+        rule_table(argv[1], int(argv[2]), int(argv[3]))
         return 0
     if len(argv) == 3 and argv[0] == "route":
         if not torch.cuda.is_available():

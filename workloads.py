@@ -109,6 +109,10 @@ PAPER_SWEEP = {w.name: w for w in (
     # filters, a small image
     _mk("A_768_K192_F8", "single", 1, 1, 768, 768, 192, 8, "u11", "u11", 45),
     _mk("A_64_K128_F8", "single", 1, 1, 64, 64, 128, 8, "u11", "u11", 46),
+    # one image of a deep layer: its few tiles are shared by the whole chip
+    _mk("B_N1_C256_14_F3", "general", 1, 256, 14, 14, 256, 3, "u01", "he", 47),
+    # a 1x1 (bottleneck) layer
+    _mk("B_C512_28_F1", "general", 32, 512, 28, 28, 128, 1, "u01", "he", 48),
 )}
 
 

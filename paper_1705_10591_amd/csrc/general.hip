@@ -151,6 +151,16 @@ bool gen_capturing(hipStream_t st)
 
 namespace {
 
+// While it lives, this thread's allocations do not count as part of captures that go on elsewhere, which
+// they would end as invalid.
+class BesideCaptures {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    bool changed = false;
+public:
+    explicit BesideCaptures(bool apply) { changed = apply && hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess; }
+    ~BesideCaptures() { if (changed) (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
 // The first request on a (device, stream) brings partial sums AND counters, whatever it asks for: a call
 // that is captured later may take another kernel than the call that ran before it, and a capture
 // does not allow an allocation.
@@ -178,6 +188,7 @@ GenWorkspace take_workspace(hipStream_t st, size_t part_floats, size_t ncnt)
         e = mine;
     }
     e->mutex.lock();
+    const BesideCaptures beside(!capturing);
     const bool mark = thread != 0 && !capturing;
     // When the call has enqueued its kernels.  (Measured: a device synchronisation does not wait for the
     // per-thread stream of a thread that has ended.  An event on it tells when its calls are done.)

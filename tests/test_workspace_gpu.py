@@ -198,3 +198,29 @@ def test_the_per_thread_stream_has_a_workspace_for_every_thread():
         left.append(run(True))
     # 24 threads, at most four at a time: not 24 blocks (a thread may begin while the one before it, joined, ends)
     assert left[0] - left[2] <= 4 * (65 << 20), "the threads' blocks are used again"
+
+
+def test_a_first_call_does_not_disturb_a_capture_on_another_stream():
+    """The first call of a large layer on a stream allocates its workspace; a capture going on elsewhere, in the
+    default mode, stays valid."""
+    shape = (1, 64, 224, 224, 64, 3)            # (whole tiles on the fp32 kernel: no workspace there)
+    x, f, xd, fd, out = make(8520, shape)
+    x1, f1, xd1, fd1, out1 = make(8521, (2, 8, 30, 30, 70, 3))
+    want, want1 = dconv.dconv_general(xd, fd), dconv.dconv_general(xd1, fd1)
+    N, C, H, W, K, F = shape
+    s, vp = fresh_stream(), ctypes.c_void_p
+    g, capturing = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    print("a first call on a stream beside a capture", flush=True)
+    with torch.cuda.graph(g, stream=capturing):
+        dconv.dconv_general(xd1, fd1, out=out1)
+        rc = dconv.load_library().dconv_general(vp(xd.data_ptr()), N, C, H, W, vp(fd.data_ptr()), K, F, vp(out.data_ptr()),
+                                                vp(s.cuda_stream))
+        dconv.dconv_general(xd1, fd1, out=out1)
+    assert rc == dconv.STATUS_OK
+    s.synchronize()
+    assert torch.equal(out, want)
+    for rep in range(3):
+        out1.fill_(float("nan"))
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out1, want1), f"replay {rep}"

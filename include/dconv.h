@@ -33,8 +33,9 @@
  *     term may be off by up to 1 ulp instead of 1/2, and bit-exact sums need a
  *     bit to spare.  Values below 2^-103 lose what lies below 2^-134 of them
  *     where an output reaches 2^-60; smaller outputs they may have touched, and
- *     outputs that are not finite, are computed again in fp32, which takes
- *     longer.  DCONV_VARIANT_TILED stays on fp32 products.
+ *     outputs that are not finite, are computed again in fp32: calls with such
+ *     values were measured at up to 4 times what DCONV_VARIANT_TILED takes,
+ *     which stays on fp32 products and takes the same time for any data.
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).
  *     Work is enqueued on it and the call returns without synchronising.
  *     The launch happens on the device that is current in the calling thread;

@@ -490,7 +490,8 @@ int launch_split(const float* in, const float* filt, float* out, const Shape& s,
 // the small kernel in front.  Shared tiles cost 0.41 us a step and the parts of a tile meet at
 // about 1.1 us each.  fp32: 133 TFLOP/s of what a block of 32 or 64 filters computes and 8 us, more on
 // layers that do not fill the chip.  It has to promise a seventh: over those layers the chosen ones
-// are 1.4 times faster on average and 6 of 1000 slower by 3 to 12 %.
+// are 1.4 times faster on average and 6 of 1000 slower by 3 to 12 %; on 400 others 1.46 times and 1
+// slower, by 7 % (profiles/rule_products_of_parts.txt).
 // (0: no, 1: whole tiles, 2: shared)
 int split_mode(const Shape& s)
 {

@@ -920,7 +920,7 @@ int gen_try_launch(const float* in, const float* filt, float* out, const Shape& 
         // fitted to 260 small layers (1 to 8 images of 7 x 7 to 60 x 60, 16 to 1024 channels, 1x1, 3x3
         // and 5x5 filters; rms 7 %), the time of the choice above to the same (19 %); where the
         // first promises a tenth less (and 2.5 us: below, the launch decides) the layers are 1.6 times
-        // faster on average (one image of 256 x 14 x 14, 256 3x3 filters: 25.4 -> 14.3 us; 512 x 7 x
+        // faster on average, 1.75 on 260 others (profiles/rule_second_kernel.txt; one image of 256 x 14 x 14, 256 3x3 filters: 25.4 -> 14.3 us; 512 x 7 x
         // 7, 512: 32.3 -> 18.3 us; 96 x 20 x 20, 32: 18.3 -> 10.0 us), none slower by more than 4 %.
         alone_G = G;
         alone_split = split;

@@ -40,6 +40,10 @@ int dispatch(bool single, const float* in, const float* filt, float* out,
     switch (variant) {
     case DCONV_VARIANT_AUTO:
         if (single && dconv::single_few_preferred(s)) return dconv::launch_single_few(in, filt, out, s, st);
+        if (dconv::split_taps_preferred(s)) {
+            const int rc = dconv::launch_split_taps(in, filt, out, s, st, static_ws);
+            if (rc != DCONV_UNSUPPORTED) return rc;
+        }
         // (filters beyond the special case's 11 x 11: the general kernel takes one channel too;
         // so do narrow or short images and large filters, where it is the faster one)
         if (single && (!tiled_ok || dconv::single_general_preferred(s)) && dconv::general_tiled_supports(s))
@@ -90,7 +94,7 @@ int general_entry(const float* in, int N, int C, int H, int W, const float* filt
     if (variant == DCONV_VARIANT_AUTO &&
         ((N == 1 && C == 1) || dconv::single_batch_preferred(s) ||
          (dconv::single_tiled_supports(s) && !dconv::general_tiled_supports(s))))
-        return dispatch(true, in, filt, out, s, variant, stream);
+        return dispatch(true, in, filt, out, s, variant, stream, static_ws);
     return dispatch(false, in, filt, out, s, variant, stream, static_ws);
 }
 

@@ -63,6 +63,9 @@ int launch_single_tiled(const float* img, const float* filt, float* out, const S
 // taken apart on the bf16 matrix cores (split_kernel.h), with the shape's own configuration only
 int launch_general_tiled(const float* in, const float* filt, float* out, const Shape& s,
                          hipStream_t st, int cfg, bool static_ws, bool may_split);
+// few channels on the bf16 matrix cores (split_taps.hip): DCONV_UNSUPPORTED where it cannot run
+int launch_split_taps(const float* in, const float* filt, float* out, const Shape& s, hipStream_t st, bool static_ws);
+bool split_taps_preferred(const Shape& s);
 int single_tile_configs();
 int general_tile_configs();
 // what the dispatchers pick by shape: the special case's tile configuration, the general case's

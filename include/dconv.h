@@ -97,7 +97,10 @@ enum {
                                  such layers where its estimated kernel time is
                                  below the matrix-core kernel's, whose 32-filter
                                  block would be mostly padding (few filters, or
-                                 up to sixteen on few channels)                  */
+                                 up to sixteen on few channels); where that is
+                                 estimated to be faster such a layer runs with
+                                 the taps of all filters as rows of a product on
+                                 the fp32 matrix cores, under AUTO and by name   */
     DCONV_VARIANT_SPECIAL_CASE = 4,
                               /* dconv_general with C = 1 (any filter up to
                                  11x11) or C <= 4 (filters up to 5x5) only: the
@@ -263,7 +266,8 @@ int dconv_tile_config_count(int single_channel);
  * shape of the fp32 kernel, which runs them under DCONV_VARIANT_TILED and when the
  * call is captured; the kernel that takes products apart has one tile shape.  One
  * image of one channel from 6 GFLOP on may be taken apart too: the answer is what
- * runs below that.)
+ * runs below that.  Up to sixteen filters for which the answer is a tile shape may
+ * run with their taps as rows of a product, where that is estimated to be faster.)
  */
 enum dconv_choice {
     DCONV_CHOICE_FEW_FILTERS = -1,  /* the vector-ALU kernel for few filters of that entry point */

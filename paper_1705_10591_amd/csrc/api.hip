@@ -91,10 +91,15 @@ int general_entry(const float* in, int N, int C, int H, int W, const float* filt
     // from nine on up to 2.8 times on layers of few channels)
     if (variant == DCONV_VARIANT_AUTO && !(N == 1 && C == 1) && dconv::general_few_preferred(s))
         return dconv::launch_general_few(in, filt, out, s, (hipStream_t)stream);
-    if (variant == DCONV_VARIANT_AUTO &&
-        ((N == 1 && C == 1) || dconv::single_batch_preferred(s) ||
-         (dconv::single_tiled_supports(s) && !dconv::general_tiled_supports(s))))
-        return dispatch(true, in, filt, out, s, variant, stream, static_ws);
+    const bool special = variant == DCONV_VARIANT_AUTO &&
+                         ((N == 1 && C == 1) || dconv::single_batch_preferred(s) ||
+                          (dconv::single_tiled_supports(s) && !dconv::general_tiled_supports(s)));
+    // (up to sixteen filters that would go to the general matrix-core kernel: their taps as rows of a product)
+    if (variant == DCONV_VARIANT_AUTO && !special && !dconv::split_taps_preferred(s) && dconv::few_taps_preferred(s)) {
+        const int rc = dconv::launch_few_taps(in, filt, out, s, (hipStream_t)stream);
+        if (rc != DCONV_UNSUPPORTED) return rc;
+    }
+    if (special) return dispatch(true, in, filt, out, s, variant, stream, static_ws);
     return dispatch(false, in, filt, out, s, variant, stream, static_ws);
 }
 

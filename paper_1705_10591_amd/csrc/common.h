@@ -75,6 +75,9 @@ int general_auto_shape(const Shape& s);
 int launch_single_few(const float* img, const float* filt, float* out, const Shape& s, hipStream_t st);
 // the general case with up to eight filters on the vector ALU (general_fewfilters.hip)
 int launch_general_few(const float* in, const float* filt, float* out, const Shape& s, hipStream_t st);
+// ... and with the taps of all filters on the matrix cores (few_taps_kernel.h)
+int launch_few_taps(const float* in, const float* filt, float* out, const Shape& s, hipStream_t st);
+bool few_taps_preferred(const Shape& s);
 bool general_few_supports(const Shape& s);
 bool general_few_preferred(const Shape& s);
 bool single_few_supports(const Shape& s);      // the few-filters kernel can run the shape

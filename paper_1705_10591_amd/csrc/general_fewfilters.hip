@@ -1,5 +1,6 @@
 // The few-filters kernel of the general case (general_few_kernel.h): when it runs.
 #include "general_few_kernel.h"
+#include "few_taps_kernel.h"
 
 #include <algorithm>
 
@@ -36,10 +37,8 @@ bool general_few_supports(const Shape& s)
 // chosen it is up to 6 times faster (101 x 3 x 64 x 640, two 1x1 filters: 97 -> 16 us; 8 x 16 x 224
 // x 224, one 7x7 filter: 189 -> 23 us; 8 x 64 x 224 x 224, three 3x3 filters: 139 -> 49 us; eight:
 // 139 -> 81 us; 21 x 8 x 96 x 640, twelve 5x5: 174 -> 80 us).
-bool general_few_preferred(const Shape& s)
+static double few_time(const Shape& s, double* tiles_out)
 {
-    // (one image of one channel is the special case proper, which has its own few-filters kernel)
-    if (!general_few_supports(s) || (s.C == 1 && s.N == 1)) return false;
     static const int kCompiled[17] = {0, 1, 2, 3, 4, 6, 6, 8, 8, 12, 12, 12, 12, 16, 16, 16, 16};
     const GfTile t = gf_tile_for(s);
     const double tiles = (double)gf_tiles(s, t.lpr, t.rpw);
@@ -51,15 +50,73 @@ bool general_few_preferred(const Shape& s)
     const double bytes = 4.0 * ((double)s.N * s.C * s.H * s.W + (double)s.N * s.K * s.Ho * s.Wo);
     const int per_barrier = (t.rpw == 1 && kc <= 8) ? 2 : 1;              // channels (see launch_gf)
     const double chain = s.C * (0.30 / per_barrier + 0.010 * (tr + s.F - 1) + 0.0105 * kc * ff * t.rpw + 0.03 * kc);
-    const double few = 3.4 + std::max({chain * std::max(1.0, tiles / 430.0), bytes / 5.1e6,
-                                       2.0 * macs * kc / inside / 70e6});
+    *tiles_out = tiles;
+    return 3.4 + std::max({chain * std::max(1.0, tiles / 430.0), bytes / 5.1e6, 2.0 * macs * kc / inside / 70e6});
+}
+bool general_few_preferred(const Shape& s)
+{
+    // (one image of one channel is the special case proper, which has its own few-filters kernel)
+    if (!general_few_supports(s) || (s.C == 1 && s.N == 1)) return false;
+    double tiles;
+    const double few = few_time(s, &tiles);
+    const int ff = s.F * s.F;
+    const double macs = (double)s.N * s.Ho * s.Wo * s.C * ff;             // per filter
+    const double bytes = 4.0 * ((double)s.N * s.C * s.H * s.W + (double)s.N * s.K * s.Ho * s.Wo);
     const double tiled = 7.1 + std::max({0.055 * s.C + 0.009 * s.C * ff, 2.0 * macs * 32 / 88e6, bytes / 2.6e6});
     return few < (tiles >= 768 ? 1.0 : 0.95) * tiled;
+}
+
+// When the taps of all filters go to the matrix cores (few_taps_kernel.h) instead: where its estimated time is
+// below 95 % of the vector-ALU kernel's, for layers that are that one's, or 85 % of the general matrix-core
+// kernel's, for the others (up to 64 taps there: with more, sums of many channels are no closer to the exact
+// ones).  Fitted to kernel times of 1600 layers from replayed graphs (1 to 16 filters of 1x1 to 7x7, 2 to 512
+// channels, 14 x 14 to 256 x 512 maps, 1 to 64 images), in microseconds; rms 15 % for this kernel, 22 % for the
+// general one: 3.9, the larger one of the plan's estimate and of input and output at 4.4 TB/s with a third of
+// the smaller one, 0.77 per thousand weights; 8.1, a 32-filter block at 137 TFLOP/s and the root of it, input
+// and output at 4.2 TB/s and a chain per channel.  Of 900 layers 334 were of the first kind: 102 are chosen, 1.43
+// times faster, 13 of them slower (by a third twice, else by up to 16 %); 566 of the others: 270 chosen, 1.86
+// times faster, 11 of them slower, by up to 23 %.
+bool few_taps_preferred(const Shape& s)
+{
+    if (s.K > 16 || s.F > 7 || (s.C == 1 && s.N == 1)) return false;
+    const FewTapsPlan pl = make_few_taps_plan(s);
+    if (!pl.ok) return false;
+    const double ff = (double)s.F * s.F, px = (double)s.N * s.Ho * s.Wo;
+    const double mb = 4e-6 * ((double)s.N * s.C * s.H * s.W + px * s.K), memory = mb / 4.4;
+    const double here = 3.9 + 0.99 * std::max(pl.cost, memory) + 0.357 * std::min(pl.cost, memory) + 0.77e-3 * s.K * ff * s.C;
+    if (general_few_preferred(s)) {
+        double tiles;
+        return here < 0.95 * few_time(s, &tiles);
+    }
+    if (pl.mb > 4) return false;
+    const double mflop = 2e-6 * px * 32 * s.C * ff;
+    return here < 0.85 * (8.1 + 0.0073 * mflop + 0.191 * std::sqrt(mflop) + 0.24 * mb + (0.0078 + 0.0183 * std::max(1.0, px / 256 / 512)) * s.C);
+}
+
+int launch_few_taps(const float* in, const float* filt, float* out, const Shape& s, hipStream_t st)
+{
+    const FewTapsPlan pl = make_few_taps_plan(s);
+    if (!pl.ok) return DCONV_UNSUPPORTED;
+    switch (s.F) {
+    case 1: return few_taps_for_F<1>(in, filt, out, s, st, pl);
+    case 2: return few_taps_for_F<2>(in, filt, out, s, st, pl);
+    case 3: return few_taps_for_F<3>(in, filt, out, s, st, pl);
+    case 4: return few_taps_for_F<4>(in, filt, out, s, st, pl);
+    case 5: return few_taps_for_F<5>(in, filt, out, s, st, pl);
+    case 6: return few_taps_for_F<6>(in, filt, out, s, st, pl);
+    case 7: return few_taps_for_F<7>(in, filt, out, s, st, pl);
+    default: return DCONV_UNSUPPORTED;
+    }
 }
 
 int launch_general_few(const float* in, const float* filt, float* out, const Shape& s, hipStream_t st)
 {
     if (!general_few_supports(s)) return DCONV_UNSUPPORTED;
+    // (whatever names the few-filters kernel of a layer that is its own runs the faster one of the two)
+    if (general_few_preferred(s) && few_taps_preferred(s)) {
+        const int rc = launch_few_taps(in, filt, out, s, st);
+        if (rc != DCONV_UNSUPPORTED) return rc;
+    }
     switch (s.F) {
     case 1: return gf_launch_for_F<1>(in, filt, out, s, st);
     case 2: return gf_launch_for_F<2>(in, filt, out, s, st);

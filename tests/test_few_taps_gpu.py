@@ -1,0 +1,66 @@
+"""Few filters with the taps of all filters as rows of a matrix product (AUTO, by estimated time).  The
+shapes are small ones that the library's rule sends there.
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import workloads as wl
+import paper_1705_10591_amd as dconv
+from helpers import assert_within_bound
+
+pytestmark = pytest.mark.gpu
+
+# (N, C, H, W, K, F): every filter side, one to seven blocks of tap rows, four and eight waves a workgroup, one,
+# two and four column blocks of 64 per row, two column strips, one and two sets of sums in LDS; channels off
+# multiples of four and sixteen, widths off multiples of four, bands that end early
+SHAPES = [(2, 16, 6, 4, 1, 1), (5, 10, 30, 263, 1, 1), (6, 13, 85, 65, 1, 1), (4, 13, 73, 65, 1, 2), (3, 146, 49, 130, 8, 2),
+          (4, 21, 53, 387, 9, 2), (6, 11, 89, 111, 13, 2), (6, 73, 90, 77, 1, 3), (6, 8, 89, 9, 1, 3), (6, 147, 90, 74, 3, 3),
+          (3, 13, 20, 130, 2, 3), (4, 13, 19, 366, 4, 3), (5, 7, 17, 97, 5, 3), (5, 34, 51, 221, 6, 3), (3, 50, 46, 261, 2, 4),
+          (5, 16, 73, 376, 5, 4), (5, 30, 86, 318, 6, 4), (1, 30, 87, 271, 2, 5), (6, 17, 87, 117, 3, 5), (4, 26, 83, 237, 4, 5),
+          (4, 11, 75, 66, 1, 6), (6, 11, 83, 125, 3, 6), (4, 38, 19, 381, 1, 7), (3, 26, 77, 193, 2, 7)]
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_within_the_bound_between_guard_bands(shape):
+    N, C, H, W, K, F = shape
+    print(f"few filters {shape}", flush=True)
+    x, f = wl.random_case(9900 + C + F, N, C, H, W, K, F, "u01", "he")
+    fd = torch.from_numpy(f).cuda()
+    xb = torch.empty(x.size + 1, device="cuda")[1:].view(x.shape)      # images need no alignment beyond a float's
+    xb.copy_(torch.from_numpy(x))
+    want = (N, K, H - F + 1, W - F + 1)
+    buf = torch.full((int(np.prod(want)) + 2048,), float("nan"), device="cuda")
+    out = buf[1001:len(buf) - 1047].view(want)
+    dconv.dconv_general(xb, fd, out=out)
+    again = dconv.dconv_general(xb.clone(), fd, noalloc=True)
+    few, tiled = (dconv.dconv_general(xb, fd, variant=v) for v in (dconv.VARIANT_FEW_FILTERS, dconv.VARIANT_TILED))
+    chosen = dconv.tile_choice(False, *shape) == dconv.CHOICE_FEW_FILTERS
+    torch.cuda.synchronize()
+    got = out.cpu().numpy()
+    acc, mag, _ = oracle.general(x, f)
+    assert_within_bound(got, acc, mag, f"few filters {shape}")
+    assert torch.equal(out, again)
+    # a layer that the few-filters kernel is chosen for runs the same by that name; elsewhere it names the
+    # vector-ALU kernel, whose sums are one chain: no closer to the exact ones
+    # (with 1x1 filters and a few channels the general kernel's chain is the same)
+    assert F == 1 or torch.equal(out, few) == chosen and not torch.equal(out, tiled), "taps as rows of a product are expected to run here"
+    err = [np.linalg.norm(o.cpu().numpy() - acc) for o in (out, few)]
+    assert err[0] <= err[1], err
+    assert torch.isnan(buf[:1001]).all() and torch.isnan(buf[len(buf) - 1047:]).all()
+    # one pixel that is not finite reaches the outputs whose windows hold it, and no other
+    at = (N - 1, C - 1, H // 2, W - 2)
+    xb[at] = float("nan")
+    marked = dconv.dconv_general(xb, fd)
+    hit = torch.zeros_like(out, dtype=torch.bool)
+    hit[N - 1, :, max(0, at[2] - F + 1):at[2] + 1, max(0, at[3] - F + 1):at[3] + 1] = True
+    assert torch.equal(torch.isnan(marked), hit) and torch.equal(marked[~hit], out[~hit])
+
+
+@pytest.mark.parametrize("shape", SHAPES[3::4], ids=lambda s: "x".join(map(str, s)))
+def test_integer_inputs_are_exact(shape):
+    x, f = wl.integer_case(9950, *shape)
+    out = dconv.dconv_general(torch.from_numpy(x).cuda(), torch.from_numpy(f).cuda())
+    torch.cuda.synchronize()
+    assert np.array_equal(out.cpu().numpy(), oracle.general(x, f)[0].astype(np.float32))

@@ -83,7 +83,11 @@ enum {
     DCONV_VARIANT_TILED = 2,  /* LDS-staged, matrix-core tiled kernel, tile
                                  configuration picked by shape.  dconv_general_v:
                                  always the fp32 matrix cores, also for the large
-                                 layers whose products AUTO takes apart         */
+                                 layers whose products AUTO takes apart.  Short
+                                 launches (estimated from the shape) run on small
+                                 tiles of their own, under AUTO, under this name
+                                 and under the configuration that
+                                 dconv_tile_choice names                         */
     DCONV_VARIANT_FEW_FILTERS = 3,
                               /* F <= 7: vector-ALU kernels with a sliding
                                  register window and wave-uniform weights.

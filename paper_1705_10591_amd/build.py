@@ -23,7 +23,7 @@ SOURCES = [("api.hip", [], "api"), ("simple.hip", [], "simple"), ("single.hip", 
           [("general_inst.hip", [f"-DDCONV_F={f}"], f"general_f{f}") for f in range(1, 33)] + \
           [("split_inst.hip", [f"-DDCONV_F={f}"], f"split_f{f}") for f in range(2, 8)] + \
           [("few_taps_inst.hip", [f"-DDCONV_F={f}"], f"few_taps_f{f}") for f in range(1, 8)] + \
-          [("split_taps.hip", [], "split_taps")] + \
+          [("split_taps.hip", [], "split_taps"), ("short.hip", [], "short")] + \
           [("half.hip", [], "half"), ("half_1x1.hip", [], "half_1x1")] + \
           [("half_inst.hip", [f"-DDCONV_F={f}"], f"half_f{f}") for f in range(1, 33)]
 

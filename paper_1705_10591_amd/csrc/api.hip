@@ -40,9 +40,14 @@ int dispatch(bool single, const float* in, const float* filt, float* out,
     switch (variant) {
     case DCONV_VARIANT_AUTO:
         if (single && dconv::single_few_preferred(s)) return dconv::launch_single_few(in, filt, out, s, st);
-        if (dconv::split_taps_preferred(s)) {
-            const int rc = dconv::launch_split_taps(in, filt, out, s, st, static_ws);
-            if (rc != DCONV_UNSUPPORTED) return rc;
+        // (few channels, where that is estimated to be faster than the general kernels and small tiles)
+        {
+            int cfg;
+            const double taps = dconv::split_taps_time_if_preferred(s);
+            if (taps < 1e300 && (single || taps < dconv::short_time_if_preferred(s, &cfg))) {
+                const int rc = dconv::launch_split_taps(in, filt, out, s, st, static_ws);
+                if (rc != DCONV_UNSUPPORTED) return rc;
+            }
         }
         // (filters beyond the special case's 11 x 11: the general kernel takes one channel too;
         // so do narrow or short images and large filters, where it is the faster one)
@@ -95,9 +100,13 @@ int general_entry(const float* in, int N, int C, int H, int W, const float* filt
                          ((N == 1 && C == 1) || dconv::single_batch_preferred(s) ||
                           (dconv::single_tiled_supports(s) && !dconv::general_tiled_supports(s)));
     // (up to sixteen filters that would go to the general matrix-core kernel: their taps as rows of a product)
-    if (variant == DCONV_VARIANT_AUTO && !special && !dconv::split_taps_preferred(s) && dconv::few_taps_preferred(s)) {
-        const int rc = dconv::launch_few_taps(in, filt, out, s, (hipStream_t)stream);
-        if (rc != DCONV_UNSUPPORTED) return rc;
+    if (variant == DCONV_VARIANT_AUTO && !special && K <= 16) {
+        int cfg;
+        const double few = dconv::few_taps_time_if_preferred(s);
+        if (few < 1e300 && few < dconv::split_taps_time_if_preferred(s) && few < dconv::short_time_if_preferred(s, &cfg)) {
+            const int rc = dconv::launch_few_taps(in, filt, out, s, (hipStream_t)stream);
+            if (rc != DCONV_UNSUPPORTED) return rc;
+        }
     }
     if (special) return dispatch(true, in, filt, out, s, variant, stream, static_ws);
     return dispatch(false, in, filt, out, s, variant, stream, static_ws);

@@ -65,19 +65,25 @@ int launch_general_tiled(const float* in, const float* filt, float* out, const S
                          hipStream_t st, int cfg, bool static_ws, bool may_split);
 // few channels on the bf16 matrix cores (split_taps.hip): DCONV_UNSUPPORTED where it cannot run
 int launch_split_taps(const float* in, const float* filt, float* out, const Shape& s, hipStream_t st, bool static_ws);
-bool split_taps_preferred(const Shape& s);
+double split_taps_time_if_preferred(const Shape& s);
 int single_tile_configs();
 int general_tile_configs();
 // what the dispatchers pick by shape: the special case's tile configuration, the general case's
 // tile shape (pure host arithmetic)
 int single_auto_config(const Shape& s);
 int general_auto_shape(const Shape& s);
+// short launches on small tiles (short.hip)
+int launch_short(const float* in, const float* filt, float* out, const Shape& s, hipStream_t st, int cfg);
+// estimated kernel times in us where a kernel is the better choice (1e300 where it isn't), for the choice among
+// those that are
+double short_time_if_preferred(const Shape& s, int* cfg);
+bool short_in_place_of_shared_tiles(const Shape& s);     // ... of tiles that the general kernel would share
 int launch_single_few(const float* img, const float* filt, float* out, const Shape& s, hipStream_t st);
 // the general case with up to eight filters on the vector ALU (general_fewfilters.hip)
 int launch_general_few(const float* in, const float* filt, float* out, const Shape& s, hipStream_t st);
 // ... and with the taps of all filters on the matrix cores (few_taps_kernel.h)
 int launch_few_taps(const float* in, const float* filt, float* out, const Shape& s, hipStream_t st);
-bool few_taps_preferred(const Shape& s);
+double few_taps_time_if_preferred(const Shape& s);
 bool general_few_supports(const Shape& s);
 bool general_few_preferred(const Shape& s);
 bool single_few_supports(const Shape& s);      // the few-filters kernel can run the shape

@@ -320,7 +320,7 @@ namespace {
 
 // Tile configurations offered through the ABI: tile shape x schedule.
 //   shape    0: 64 filters x 128 pixels, 1: 64 x 256, 2: 32 x 256
-//   schedule 0: by shape, 1: whole tiles only, 2: tiles cut over channels wherever the even
+//   schedule 0: by shape (short launches of the shape's own tile: short.hip), 1: whole tiles only, 2: tiles cut over channels wherever the even
 //            split of the work falls, 3: the same on a grid of 7 workgroups (so that small
 //            test shapes exercise every way a tile can be shared)
 //   write-back: configurations 0 to 11 store straight from the accumulators, 12 to 23 are the
@@ -549,6 +549,18 @@ int launch_general_tiled(const float* in, const float* filt, float* out, const S
     if (may_split && cfg < 0) {
         const int rc = try_split(in, filt, out, s, st, static_ws);
         if (rc != DCONV_UNSUPPORTED) return rc;
+    }
+    // Short launches: small tiles whose reduction the waves of a workgroup share.  They are part of the schedule by
+    // shape, so the configuration that the shape gets by itself runs them too when it is named, and only that one.
+    if (cfg < 0 || cfg == shape_for(s)) {
+        int small;
+        if (short_time_if_preferred(s, &small) < 1e300 && split_mode(s) == 0) {
+            // (a layer whose tiles the general kernel would share still brings the stream its workspace: programs run
+            // such a call before they capture others)
+            if (!static_ws && short_in_place_of_shared_tiles(s) && !gen_capturing(st)) (void)gen_workspace(st, 0, 0);
+            const int rc = launch_short(in, filt, out, s, st, small);
+            if (rc != DCONV_UNSUPPORTED) return rc;
+        }
     }
     if (cfg < 0) {
         const GenSched sched{0, 0, false, static_ws, 0};

@@ -76,21 +76,21 @@ bool general_few_preferred(const Shape& s)
 // and output at 4.2 TB/s and a chain per channel.  Of 900 layers 334 were of the first kind: 102 are chosen, 1.43
 // times faster, 13 of them slower (by a third twice, else by up to 16 %); 566 of the others: 270 chosen, 1.86
 // times faster, 11 of them slower, by up to 23 %.
-bool few_taps_preferred(const Shape& s)
+double few_taps_time_if_preferred(const Shape& s)
 {
-    if (s.K > 16 || s.F > 7 || (s.C == 1 && s.N == 1)) return false;
+    if (s.K > 16 || s.F > 7 || (s.C == 1 && s.N == 1)) return 1e300;
     const FewTapsPlan pl = make_few_taps_plan(s);
-    if (!pl.ok) return false;
+    if (!pl.ok) return 1e300;
     const double ff = (double)s.F * s.F, px = (double)s.N * s.Ho * s.Wo;
     const double mb = 4e-6 * ((double)s.N * s.C * s.H * s.W + px * s.K), memory = mb / 4.4;
     const double here = 3.9 + 0.99 * std::max(pl.cost, memory) + 0.357 * std::min(pl.cost, memory) + 0.77e-3 * s.K * ff * s.C;
     if (general_few_preferred(s)) {
         double tiles;
-        return here < 0.95 * few_time(s, &tiles);
+        return here < 0.95 * few_time(s, &tiles) ? here : 1e300;
     }
-    if (pl.mb > 4) return false;
+    if (pl.mb > 4) return 1e300;
     const double mflop = 2e-6 * px * 32 * s.C * ff;
-    return here < 0.85 * (8.1 + 0.0073 * mflop + 0.191 * std::sqrt(mflop) + 0.24 * mb + (0.0078 + 0.0183 * std::max(1.0, px / 256 / 512)) * s.C);
+    return here < 0.85 * (8.1 + 0.0073 * mflop + 0.191 * std::sqrt(mflop) + 0.24 * mb + (0.0078 + 0.0183 * std::max(1.0, px / 256 / 512)) * s.C) ? here : 1e300;
 }
 
 int launch_few_taps(const float* in, const float* filt, float* out, const Shape& s, hipStream_t st)
@@ -113,7 +113,7 @@ int launch_general_few(const float* in, const float* filt, float* out, const Sha
 {
     if (!general_few_supports(s)) return DCONV_UNSUPPORTED;
     // (whatever names the few-filters kernel of a layer that is its own runs the faster one of the two)
-    if (general_few_preferred(s) && few_taps_preferred(s)) {
+    if (general_few_preferred(s) && few_taps_time_if_preferred(s) < 1e300) {
         const int rc = launch_few_taps(in, filt, out, s, st);
         if (rc != DCONV_UNSUPPORTED) return rc;
     }

@@ -765,28 +765,28 @@ int taps_launch(const float* in, const float* filt, float* out, const Shape& s, 
 // half as much again beyond the memory-side cache.  The others: 7.9 us per GFLOP.  It has to promise a
 // tenth: of 1400 layers 489 are chosen, 1.5 times faster on average, 18 of them slower, by up to 27 %
 // (large images, whose lines the special case's kernel writes whole).
-bool split_taps_preferred(const Shape& s)
+double split_taps_time_if_preferred(const Shape& s)
 {
-    if (s.C > 16 || s.F < 2 || s.F > 11 || s.K < 9) return false;
+    if (s.C > 16 || s.F < 2 || s.F > 11 || s.K < 9) return 1e300;
     const TapsSteps t = taps_steps(s);
     // (a longer sum is no closer to the exact one than the fp32 kernel's where that adds a tile's parts: 968 taps
     // 1.6e-7 against 1.5e-7; up to 480 taps at most 1.4e-7, and 3.4e-7 for a whole tile's there)
-    if (t.steps > 16) return false;
+    if (t.steps > 16) return 1e300;
     const double px = (double)s.N * s.Ho * s.Wo, mb = px * s.K * 4e-6;
     // (one image of one channel: from 6 GFLOP on.  Below, the configuration that dconv_tile_choice names gives
     // the bits of the plain call when it is forced, which callers rely on; 720 x 1280 with forty 9x9 filters,
     // 5.9 GFLOP, would go from 101 to 50 us)
-    if (s.N == 1 && s.C == 1 && 2.0 * px * s.K * s.F * s.F < 6e9) return false;
+    if (s.N == 1 && s.C == 1 && 2.0 * px * s.K * s.F * s.F < 6e9) return 1e300;
     // (few multiply-adds per output of a large volume: bound by its stores, which the special case's kernel
     // arranges better)
-    if (s.N == 1 && s.C == 1 && mb > 600 && s.F < 9) return false;
+    if (s.N == 1 && s.C == 1 && mb > 600 && s.F < 9) return 1e300;
     const double tiles = std::ceil(px * 1.04 / kTapsNT) * t.KB, work = t.steps * t.MB;
     const double rounds = tiles > 1536 ? tiles / 512 : std::ceil(tiles / 512);
     const bool res = taps_fits(t, t.steps, kTapsPartSmall);
     const double here = 6.3 + rounds * (0.253 * work + 1.25) + (res ? 0.344 * work : 3.0 + 0.104 * t.steps) + 0.153 * mb + 0.082 * std::max(0.0, mb - 250);
     const double taps = (double)s.C * s.F * s.F;
     const double there = 6.1 + 0.00785e-6 * 2 * px * ((s.K + 31) / 32 * 32) * taps + 0.147 * mb + 0.0168 * taps;
-    return here < 0.9 * there;
+    return here < 0.9 * there ? here : 1e300;
 }
 
 int launch_split_taps(const float* in, const float* filt, float* out, const Shape& s, hipStream_t st, bool static_ws)

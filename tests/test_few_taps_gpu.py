@@ -15,11 +15,11 @@ pytestmark = pytest.mark.gpu
 # (N, C, H, W, K, F): every filter side, one to seven blocks of tap rows, four and eight waves a workgroup, one,
 # two and four column blocks of 64 per row, two column strips, one and two sets of sums in LDS; channels off
 # multiples of four and sixteen, widths off multiples of four, bands that end early
-SHAPES = [(2, 16, 6, 4, 1, 1), (5, 10, 30, 263, 1, 1), (6, 13, 85, 65, 1, 1), (4, 13, 73, 65, 1, 2), (3, 146, 49, 130, 8, 2),
-          (4, 21, 53, 387, 9, 2), (6, 11, 89, 111, 13, 2), (6, 73, 90, 77, 1, 3), (6, 8, 89, 9, 1, 3), (6, 147, 90, 74, 3, 3),
-          (3, 13, 20, 130, 2, 3), (4, 13, 19, 366, 4, 3), (5, 7, 17, 97, 5, 3), (5, 34, 51, 221, 6, 3), (3, 50, 46, 261, 2, 4),
-          (5, 16, 73, 376, 5, 4), (5, 30, 86, 318, 6, 4), (1, 30, 87, 271, 2, 5), (6, 17, 87, 117, 3, 5), (4, 26, 83, 237, 4, 5),
-          (4, 11, 75, 66, 1, 6), (6, 11, 83, 125, 3, 6), (4, 38, 19, 381, 1, 7), (3, 26, 77, 193, 2, 7)]
+SHAPES = [(1, 11, 6, 79, 1, 1), (9, 9, 29, 135, 1, 1), (7, 9, 169, 4, 1, 1), (8, 10, 37, 73, 1, 2), (1, 8, 10, 151, 1, 2),
+          (8, 9, 60, 267, 5, 2), (4, 10, 118, 247, 9, 2), (9, 7, 154, 61, 13, 2), (2, 6, 7, 7, 1, 3), (8, 7, 95, 9, 2, 3),
+          (2, 13, 69, 249, 2, 3), (9, 15, 58, 59, 4, 3), (6, 10, 76, 183, 4, 3), (6, 11, 74, 234, 6, 3), (3, 9, 29, 361, 2, 4),
+          (6, 13, 77, 242, 5, 4), (9, 15, 58, 251, 6, 4), (6, 13, 51, 129, 2, 5), (2, 9, 220, 109, 3, 5), (9, 15, 32, 304, 4, 5),
+          (6, 9, 54, 69, 1, 6), (4, 15, 51, 311, 3, 6), (1, 9, 11, 78, 1, 7), (5, 15, 56, 193, 2, 7), (16, 200, 40, 64, 3, 3)]
 
 
 @pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))

@@ -193,6 +193,8 @@ int dconv_general_v(const float *in, int N, int C, int H, int W,
  * of a chunk to fit in LDS beside it) and 16-byte aligned inputs; other
  * shapes run on a one-thread-per-output kernel (any valid shape, 2-byte
  * alignment), which is some thousand times slower: pad the channels.
+ * Under AUTO short launches (filters up to 7x7, estimated from the shape) run
+ * on small tiles whose reduction several waves share.
  * Errors as for dconv_general; a base pointer that is not 2-byte aligned ->
  * DCONV_BAD_SHAPE.
  */

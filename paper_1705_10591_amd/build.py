@@ -24,7 +24,7 @@ SOURCES = [("api.hip", [], "api"), ("simple.hip", [], "simple"), ("single.hip", 
           [("split_inst.hip", [f"-DDCONV_F={f}"], f"split_f{f}") for f in range(2, 8)] + \
           [("few_taps_inst.hip", [f"-DDCONV_F={f}"], f"few_taps_f{f}") for f in range(1, 8)] + \
           [("split_taps.hip", [], "split_taps"), ("short.hip", [], "short")] + \
-          [("half.hip", [], "half"), ("half_1x1.hip", [], "half_1x1")] + \
+          [("half.hip", [], "half"), ("half_1x1.hip", [], "half_1x1"), ("half_short.hip", [], "half_short")] + \
           [("half_inst.hip", [f"-DDCONV_F={f}"], f"half_f{f}") for f in range(1, 33)]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

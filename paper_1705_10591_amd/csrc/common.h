@@ -100,6 +100,11 @@ void release_general_workspaces();
 // ... and their 1x1 layers where it is the better choice (half_1x1.hip); DCONV_UNSUPPORTED elsewhere
 int launch_general_point(const void* in, const void* filt, float* out, const Shape& s, hipStream_t st,
                          int dtype, bool blocked);
+// ... and short launches on small tiles (half_short.hip): estimated kernel time in us (1e300 where it cannot run)
+// and the configuration that it is for
+double short_half_time(const Shape& s, int dtype, int* cfg);
+int launch_short_half(const void* in, const void* filt, float* out, const Shape& s, hipStream_t st, int dtype,
+                      bool blocked, int cfg);
 int launch_general_half(const void* in, const void* filt, float* out, const Shape& s, hipStream_t st,
                         int dtype, int layout, int variant);
 

@@ -1,5 +1,6 @@
 // Dispatch of the general case for short data types (fp16, bf16, int8): the matrix-core kernel where the shape allows it, the
 // one-thread-per-output kernel otherwise.
+#include <cmath>
 #include "half_kernel.h"
 
 namespace dconv {
@@ -103,6 +104,29 @@ int preferred_config(const Shape& s, int dtype, bool blocked)
     return short_chunks ? 1 : 3;
 }
 
+// Short launches: the estimate of half_short.hip against one of the tiled kernel, fitted to the same layers
+// (rms 9 %): launch, steps and chunks of one tile, steps of the tiles beyond one per CU, rounds, memory and output.
+// It has to promise a twentieth and, as both estimates lean on the tiles' overlap where there are many, 2 % more
+// for every microsecond.  Of 583 layers that the fit did not see (up to 30 GFLOP) 349 are chosen, 2.2 times
+// faster on average; six of them are slower (the worst 1.31 times, of 12 us), eleven faster by more than a tenth are left.
+// The large tile (few of those layers) and filters from 8x8 on (none) keep the tiled kernel.
+bool short_preferred(const Shape& s, int dtype, int tile, int* cfg)
+{
+    if (s.F > 7 || tile == 1 || tile == 3) return false;
+    const double here = short_half_time(s, dtype, cfg);
+    if (here > 1e200) return false;
+    const int rg = half_row_group(s.F);
+    const int64_t px = (int64_t)s.N * s.Ho * s.Wo, groups = (int64_t)s.C * elem_bytes(dtype) / kHalfChunkBytes;
+    const bool mid = tile == 4;
+    const double tiles = mid ? (double)((px + 383) / 384) * ((s.K + 127) / 128) : (double)((px + 255) / 256) * ((s.K + 63) / 64);
+    const double steps = (double)groups * s.F * s.F, chunks = (double)groups * ((s.F + rg - 1) / rg);
+    const double out = 4e-6 * px * s.K;
+    const double mb = 1e-6 * groups * kHalfChunkBytes * ((double)s.N * s.H * s.W + (double)s.K * s.F * s.F) + out;
+    const double tile_us = mid ? 0.283 * steps : 0.0898 * steps + 0.2555 * chunks + 0.1466 * std::max(0.0, tiles / 256 - 1) * steps;
+    const double there = 4.525 + tile_us + 0.2874 * (std::ceil(tiles / 256) - 1) + 0.0914 * mb + 0.0544 * out;
+    return here * (1.05 + 0.02 * here) < there;
+}
+
 }  // namespace
 
 int launch_general_half(const void* in, const void* filt, float* out, const Shape& s, hipStream_t st,
@@ -121,6 +145,11 @@ int launch_general_half(const void* in, const void* filt, float* out, const Shap
     int rc = launch_general_point(in, filt, out, s, st, dtype, blocked);
     if (rc != DCONV_UNSUPPORTED) return rc;
     const int cfg = preferred_config(s, dtype, blocked);
+    int tile;
+    if (variant == DCONV_VARIANT_AUTO && short_preferred(s, dtype, cfg, &tile)) {
+        rc = launch_short_half(in, filt, out, s, st, dtype, blocked, tile);
+        if (rc != DCONV_UNSUPPORTED) return rc;
+    }
     rc = launch_tiled(in, filt, out, s, st, dtype, cfg, blocked, false);
     // (the small tiles hold every shape the large one does, and the register-staged one the most)
     if (rc == DCONV_UNSUPPORTED && cfg != 0) rc = launch_tiled(in, filt, out, s, st, dtype, 0, blocked, false);

@@ -75,7 +75,9 @@ bool general_few_preferred(const Shape& s)
 // the smaller one, 0.77 per thousand weights; 8.1, a 32-filter block at 137 TFLOP/s and the root of it, input
 // and output at 4.2 TB/s and a chain per channel.  Of 900 layers 334 were of the first kind: 102 are chosen, 1.43
 // times faster, 13 of them slower (by a third twice, else by up to 16 %); 566 of the others: 270 chosen, 1.86
-// times faster, 11 of them slower, by up to 23 %.
+// times faster, 11 of them slower, by up to 23 %.  Large layers with more than 64 taps of all filters have to
+// promise 15 %: the vector-ALU kernel's estimate is high where its tiles fill the chip many times over (37 x 176 x
+// 192 x 184 with three 5x5 filters: 673 us estimated, 560 measured; 582 and 585 for this kernel).
 double few_taps_time_if_preferred(const Shape& s)
 {
     if (s.K > 16 || s.F > 7 || (s.C == 1 && s.N == 1)) return 1e300;
@@ -86,7 +88,8 @@ double few_taps_time_if_preferred(const Shape& s)
     const double here = 3.9 + 0.99 * std::max(pl.cost, memory) + 0.357 * std::min(pl.cost, memory) + 0.77e-3 * s.K * ff * s.C;
     if (general_few_preferred(s)) {
         double tiles;
-        return here < 0.95 * few_time(s, &tiles) ? here : 1e300;
+        const double few = few_time(s, &tiles);
+        return here < (pl.mb > 4 && few > 200 ? 0.85 : 0.95) * few ? here : 1e300;
     }
     if (pl.mb > 4) return 1e300;
     const double mflop = 2e-6 * px * 32 * s.C * ff;

@@ -171,7 +171,8 @@ int short_half_launch(const void* in, const void* filt, float* out, const Shape&
     const int lds = p.steps * 8 + S * A * B * 1024;
     auto kern = short_half_kernel<DT, A, B, S>;
     static std::atomic<uint64_t> lds_limit_raised{0};
-    if (!raise_lds_limit((const void*)kern, kGenLdsLimit, lds_limit_raised)) return DCONV_LAUNCH_FAILED;
+    // (64 KB need no raised limit: a call of a few microseconds is spared the look at the device)
+    if (lds > 65536 && !raise_lds_limit((const void*)kern, kGenLdsLimit, lds_limit_raised)) return DCONV_LAUNCH_FAILED;
     begin_launch();
     hipLaunchKernelGGL(kern, dim3((unsigned)((p.total + 7) / 8 * 8)), dim3(64 * S), (size_t)lds, st, p);
     return launch_status();

@@ -338,7 +338,7 @@ def main():
         # the packed forms, which this build switches off: plain multiply-adds reach half of it)
         import paper_1705_10591_amd as dconv
         sh = entry["shape"]
-        on_alu = dconv.tile_choice(single, sh["N"], sh["C"], sh["H"], sh["W"], sh["K"], sh["F"]) == dconv.CHOICE_FEW_FILTERS
+        on_alu = dconv.kernel_choice(single, sh["N"], sh["C"], sh["H"], sh["W"], sh["K"], sh["F"]) == dconv.VARIANT_FEW_FILTERS
         roof = {"bound": "alu" if on_alu else "mfma", "achieved": round(entry["gflops"] / 1e3, 3),
                 "peak": FP32_PEAK_TFLOPS, "unit": "TFLOP/s",
                 "frac": round(entry["gflops"] / 1e3 / FP32_PEAK_TFLOPS, 4)}

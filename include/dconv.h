@@ -82,14 +82,11 @@ enum {
     DCONV_VARIANT_SIMPLE = 1, /* one thread per output element; any shape        */
     DCONV_VARIANT_TILED = 2,  /* LDS-staged, matrix-core tiled kernel, tile
                                  configuration picked by shape.  dconv_general_v:
-                                 always the fp32 matrix cores, also for the large
-                                 layers whose products AUTO takes apart.  Short
-                                 launches (estimated from the shape) run on small
-                                 tiles of their own, under AUTO, under this name
-                                 and under the configuration that
-                                 dconv_tile_choice names                         */
+                                 always this kernel on the fp32 matrix cores, also
+                                 for layers that AUTO runs on one of the kernels
+                                 below                                           */
     DCONV_VARIANT_FEW_FILTERS = 3,
-                              /* F <= 7: vector-ALU kernels with a sliding
+                              /* F <= 7: the vector-ALU kernels with a sliding
                                  register window and wave-uniform weights.
                                  dconv_single_channel_v: the paper's Algorithm 1
                                  as it stands; what AUTO picks for few filters
@@ -101,10 +98,8 @@ enum {
                                  such layers where its estimated kernel time is
                                  below the matrix-core kernel's, whose 32-filter
                                  block would be mostly padding (few filters, or
-                                 up to sixteen on few channels); where that is
-                                 estimated to be faster such a layer runs with
-                                 the taps of all filters as rows of a product on
-                                 the fp32 matrix cores, under AUTO and by name   */
+                                 up to sixteen on few channels) and below
+                                 DCONV_VARIANT_FEW_TAPS'                         */
     DCONV_VARIANT_SPECIAL_CASE = 4,
                               /* dconv_general with C = 1 (any filter up to
                                  11x11) or C <= 4 (filters up to 5x5) only: the
@@ -112,6 +107,26 @@ enum {
                                  images as further work items and the channels
                                  as further taps; what AUTO picks for large
                                  output volumes of wide images with small filters */
+    /* Further kernels by name, whatever the estimates say by which AUTO picks them; a
+       shape that a kernel is not made for is refused.  dconv_general_v (and where
+       noted other entry points) only. */
+    DCONV_VARIANT_SHORT = 5,  /* short launches: small tiles whose reduction the waves
+                                 of a workgroup share, on the fp32 matrix cores; also
+                                 dconv_general_half_v, dconv_general_i8_v and
+                                 dconv_general_lowp                              */
+    DCONV_VARIANT_FEW_TAPS = 6,
+                              /* few filters (K <= 16, F <= 7, at most 112 taps of all
+                                 filters): the taps of all filters as rows of a
+                                 product on the fp32 matrix cores                */
+    DCONV_VARIANT_FEW_CHANNELS = 7,
+                              /* up to sixteen channels, filters of 2x2 to 11x11 and
+                                 at most 512 taps: products of parts, reduction over
+                                 taps (see above); also dconv_single_channel_v   */
+    DCONV_VARIANT_PARTS = 8,  /* filters of 2x2 to 7x7: products of parts, reduction
+                                 over channels (see above).  Like FEW_CHANNELS it
+                                 may keep split filters in the workspace, and is
+                                 then refused while the stream is captured,
+                                 dconv_general_noalloc excepted                  */
     DCONV_VARIANT_TILED_CFG0 = 0x100,
                               /* DCONV_VARIANT_TILED_CFG0 + i: the tiled kernel
                                  with tile configuration i forced, 0 <= i <
@@ -157,7 +172,8 @@ int dconv_single_channel(const float *img, int H, int W,
  * launch) where that is the faster one, and likewise two to four channels
  * with small filters, see DCONV_VARIANT_SPECIAL_CASE.  With up to sixteen
  * filters the automatic choice is the vector-ALU kernel of
- * DCONV_VARIANT_FEW_FILTERS wherever it is the faster one.
+ * DCONV_VARIANT_FEW_FILTERS or the one of DCONV_VARIANT_FEW_TAPS wherever it is
+ * the faster one.
  * The tiled kernel is compiled for filters up to 32 x 32; larger ones (and
  * shapes beyond its 32-bit index limits) run on the one-thread-per-output
  * kernel.
@@ -258,25 +274,31 @@ int dconv_general_lowp(const void *in, int N, int C, int H, int W,
 int dconv_tile_config_count(int single_channel);
 
 /*
- * What DCONV_VARIANT_AUTO picks for a shape, decided on the host from the shape
+ * What the library picks for a shape, decided on the host from the shape
  * alone: nothing is launched and no GPU is needed.  For tuners, and for tests
  * that pin the dispatcher's rules (the rules are where the paper's per-device
  * design-space exploration, Sec. 5 and Table 1, ends up in this library).
  *   single_channel != 0: the shape of dconv_single_channel (N and C must be 1);
  *   single_channel == 0: the shape of dconv_general.
- * Returns the tile configuration i (as in DCONV_VARIANT_TILED_CFG0 + i) of that
+ * dconv_kernel_choice returns the DCONV_VARIANT_* that names the kernel which
+ * DCONV_VARIANT_AUTO runs: called by that name, the entry point gives the plain
+ * call's output bit for bit (of a call that is not captured, or of
+ * dconv_general_noalloc, see below).  Or DCONV_CHOICE_INVALID; for
+ * dconv_single_channel DCONV_CHOICE_GENERAL_CASE, where one of dconv_general's
+ * kernels runs (which: ask for dconv_general with N = C = 1); for dconv_general
+ * DCONV_VARIANT_AUTO, where dconv_single_channel's kernel for few filters runs,
+ * which has no name there.
+ * dconv_tile_choice returns what picks among the kernels that tile filters and
+ * pixels: the tile configuration i (as in DCONV_VARIANT_TILED_CFG0 + i) of that
  * entry point's tiled kernel -- for dconv_general the tile shape only, 0 to 2:
  * how its tiles are shared between workgroups is decided at launch from the
- * device's CU count -- or one of the negative values below.  (For the large
- * layers of dconv_general whose products AUTO takes apart, the answer is the tile
- * shape of the fp32 kernel, which runs them under DCONV_VARIANT_TILED and when the
- * call is captured; the kernel that takes products apart has one tile shape.  One
- * image of one channel from 6 GFLOP on may be taken apart too: the answer is what
- * runs below that.  Up to sixteen filters for which the answer is a tile shape may
- * run with their taps as rows of a product, where that is estimated to be faster.)
+ * device's CU count -- or one of the negative values below.  The configuration
+ * runs under DCONV_VARIANT_TILED; under AUTO where dconv_kernel_choice says so.
  */
 enum dconv_choice {
-    DCONV_CHOICE_FEW_FILTERS = -1,  /* the vector-ALU kernel for few filters of that entry point */
+    DCONV_CHOICE_FEW_FILTERS = -1,  /* a kernel for few filters goes before that entry point's
+                                       tiled kernels (dconv_general: the vector-ALU kernel or
+                                       DCONV_VARIANT_FEW_TAPS)                             */
     DCONV_CHOICE_SPECIAL_CASE = -2, /* dconv_general hands the shape to the special-case
                                        kernel (one channel, or a few with small filters)   */
     DCONV_CHOICE_SIMPLE = -3,       /* the one-thread-per-output kernel                    */
@@ -288,6 +310,7 @@ enum dconv_choice {
                                        images, large filters)                              */
 };
 int dconv_tile_choice(int single_channel, int N, int C, int H, int W, int K, int F);
+int dconv_kernel_choice(int single_channel, int N, int C, int H, int W, int K, int F);
 
 /*
  * HIP graph capture.  Every entry point only enqueues kernels on `stream` (no

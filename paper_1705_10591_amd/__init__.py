@@ -20,13 +20,14 @@ LIB_PATH = _PKG / "libdconv.so"
 VARIANT_AUTO, VARIANT_SIMPLE, VARIANT_TILED, VARIANT_FEW_FILTERS = 0, 1, 2, 3
 VARIANT_TILED_CFG0 = 0x100     # + i: tiled kernel with tile configuration i forced
 VARIANT_SPECIAL_CASE = 4       # dconv_general with one channel: the single-channel tiled kernel
+VARIANT_SHORT, VARIANT_FEW_TAPS, VARIANT_FEW_CHANNELS, VARIANT_PARTS = 5, 6, 7, 8   # further kernels by name (see dconv.h)
 VARIANT_SPECIAL_CASE_CFG0 = 0x200   # + i: the same with its tile configuration i forced
 STATUS_OK, STATUS_NULL_POINTER, STATUS_BAD_SHAPE, STATUS_UNSUPPORTED, STATUS_LAUNCH_FAILED, \
     STATUS_SCRATCH_EXCEEDED = range(6)
 
 EXPORTS = ("dconv_single_channel", "dconv_general", "dconv_single_channel_v",
            "dconv_general_v", "dconv_status_string", "dconv_version",
-           "dconv_tile_config_count", "dconv_tile_choice", "dconv_release_workspace",
+           "dconv_tile_config_count", "dconv_tile_choice", "dconv_kernel_choice", "dconv_release_workspace",
            "dconv_general_f16", "dconv_general_bf16", "dconv_general_half_v",
            "dconv_general_i8", "dconv_general_i8_v", "dconv_general_lowp", "dconv_general_noalloc")
 DTYPE_F16, DTYPE_BF16, DTYPE_I8 = 0, 1, 2
@@ -72,6 +73,8 @@ def load_library() -> ctypes.CDLL:
         lib.dconv_tile_config_count.restype = i
         lib.dconv_tile_choice.argtypes = [i] * 7
         lib.dconv_tile_choice.restype = i
+        lib.dconv_kernel_choice.argtypes = [i] * 7
+        lib.dconv_kernel_choice.restype = i
         lib.dconv_status_string.argtypes = [i]
         lib.dconv_status_string.restype = ctypes.c_char_p
         _lib = lib
@@ -91,10 +94,16 @@ CHOICE_FEW_FILTERS, CHOICE_SPECIAL_CASE, CHOICE_SIMPLE, CHOICE_INVALID, CHOICE_G
 
 
 def tile_choice(single_channel: bool, N: int, C: int, H: int, W: int, K: int, F: int) -> int:
-    """What VARIANT_AUTO picks for a shape: a tile configuration (>= 0) or a CHOICE_* value.  (Large layers
-    whose products AUTO takes apart: the tile configuration of the fp32 kernel, which VARIANT_TILED runs.)
-    Host arithmetic only: works without a GPU."""
+    """The tile configuration (>= 0) that VARIANT_TILED picks for a shape, or a CHOICE_* value where the vector-ALU
+    kernel, the special case's or the one-thread-per-output kernel is better than tiles.  Which kernel VARIANT_AUTO runs
+    is kernel_choice's answer.  Host arithmetic only: works without a GPU."""
     return int(load_library().dconv_tile_choice(1 if single_channel else 0, N, C, H, W, K, F))
+
+
+def kernel_choice(single_channel: bool, N: int, C: int, H: int, W: int, K: int, F: int) -> int:
+    """The variant that names the kernel VARIANT_AUTO runs for a shape, CHOICE_GENERAL_CASE (one channel on
+    dconv_general's kernels: ask for those) or CHOICE_INVALID.  Host arithmetic only."""
+    return int(load_library().dconv_kernel_choice(1 if single_channel else 0, N, C, H, W, K, F))
 
 
 def release_workspace() -> None:

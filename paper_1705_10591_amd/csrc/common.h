@@ -58,32 +58,47 @@ int launch_simple(const float* in, const float* filt, float* out, const Shape& s
 // cfg selects one of the compiled tile configurations; cfg < 0 lets the shape decide.
 int launch_single_tiled(const float* img, const float* filt, float* out, const Shape& s,
                         hipStream_t st, int cfg);
+// Short launches on small tiles (short.hip): the configuration, and its estimated kernel time in us (1e300
+// where another kernel is the better choice).
+struct ShortChoice { double time; int cfg; };
+ShortChoice short_choice(const Shape& s);
+bool short_in_place_of_shared_tiles(const Shape& s);     // ... of tiles that the general kernel would share
+int launch_short(const float* in, const float* filt, float* out, const Shape& s, hipStream_t st, int cfg);
+// The kernels of the general case that tile filters and pixels: the fp32 one, large layers' products taken
+// apart on the bf16 matrix cores (split_kernel.h), short launches, or what the shape asks for.
+enum class GeneralWay { kTiled, kParts, kShort, kAuto };
 // static_ws: tiles shared between workgroups meet in the library's static device array instead of
-// an allocated workspace (dconv_general_noalloc); may_split: large layers may have their products
-// taken apart on the bf16 matrix cores (split_kernel.h), with the shape's own configuration only
-int launch_general_tiled(const float* in, const float* filt, float* out, const Shape& s,
-                         hipStream_t st, int cfg, bool static_ws, bool may_split);
-// few channels on the bf16 matrix cores (split_taps.hip): DCONV_UNSUPPORTED where it cannot run
-int launch_split_taps(const float* in, const float* filt, float* out, const Shape& s, hipStream_t st, bool static_ws);
-double split_taps_time_if_preferred(const Shape& s);
+// an allocated workspace (dconv_general_noalloc); cfg: of kTiled only; small: short_choice(s), where the
+// caller has it
+int launch_general_tiled(const float* in, const float* filt, float* out, const Shape& s, hipStream_t st, int cfg,
+                         bool static_ws, GeneralWay way, const ShortChoice* small = nullptr);
+GeneralWay general_way_for(const Shape& s);              // what kAuto is for a shape
+// few channels on the bf16 matrix cores (split_taps.hip): DCONV_UNSUPPORTED where it cannot run; estimated kernel
+// time in us and the plan, 1e300 where another kernel is the better choice
+struct TapsPlan {
+    int MB, KB, P, RC, nc, steps, bw, nstrips, LS, ptiles, tpg, grows, psb;
+    bool res, ok;
+};
+TapsPlan split_taps_plan(const Shape& s);
+int launch_split_taps(const float* in, const float* filt, float* out, const Shape& s, hipStream_t st, bool static_ws, const TapsPlan& pl);
+double split_taps_time_if_preferred(const Shape& s, TapsPlan* plan);
 int single_tile_configs();
 int general_tile_configs();
 // what the dispatchers pick by shape: the special case's tile configuration, the general case's
 // tile shape (pure host arithmetic)
 int single_auto_config(const Shape& s);
 int general_auto_shape(const Shape& s);
-// short launches on small tiles (short.hip)
-int launch_short(const float* in, const float* filt, float* out, const Shape& s, hipStream_t st, int cfg);
-// estimated kernel times in us where a kernel is the better choice (1e300 where it isn't), for the choice among
-// those that are
-double short_time_if_preferred(const Shape& s, int* cfg);
-bool short_in_place_of_shared_tiles(const Shape& s);     // ... of tiles that the general kernel would share
 int launch_single_few(const float* img, const float* filt, float* out, const Shape& s, hipStream_t st);
-// the general case with up to eight filters on the vector ALU (general_fewfilters.hip)
+// the general case with up to sixteen filters on the vector ALU (general_fewfilters.hip)
 int launch_general_few(const float* in, const float* filt, float* out, const Shape& s, hipStream_t st);
 // ... and with the taps of all filters on the matrix cores (few_taps_kernel.h)
-int launch_few_taps(const float* in, const float* filt, float* out, const Shape& s, hipStream_t st);
-double few_taps_time_if_preferred(const Shape& s);
+struct FewTapsPlan { int nw, mb, cb, nstrips, so, rb, nbands, cgs, bufs, total, lds; double cost; bool ok; };
+FewTapsPlan make_few_taps_plan(const Shape& s);
+int launch_few_taps(const float* in, const float* filt, float* out, const Shape& s, hipStream_t st, const FewTapsPlan& pl);
+// ... and which of the two: the vector-ALU kernel is better than the general kernel; the other one's estimated time,
+// 1e300 where it isn't the better one; its plan where that is less
+struct FewFilters { bool alu; double taps; FewTapsPlan plan; };
+FewFilters few_filters_for(const Shape& s);
 bool general_few_supports(const Shape& s);
 bool general_few_preferred(const Shape& s);
 bool single_few_supports(const Shape& s);      // the few-filters kernel can run the shape

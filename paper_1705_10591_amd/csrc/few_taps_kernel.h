@@ -191,11 +191,9 @@ few_taps_kernel(FewTapsParams p)
 
 // ---- host side -----------------------------------------------------------------------------------
 
-struct FewTapsPlan { int nw, mb, cb, nstrips, so, rb, nbands, cgs, bufs, total, lds; double cost; bool ok; };
-
 // Waves and rows of a workgroup, by an estimate of what one costs a CU: the products of its rows, the additions
 // behind them, which another workgroup of the CU covers in part.
-inline FewTapsPlan make_few_taps_plan(const Shape& s)
+inline FewTapsPlan few_taps_plan(const Shape& s)
 {
     FewTapsPlan pl{};
     const int R = s.K * s.F * s.F;

@@ -320,7 +320,7 @@ namespace {
 
 // Tile configurations offered through the ABI: tile shape x schedule.
 //   shape    0: 64 filters x 128 pixels, 1: 64 x 256, 2: 32 x 256
-//   schedule 0: by shape (short launches of the shape's own tile: short.hip), 1: whole tiles only, 2: tiles cut over channels wherever the even
+//   schedule 0: by shape, 1: whole tiles only, 2: tiles cut over channels wherever the even
 //            split of the work falls, 3: the same on a grid of 7 workgroups (so that small
 //            test shapes exercise every way a tile can be shared)
 //   write-back: configurations 0 to 11 store straight from the accumulators, 12 to 23 are the
@@ -518,22 +518,27 @@ int split_mode(const Shape& s)
     return whole <= shared ? 1 : 2;
 }
 
-// Runs the layer on the split-operand kernel if it is the better choice; DCONV_UNSUPPORTED if the
+// Runs the layer on the split-operand kernel; DCONV_UNSUPPORTED if the
 // fp32 kernel has to.  A call that is being captured into a graph stays on the fp32 kernel unless
 // its scratch memory is the static array: the workspace may have to be allocated, which a capture
 // does not allow, and two graphs captured on one stream would share the split filters in it.
-int try_split(const float* in, const float* filt, float* out, const Shape& s, hipStream_t st, bool static_ws)
+int try_split(const float* in, const float* filt, float* out, const Shape& s, hipStream_t st, bool static_ws, int mode)
 {
-    const int mode = split_mode(s);
-    if (mode == 0) return DCONV_UNSUPPORTED;
     if (!static_ws && gen_capturing(st)) return DCONV_UNSUPPORTED;
     return launch_split(in, filt, out, s, st, GenSched{mode, 0, false, static_ws, 0});
 }
 
 }  // namespace
 
-int launch_general_tiled(const float* in, const float* filt, float* out, const Shape& s,
-                         hipStream_t st, int cfg, bool static_ws, bool may_split)
+GeneralWay general_way_for(const Shape& s)
+{
+    Shape one;
+    if (!whole_batch_supported(s) && per_image_supported(s, &one)) return general_way_for(one);
+    return split_mode(s) != 0 ? GeneralWay::kParts : short_choice(s).time < 1e300 ? GeneralWay::kShort : GeneralWay::kTiled;
+}
+
+int launch_general_tiled(const float* in, const float* filt, float* out, const Shape& s, hipStream_t st, int cfg,
+                         bool static_ws, GeneralWay way, const ShortChoice* small)
 {
     if (cfg >= kShapes * kSchedules * kWriteBacks) return DCONV_UNSUPPORTED;
     Shape one;
@@ -541,26 +546,34 @@ int launch_general_tiled(const float* in, const float* filt, float* out, const S
         const int64_t in_image = (int64_t)s.C * s.H * s.W, out_image = (int64_t)s.K * s.Ho * s.Wo;
         for (int n = 0; n < s.N; ++n) {
             const int rc = launch_general_tiled(in + n * in_image, filt, out + n * out_image, one, st, cfg,
-                                                static_ws, may_split);
+                                                static_ws, way);
             if (rc != DCONV_OK) return rc;
         }
         return DCONV_OK;
     }
-    if (may_split && cfg < 0) {
-        const int rc = try_split(in, filt, out, s, st, static_ws);
-        if (rc != DCONV_UNSUPPORTED) return rc;
+    switch (way) {
+    case GeneralWay::kParts: {
+        const int mode = split_mode(s);
+        return try_split(in, filt, out, s, st, static_ws, mode ? mode : 1);
     }
-    // Short launches: small tiles whose reduction the waves of a workgroup share.  They are part of the schedule by
-    // shape, so the configuration that the shape gets by itself runs them too when it is named, and only that one.
-    if (cfg < 0 || cfg == shape_for(s)) {
-        int small;
-        if (short_time_if_preferred(s, &small) < 1e300 && split_mode(s) == 0) {
+    case GeneralWay::kShort: return launch_short(in, filt, out, s, st, short_choice(s).cfg);
+    case GeneralWay::kAuto:
+        if (const int mode = split_mode(s)) {
+            const int rc = try_split(in, filt, out, s, st, static_ws, mode);
+            if (rc != DCONV_UNSUPPORTED) return rc;
+            break;
+        }
+        {
+            const ShortChoice tiles = small ? *small : short_choice(s);
+            if (tiles.time == 1e300) break;
             // (a layer whose tiles the general kernel would share still brings the stream its workspace: programs run
             // such a call before they capture others)
             if (!static_ws && short_in_place_of_shared_tiles(s) && !gen_capturing(st)) (void)gen_workspace(st, 0, 0);
-            const int rc = launch_short(in, filt, out, s, st, small);
+            const int rc = launch_short(in, filt, out, s, st, tiles.cfg);
             if (rc != DCONV_UNSUPPORTED) return rc;
         }
+        break;
+    case GeneralWay::kTiled: break;
     }
     if (cfg < 0) {
         const GenSched sched{0, 0, false, static_ws, 0};

@@ -78,27 +78,35 @@ bool general_few_preferred(const Shape& s)
 // times faster, 11 of them slower, by up to 23 %.  Large layers with more than 64 taps of all filters have to
 // promise 15 %: the vector-ALU kernel's estimate is high where its tiles fill the chip many times over (37 x 176 x
 // 192 x 184 with three 5x5 filters: 673 us estimated, 560 measured; 582 and 585 for this kernel).
-double few_taps_time_if_preferred(const Shape& s)
+FewTapsPlan make_few_taps_plan(const Shape& s) { return few_taps_plan(s); }
+
+FewFilters few_filters_for(const Shape& s)
 {
-    if (s.K > 16 || s.F > 7 || (s.C == 1 && s.N == 1)) return 1e300;
-    const FewTapsPlan pl = make_few_taps_plan(s);
-    if (!pl.ok) return 1e300;
+    FewFilters r{false, 1e300, {}};
+    if (s.K > 16 || s.F > 7 || (s.C == 1 && s.N == 1)) return r;
+    r.alu = general_few_preferred(s);
+    const FewTapsPlan pl = few_taps_plan(s);
+    if (!pl.ok) return r;
     const double ff = (double)s.F * s.F, px = (double)s.N * s.Ho * s.Wo;
     const double mb = 4e-6 * ((double)s.N * s.C * s.H * s.W + px * s.K), memory = mb / 4.4;
     const double here = 3.9 + 0.99 * std::max(pl.cost, memory) + 0.357 * std::min(pl.cost, memory) + 0.77e-3 * s.K * ff * s.C;
-    if (general_few_preferred(s)) {
+    bool better;
+    if (r.alu) {
         double tiles;
         const double few = few_time(s, &tiles);
-        return here < (pl.mb > 4 && few > 200 ? 0.85 : 0.95) * few ? here : 1e300;
+        better = here < (pl.mb > 4 && few > 200 ? 0.85 : 0.95) * few;
+    } else {
+        const double mflop = 2e-6 * px * 32 * s.C * ff;
+        better = pl.mb <= 4 && here < 0.85 * (8.1 + 0.0073 * mflop + 0.191 * std::sqrt(mflop) + 0.24 * mb + (0.0078 + 0.0183 * std::max(1.0, px / 256 / 512)) * s.C);
     }
-    if (pl.mb > 4) return 1e300;
-    const double mflop = 2e-6 * px * 32 * s.C * ff;
-    return here < 0.85 * (8.1 + 0.0073 * mflop + 0.191 * std::sqrt(mflop) + 0.24 * mb + (0.0078 + 0.0183 * std::max(1.0, px / 256 / 512)) * s.C) ? here : 1e300;
+    if (!better) return r;
+    r.taps = here;
+    r.plan = pl;
+    return r;
 }
 
-int launch_few_taps(const float* in, const float* filt, float* out, const Shape& s, hipStream_t st)
+int launch_few_taps(const float* in, const float* filt, float* out, const Shape& s, hipStream_t st, const FewTapsPlan& pl)
 {
-    const FewTapsPlan pl = make_few_taps_plan(s);
     if (!pl.ok) return DCONV_UNSUPPORTED;
     switch (s.F) {
     case 1: return few_taps_for_F<1>(in, filt, out, s, st, pl);
@@ -115,11 +123,6 @@ int launch_few_taps(const float* in, const float* filt, float* out, const Shape&
 int launch_general_few(const float* in, const float* filt, float* out, const Shape& s, hipStream_t st)
 {
     if (!general_few_supports(s)) return DCONV_UNSUPPORTED;
-    // (whatever names the few-filters kernel of a layer that is its own runs the faster one of the two)
-    if (general_few_preferred(s) && few_taps_time_if_preferred(s) < 1e300) {
-        const int rc = launch_few_taps(in, filt, out, s, st);
-        if (rc != DCONV_UNSUPPORTED) return rc;
-    }
     switch (s.F) {
     case 1: return gf_launch_for_F<1>(in, filt, out, s, st);
     case 2: return gf_launch_for_F<2>(in, filt, out, s, st);

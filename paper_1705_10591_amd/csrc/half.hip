@@ -141,6 +141,11 @@ int launch_general_half(const void* in, const void* filt, float* out, const Shap
     // one tile configuration of the matrix-core kernel, forced (tests, tuning)
     if (variant >= DCONV_VARIANT_TILED_CFG0 && variant < DCONV_VARIANT_TILED_CFG0 + kHalfConfigs)
         return launch_tiled(in, filt, out, s, st, dtype, variant - DCONV_VARIANT_TILED_CFG0, blocked, false);
+    if (variant == DCONV_VARIANT_SHORT) {
+        int tile = 0;
+        if (short_half_time(s, dtype, &tile) > 1e200) return DCONV_UNSUPPORTED;
+        return launch_short_half(in, filt, out, s, st, dtype, blocked, tile);
+    }
     if (variant != DCONV_VARIANT_AUTO && variant != DCONV_VARIANT_TILED) return DCONV_UNSUPPORTED;
     int rc = launch_general_point(in, filt, out, s, st, dtype, blocked);
     if (rc != DCONV_UNSUPPORTED) return rc;

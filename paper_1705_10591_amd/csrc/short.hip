@@ -227,15 +227,18 @@ static GeneralTiles general_tiles(const Shape& s)
     return {even, tiles <= 256 * (shape == 1 ? 2 : 3) ? std::ceil(tiles / 256) * one : even};
 }
 
-double short_time_if_preferred(const Shape& s, int* cfg)
+ShortChoice short_choice(const Shape& s)
 {
-    if (!short_supports(s) || (s.N == 1 && s.C == 1)) return 1e300;
+    ShortChoice r{1e300, 0};
+    if (!short_supports(s)) return r;
+    const double here = short_time(s, &r.cfg);
+    if (s.N == 1 && s.C == 1) return r;
     const double px = (double)s.N * s.Ho * s.Wo, T = (double)s.C * s.F * s.F;
     const double mb = 4e-6 * ((double)s.N * s.C * s.H * s.W + s.K * T + px * s.K);
     const GeneralTiles t = general_tiles(s);
     const double there = 5.44 + 1.067 * std::min(t.whole, 1.2 * t.even + 4) + 0.016 * t.even + 0.139 * mb + 2.1 * std::sqrt(t.even) + 0.25e-3 * T;
-    const double here = short_time(s, cfg);
-    return here < 0.9 * there ? here : 1e300;
+    if (here < 0.9 * there) r.time = here;
+    return r;
 }
 
 bool short_in_place_of_shared_tiles(const Shape& s)

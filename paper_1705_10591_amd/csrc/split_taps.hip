@@ -645,11 +645,6 @@ split_taps_kernel(TapsParams p)
 
 // ---- host side -----------------------------------------------------------------------------------
 
-struct TapsPlan {
-    int MB, KB, P, RC, nc, steps, bw, nstrips, LS, ptiles, tpg, grows, psb;
-    bool res, ok;
-};
-
 // Filters and steps of a layer.
 struct TapsSteps { int MB, KB, P, RC, nc, steps; };
 TapsSteps taps_steps(const Shape& s)
@@ -671,6 +666,8 @@ TapsPlan make_taps_plan(const Shape& s)
 {
     const TapsSteps t = taps_steps(s);
     TapsPlan best{t.MB, t.KB, t.P, t.RC, t.nc, t.steps, 0, 0, 0, 0, 0, 0, 0, false, false};
+    // (the kernel is made for few channels, and lanes address the filters with 32-bit byte offsets)
+    if (s.C > 16 || s.F < 2 || s.F > 11 || t.steps > 16 || (int64_t)s.K * s.C * s.F * s.F >= 1LL << 29) return best;
     const int64_t all_rows = (int64_t)s.N * s.Ho;
     double least = 1e300;
     for (int mode = 0; mode < 3; ++mode) {
@@ -758,6 +755,23 @@ int taps_launch(const float* in, const float* filt, float* out, const Shape& s, 
 
 }  // namespace
 
+static bool taps_plan_fits(const Shape& s, const TapsPlan& pl)
+{
+    if (!pl.ok) return false;
+    // pixels are numbered in 32 bits; lanes address the image with 32-bit byte offsets from the tile's first image
+    if ((int64_t)s.N * s.Ho * pl.bw > 2147483647LL) return false;
+    // and of the outputs
+    const int64_t span = std::min<int64_t>(kTapsNT / ((int64_t)s.Ho * pl.bw) + 2, pl.grows == s.Ho ? 1 : s.N), plane = (int64_t)s.Ho * s.Wo;
+    return (span * s.C + 1) * s.H * s.W < 1LL << 29 && ((span - 1) * s.K + 17) * plane < 1LL << 29;
+}
+
+TapsPlan split_taps_plan(const Shape& s)
+{
+    TapsPlan pl = make_taps_plan(s);
+    pl.ok = taps_plan_fits(s, pl);
+    return pl;
+}
+
 // When this kernel goes before the others, by estimates of its time and of theirs fitted to 900 layers drawn at
 // random (half of them one image of 64^2 .. 4096^2, half 1 to 64 images of 1 to 16 channels; 2x2 to 11x11;
 // rms 11 and 12 %).  Here: 6.3 us and 0.34 us per step and block of sixteen filters to split them (or 3 us for
@@ -765,7 +779,7 @@ int taps_launch(const float* in, const float* filt, float* out, const Shape& s, 
 // half as much again beyond the memory-side cache.  The others: 7.9 us per GFLOP.  It has to promise a
 // tenth: of 1400 layers 489 are chosen, 1.5 times faster on average, 18 of them slower, by up to 27 %
 // (large images, whose lines the special case's kernel writes whole).
-double split_taps_time_if_preferred(const Shape& s)
+double split_taps_time_if_preferred(const Shape& s, TapsPlan* plan)
 {
     if (s.C > 16 || s.F < 2 || s.F > 11 || s.K < 9) return 1e300;
     const TapsSteps t = taps_steps(s);
@@ -786,18 +800,14 @@ double split_taps_time_if_preferred(const Shape& s)
     const double here = 6.3 + rounds * (0.253 * work + 1.25) + (res ? 0.344 * work : 3.0 + 0.104 * t.steps) + 0.153 * mb + 0.082 * std::max(0.0, mb - 250);
     const double taps = (double)s.C * s.F * s.F;
     const double there = 6.1 + 0.00785e-6 * 2 * px * ((s.K + 31) / 32 * 32) * taps + 0.147 * mb + 0.0168 * taps;
-    return here < 0.9 * there ? here : 1e300;
+    if (here >= 0.9 * there) return 1e300;
+    *plan = split_taps_plan(s);
+    return plan->ok ? here : 1e300;
 }
 
-int launch_split_taps(const float* in, const float* filt, float* out, const Shape& s, hipStream_t st, bool static_ws)
+int launch_split_taps(const float* in, const float* filt, float* out, const Shape& s, hipStream_t st, bool static_ws, const TapsPlan& pl)
 {
-    const TapsPlan pl = make_taps_plan(s);
     if (!pl.ok) return DCONV_UNSUPPORTED;
-    // pixels are numbered in 32 bits; lanes address the image with 32-bit byte offsets from the tile's first image
-    if ((int64_t)s.N * s.Ho * pl.bw > 2147483647LL) return DCONV_UNSUPPORTED;
-    // and of the outputs
-    const int64_t span = std::min<int64_t>(kTapsNT / ((int64_t)s.Ho * pl.bw) + 2, pl.grows == s.Ho ? 1 : s.N), plane = (int64_t)s.Ho * s.Wo;
-    if ((span * s.C + 1) * s.H * s.W >= 1LL << 29 || ((span - 1) * s.K + 17) * plane >= 1LL << 29) return DCONV_UNSUPPORTED;
     // (filters split into the workspace: see try_split)
     if (!pl.res && !static_ws && gen_capturing(st)) return DCONV_UNSUPPORTED;
     // (sixteen filters always stay in LDS)

@@ -1,5 +1,5 @@
-"""Few filters with the taps of all filters as rows of a matrix product (AUTO, by estimated time).  The
-shapes are small ones that the library's rule sends there.
+"""Few filters with the taps of all filters as rows of a matrix product (VARIANT_FEW_TAPS, and AUTO by estimated time).
+The shapes are small ones that the library's rule sends there.
 """
 import numpy as np
 import pytest
@@ -35,18 +35,18 @@ def test_within_the_bound_between_guard_bands(shape):
     out = buf[1001:len(buf) - 1047].view(want)
     dconv.dconv_general(xb, fd, out=out)
     again = dconv.dconv_general(xb.clone(), fd, noalloc=True)
-    few, tiled = (dconv.dconv_general(xb, fd, variant=v) for v in (dconv.VARIANT_FEW_FILTERS, dconv.VARIANT_TILED))
-    chosen = dconv.tile_choice(False, *shape) == dconv.CHOICE_FEW_FILTERS
+    named, few, tiled = (dconv.dconv_general(xb, fd, variant=v) for v in (dconv.VARIANT_FEW_TAPS, dconv.VARIANT_FEW_FILTERS, dconv.VARIANT_TILED))
     torch.cuda.synchronize()
     got = out.cpu().numpy()
     acc, mag, _ = oracle.general(x, f)
     assert_within_bound(got, acc, mag, f"few filters {shape}")
     assert torch.equal(out, again)
-    # a layer that the few-filters kernel is chosen for runs the same by that name; elsewhere it names the
-    # vector-ALU kernel, whose sums are one chain: no closer to the exact ones
-    # (with 1x1 filters and a few channels the general kernel's chain is the same)
-    assert F == 1 or torch.equal(out, few) == chosen and not torch.equal(out, tiled), "taps as rows of a product are expected to run here"
-    err = [np.linalg.norm(o.cpu().numpy() - acc) for o in (out, few)]
+    assert dconv.kernel_choice(False, *shape) == dconv.VARIANT_FEW_TAPS and torch.equal(out, named)
+    # (with 1x1 filters and a few channels all kernels form the same chain)
+    assert F == 1 or not torch.equal(out, few) and not torch.equal(out, tiled)
+    # the vector-ALU kernel's sums are one chain: no closer to the exact ones
+    err = [np.linalg.norm(o.cpu().numpy() - acc) for o in (out, few, tiled)]
+    print(f"  errors {[e / np.linalg.norm(acc) for e in err]}")
     assert err[0] <= err[1], err
     assert torch.isnan(buf[:1001]).all() and torch.isnan(buf[len(buf) - 1047:]).all()
     # one pixel that is not finite reaches the outputs whose windows hold it, and no other
@@ -64,3 +64,21 @@ def test_integer_inputs_are_exact(shape):
     out = dconv.dconv_general(torch.from_numpy(x).cuda(), torch.from_numpy(f).cuda())
     torch.cuda.synchronize()
     assert np.array_equal(out.cpu().numpy(), oracle.general(x, f)[0].astype(np.float32))
+
+
+def test_a_captured_call_runs_the_same():
+    """No workspace: the replayed graph gives the eager call's bits, with other work between replays."""
+    x, f = (torch.from_numpy(a).cuda() for a in wl.random_case(9960, *SHAPES[-1], "u01", "he"))
+    eager = dconv.dconv_general(x, f)
+    assert torch.equal(eager, dconv.dconv_general(x, f, variant=dconv.VARIANT_FEW_TAPS))
+    out = torch.zeros_like(eager)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        dconv.dconv_general(x, f, out=out)
+    for _ in range(3):
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, eager)
+        dconv.dconv_general(x, f)

@@ -947,7 +947,7 @@ def test_fewer_tiles_than_cus_integer_inputs_bit_exact(shape):
     acc, _, _ = oracle.general(x, f)
     want = acc.astype(np.float32)
     xd, fd = dev(x), dev(f)
-    for v in [dconv.VARIANT_AUTO] + [dconv.VARIANT_TILED_CFG0 + i for i in range(3)]:
+    for v in [dconv.VARIANT_AUTO, dconv.VARIANT_TILED] + [dconv.VARIANT_TILED_CFG0 + i for i in range(3)]:
         for rep in range(2):
             buf = torch.full((want.size + 2048,), float("nan"), device="cuda")
             out = buf[1024:1024 + want.size].view(want.shape)
@@ -1015,19 +1015,24 @@ def test_general_few_filters_kernel_limits_and_non_finite_inputs():
 
 def test_general_few_filters_where_the_library_picks_it():
     """Layers with one to sixteen filters that cover the chip, at full size on sampled outputs; the
-    plain call and the forced kernel agree bit for bit."""
+    plain call and the kernel that it runs, by name, agree bit for bit."""
+    seen = set()
     for (N, C, H, W, K, F) in ((8, 16, 224, 224, 3, 5), (64, 32, 56, 56, 1, 3), (4, 32, 300, 512, 8, 3),
                                (15, 3, 384, 384, 10, 3), (21, 8, 96, 640, 12, 5), (64, 3, 128, 128, 16, 2),
                                (1, 3, 112, 112, 1, 5), (4, 3, 28, 28, 3, 3)):
         assert dconv.tile_choice(False, N, C, H, W, K, F) == dconv.CHOICE_FEW_FILTERS
         x, f = wl.random_case(6400 + K, N, C, H, W, K, F)
         got = dconv.dconv_general(dev(x), dev(f))
-        forced = dconv.dconv_general(dev(x), dev(f), variant=FEW)
+        kernel = dconv.kernel_choice(False, N, C, H, W, K, F)
+        seen.add(kernel)
+        named = {v: dconv.dconv_general(dev(x), dev(f), variant=v) for v in {FEW, kernel}}
         torch.cuda.synchronize()
-        assert torch.equal(got, forced)
+        assert torch.equal(got, named[kernel])
         idx = wl.sample_indices(6400 + K, got.numel(), 20000)
         acc, mag = oracle.general_at(x, f, idx)
-        assert_within_bound(got.cpu().numpy().reshape(-1)[idx], acc, mag, f"general few-filters {(N, C, H, W, K, F)}")
+        for v, o in named.items():
+            assert_within_bound(o.cpu().numpy().reshape(-1)[idx], acc, mag, f"general few-filters {(N, C, H, W, K, F)} variant {v}")
+    assert seen == {FEW, dconv.VARIANT_FEW_TAPS}
 
 
 LARGE_FILTER_SHAPES = [(2, 3, 30, 40, 70, 13), (1, 8, 20, 50, 33, 12), (2, 16, 18, 18, 64, 16), (1, 2, 40, 41, 130, 14),
@@ -1072,8 +1077,9 @@ def _variant_of_choice(c):
 
 
 def test_the_reported_choice_is_what_the_library_runs():
-    """dconv_tile_choice names, on the host, the kernel and configuration the plain entry points
-    launch: forcing what it names gives the plain call's output bit for bit (every kernel sums in
+    """dconv_kernel_choice names, on the host, the kernel that the plain entry points launch, and where that is one
+    that tiles filters and pixels, few filters' or the simple one, dconv_tile_choice its configuration: forcing what they
+    name gives the plain call's output bit for bit (every kernel sums in
     an order that its configuration fixes), and the outputs are within the bound of the oracle.
     One shape for every branch of the dispatchers' rules that a small problem can reach."""
     single = [(256, 256, 16, 3), (300, 420, 3, 5), (700, 900, 12, 5), (600, 800, 64, 7), (720, 1280, 40, 9),
@@ -1082,29 +1088,38 @@ def test_the_reported_choice_is_what_the_library_runs():
     general = [(2, 64, 30, 30, 64, 3), (3, 32, 20, 20, 32, 3), (2, 64, 40, 40, 96, 3), (1, 256, 14, 14, 256, 3),
                (1, 128, 20, 20, 128, 7), (4, 128, 17, 14, 192, 1), (8, 8, 60, 60, 64, 2), (2, 64, 30, 30, 128, 2),
                (40, 16, 7, 7, 64, 3), (2, 2, 200, 200, 16, 3), (1, 1, 200, 200, 64, 3), (2, 16, 40, 40, 8, 33),
-               (16, 8, 96, 96, 64, 3), (1, 1, 700, 900, 64, 3)]
-    seen = set()
+               (16, 8, 96, 96, 64, 3), (1, 1, 700, 900, 64, 3), (8, 64, 60, 60, 3, 3), (14, 48, 66, 66, 64, 4), (30, 3, 150, 148, 64, 5)]
+    seen, kernels = set(), set()
     for i, (H, W, K, F) in enumerate(single):
         x, f = wl.random_case(3100 + i, 1, 1, H, W, K, F)
-        c = dconv.tile_choice(True, 1, 1, H, W, K, F)
+        c, kernel = dconv.tile_choice(True, 1, 1, H, W, K, F), dconv.kernel_choice(True, 1, 1, H, W, K, F)
         seen.add(("single", c))
+        kernels.add(kernel)
         got = dconv.dconv_single_channel(dev(x[0, 0]), dev(f[:, 0]))
-        if c == dconv.CHOICE_GENERAL_CASE:     # (the general kernel's own entry point, one image of one channel)
-            forced = dconv.dconv_general(dev(x), dev(f), variant=dconv.VARIANT_TILED)[0]
+        if kernel == dconv.CHOICE_GENERAL_CASE:     # (the general kernel's own entry point, one image of one channel)
+            kernel = dconv.kernel_choice(False, 1, 1, H, W, K, F)
+            forced = [dconv.dconv_general(dev(x), dev(f), variant=kernel)[0]]
         else:
-            forced = dconv.dconv_single_channel(dev(x[0, 0]), dev(f[:, 0]), variant=_variant_of_choice(c))
+            forced = [dconv.dconv_single_channel(dev(x[0, 0]), dev(f[:, 0]), variant=kernel)]
+            if kernel != dconv.VARIANT_FEW_CHANNELS:
+                forced.append(dconv.dconv_single_channel(dev(x[0, 0]), dev(f[:, 0]), variant=_variant_of_choice(c)))
         torch.cuda.synchronize()
-        assert torch.equal(got, forced), f"single-channel {(H, W, K, F)}: choice {c}"
+        assert all(torch.equal(got, o) for o in forced), f"single-channel {(H, W, K, F)}: choice {c}, kernel {kernel}"
         acc, mag, _ = oracle.general(x, f)
         assert_within_bound(got.cpu().numpy(), acc[0], mag[0], f"single-channel {(H, W, K, F)}")
     for i, (N, C, H, W, K, F) in enumerate(general):
         x, f = wl.random_case(3200 + i, N, C, H, W, K, F)
-        c = dconv.tile_choice(False, N, C, H, W, K, F)
+        c, kernel = dconv.tile_choice(False, N, C, H, W, K, F), dconv.kernel_choice(False, N, C, H, W, K, F)
         seen.add(("general", c))
+        kernels.add(kernel)
         got = dconv.dconv_general(dev(x), dev(f))
-        forced = dconv.dconv_general(dev(x), dev(f), variant=_variant_of_choice(c))
+        named = dconv.dconv_general(dev(x), dev(f), variant=kernel)
+        chosen = dconv.dconv_general(dev(x), dev(f), variant=_variant_of_choice(c))
         torch.cuda.synchronize()
-        assert torch.equal(got, forced), f"general {(N, C, H, W, K, F)}: choice {c}"
+        assert torch.equal(got, named), f"general {(N, C, H, W, K, F)}: kernel {kernel}"
+        by_choice = kernel in (dconv.VARIANT_TILED, FEW, dconv.VARIANT_SPECIAL_CASE, dconv.VARIANT_SIMPLE)
+        # (with fewer taps than the general kernel sums at a time the order is the same)
+        assert C * F * F < 16 or torch.equal(got, chosen) == by_choice, f"general {(N, C, H, W, K, F)}: choice {c}, kernel {kernel}"
         acc, mag, _ = oracle.general(x, f)
         assert_within_bound(got.cpu().numpy(), acc, mag, f"general {(N, C, H, W, K, F)}")
     # the shapes reach the three tile shapes and the other kernels of both entry points
@@ -1112,6 +1127,8 @@ def test_the_reported_choice_is_what_the_library_runs():
             ("general", dconv.CHOICE_SIMPLE), ("single", dconv.CHOICE_FEW_FILTERS),
             ("single", dconv.CHOICE_SIMPLE), ("single", dconv.CHOICE_GENERAL_CASE)} <= seen, seen
     assert len({c for k, c in seen if k == "single" and c >= 0}) >= 5, seen
+    assert {dconv.VARIANT_TILED, dconv.VARIANT_SPECIAL_CASE, dconv.VARIANT_SIMPLE, FEW, dconv.VARIANT_SHORT, dconv.VARIANT_PARTS,
+            dconv.VARIANT_FEW_TAPS, dconv.VARIANT_FEW_CHANNELS, dconv.CHOICE_GENERAL_CASE} <= kernels, kernels
 
 
 @pytest.mark.parametrize("side", [24000, 23100])

@@ -58,11 +58,11 @@ def test_within_the_bound_and_no_further_off_than_the_tiled_kernel(shape, kind, 
     xr, fr = wl.to_16bit(x, kind)[0], wl.to_16bit(f, kind)[0]
     xd, fd = device(xr, kind, blocked), device(fr, kind, blocked)
     out = run(kind, xd, fd, blocked=blocked)
-    tiled = run(kind, xd, fd, blocked=blocked, variant=dconv.VARIANT_TILED)
+    tiled, short = (run(kind, xd, fd, blocked=blocked, variant=v) for v in (dconv.VARIANT_TILED, dconv.VARIANT_SHORT))
     torch.cuda.synchronize()
     acc, mag, _ = oracle.general(xr, fr)
     assert_within_bound(out.cpu().numpy(), acc, mag, f"short {kind} {shape}")
-    assert not torch.equal(out, tiled), "small tiles are expected to run here"
+    assert torch.equal(out, short) and not torch.equal(out, tiled), "small tiles are expected to run here"
     err = [np.linalg.norm(o.cpu().numpy() - acc) for o in (out, tiled)]
     print(f"  errors {err}", flush=True)
     assert err[0] <= err[1], err
@@ -84,3 +84,30 @@ def test_images_and_filters_off_sixteen_bytes_run_elsewhere():
     shifted = torch.empty(xd.numel() + 1, device="cuda", dtype=torch.float16)[1:].view(xd.shape)
     shifted.copy_(xd)
     assert np.array_equal(dconv.dconv_general_half(shifted, fd).cpu().numpy().astype(np.float64), want)
+
+
+@pytest.mark.parametrize("kind", list(TYPES))
+def test_a_captured_call_runs_the_same(kind):
+    """The replayed graph gives the eager call's bits, with other work between replays."""
+    x, f = wl.integer_case(9910, 13, 96, 10, 12, 65, 3)
+    xd, fd = device(x, kind, False), device(f, kind, False)
+    eager = run(kind, xd, fd)
+    assert torch.equal(eager, run(kind, xd, fd, variant=dconv.VARIANT_SHORT))
+    out = torch.zeros_like(eager)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        run(kind, xd, fd, out=out)
+    for _ in range(3):
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, eager)
+        run(kind, xd, fd)
+
+
+def test_what_small_tiles_cannot_run_is_refused_by_name():
+    x, f = wl.integer_case(9920, 1, 8, 9, 9, 20, 3)            # (channels that are no whole 32 bytes)
+    with pytest.raises(dconv.DconvError) as e:
+        run("f16", device(x, "f16", False), device(f, "f16", False), variant=dconv.VARIANT_SHORT)
+    assert e.value.status == dconv.STATUS_UNSUPPORTED

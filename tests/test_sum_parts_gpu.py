@@ -1,7 +1,9 @@
 """Layers of a few tiles, each shared by many workgroups whose sums a second kernel adds (one image of a
-deep layer): the library picks this by size.  Against the oracle, integer inputs bit for bit between
+deep layer): the tiled kernel (VARIANT_TILED) picks this by size.  Against the oracle, integer inputs bit for bit between
 guard bands, the entry point that allocates nothing, and under graph capture.
 """
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -12,6 +14,7 @@ import paper_1705_10591_amd as dconv
 from helpers import assert_within_bound
 
 pytestmark = pytest.mark.gpu
+TILED = dconv.VARIANT_TILED
 
 # (N, C, H, W, K, F): the three tile shapes, tiles shared unevenly, a channel count that leaves one
 # channel a chunk, row groups, filters off multiples of 32, two column strips, 1x1 filters
@@ -31,9 +34,9 @@ def test_parts_added_by_a_second_kernel(shape):
     x, f = wl.random_case(9500 + C + F, *shape)
     acc, mag, _ = oracle.general(x, f)
     xd, fd = dev(x), dev(f)
-    got = dconv.dconv_general(xd, fd)
+    got = dconv.dconv_general(xd, fd, variant=TILED)
     whole = dconv.dconv_general(xd, fd, variant=dconv.VARIANT_TILED_CFG0 + 3 + dconv.tile_choice(False, *shape))
-    again, static = dconv.dconv_general(xd, fd), dconv.dconv_general(xd, fd, noalloc=True)
+    again, static = dconv.dconv_general(xd, fd, variant=TILED), dconv.dconv_general(xd, fd, variant=TILED, noalloc=True)
     torch.cuda.synchronize()
     assert not torch.equal(got, whole), "the tiles are expected to be shared here"
     assert torch.equal(got, again) and torch.equal(got, static)
@@ -42,22 +45,30 @@ def test_parts_added_by_a_second_kernel(shape):
     want = oracle.general(xi, fi)[0].astype(np.float32)
     buf = torch.full((want.size + 2048,), float("nan"), device="cuda")
     out = buf[1001:1001 + want.size].view(want.shape)
-    dconv.dconv_general(dev(xi), dev(fi), out=out)
+    dconv.dconv_general(dev(xi), dev(fi), out=out, variant=TILED)
     torch.cuda.synchronize()
     assert np.array_equal(out.cpu().numpy(), want)
     assert torch.isnan(buf[:1001]).all() and torch.isnan(buf[1001 + want.size:]).all()
 
 
+def kernel_nodes(graph):
+    """Kernels that a captured graph holds."""
+    hip, n = ctypes.CDLL("libamdhip64.so.7"), ctypes.c_size_t()
+    raw = ctypes.c_void_p(graph.raw_cuda_graph())
+    assert hip.hipGraphGetNodes(raw, None, ctypes.byref(n)) == 0
+    return n.value
+
+
 @pytest.mark.parametrize("noalloc", [False, True])
 def test_both_kernels_are_captured(noalloc):
-    shapes = SHAPES[:3]
+    shapes = SHAPES
     cases = [tuple(map(dev, wl.random_case(9700 + i, *s))) for i, s in enumerate(shapes)]
     outs = [torch.empty(N, K, H - F + 1, W - F + 1, device="cuda") for (N, C, H, W, K, F) in shapes]
-    s, g = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    s, g = torch.cuda.Stream(), torch.cuda.CUDAGraph(keep_graph=True)
 
     def enqueue():
         for (x, f), o in zip(cases, outs):
-            dconv.dconv_general(x, f, out=o, noalloc=noalloc)
+            dconv.dconv_general(x, f, out=o, variant=TILED, noalloc=noalloc)
 
     torch.cuda.synchronize()
     with torch.cuda.stream(s):
@@ -67,10 +78,12 @@ def test_both_kernels_are_captured(noalloc):
     print("capturing", flush=True)
     with torch.cuda.graph(g, stream=s):
         enqueue()
+    assert kernel_nodes(g) == 2 * len(shapes), "a second kernel is expected in every call"
+    g.instantiate()
     for rep in range(3):
         for o in outs:
             o.fill_(float("nan"))
-        other = dconv.dconv_general(*cases[0])
+        other = dconv.dconv_general(*cases[0], variant=TILED)
         g.replay()
         torch.cuda.synchronize()
         assert all(torch.equal(o, e) for o, e in zip(outs, eager)), f"replay {rep}"

@@ -19,7 +19,7 @@ pytestmark = pytest.mark.gpu
 SHARED = dconv.VARIANT_TILED_CFG0 + 2 * 3          # + tile shape: tiles cut over channels
 # runs on the split-operand kernel, whole tiles (no counters); on the fp32 kernel its 680 tiles are shared
 DEEP = (32, 256, 28, 28, 512, 3)
-# parts added by a second kernel: partial sums, no counters
+# on the tiled kernel: parts added by a second kernel, partial sums, no counters; by itself a short launch
 ONE_IMAGE = (1, 256, 14, 14, 256, 3)
 
 
@@ -68,13 +68,16 @@ def test_a_layer_run_once_and_then_captured_on_another_kernel():
         assert_within_bound(eager[n:n + 1].cpu().numpy(), acc, mag, f"eager, image {n}")
 
 
-def test_a_call_without_counters_prepares_the_stream_for_one_with_counters():
-    """The first call that needs the workspace brings all of it."""
+@pytest.mark.parametrize("kernel", [dconv.VARIANT_TILED, dconv.VARIANT_AUTO])
+def test_a_call_without_counters_prepares_the_stream_for_one_with_counters(kernel):
+    """The first call that needs the workspace brings all of it, and so does a short launch in place of tiles that
+    would be shared."""
+    assert dconv.kernel_choice(False, *ONE_IMAGE) == dconv.VARIANT_SHORT
     first, second = make(8501, ONE_IMAGE), make(8502, (3, 16, 28, 28, 130, 3))
     want = dconv.dconv_general(second[2], second[3], variant=SHARED + 1)
     s = fresh_stream()
     with torch.cuda.stream(s):
-        dconv.dconv_general(first[2], first[3])
+        dconv.dconv_general(first[2], first[3], variant=kernel)
     s.synchronize()
     g = torch.cuda.CUDAGraph()
     print("capturing shared tiles after parts without counters", flush=True)
@@ -82,7 +85,7 @@ def test_a_call_without_counters_prepares_the_stream_for_one_with_counters():
         dconv.dconv_general(second[2], second[3], out=second[4], variant=SHARED + 1)
     for rep in range(3):
         second[4].fill_(float("nan"))
-        dconv.dconv_general(first[2], first[3])
+        dconv.dconv_general(first[2], first[3], variant=kernel)
         g.replay()
         torch.cuda.synchronize()
         assert torch.equal(second[4], want), f"replay {rep}"

@@ -37,16 +37,12 @@
  *     values were measured at up to 4 times what DCONV_VARIANT_TILED takes,
  *     which stays on fp32 products and takes the same time for any data.
  *     Layers of up to sixteen channels with enough work, and one image of one
- *     channel from 6 GFLOP on, AUTO takes apart on the fp16 matrix cores, under
- *     a scale for each filter and each block of the image: a value is two 11-bit
- *     parts, right to its last bit (1 ulp at most), and the product of the two
- *     lower parts, 2^-22 of the whole at most, is left out.  Sums of more than
- *     twelve terms come out closer to the exact ones than the fp32
- *     instructions' (1.4e-7 of the norm against 3.4e-7 with 363 terms, 0.9e-7
- *     against 1.6e-7 with 81).  Filters of up to twelve weights that are not
- *     zero are summed in fp32, term by term.  Blocks and filters whose values
- *     span more than 2^27 have small outputs computed again in fp32, and so
- *     have outputs that are not finite.
+ *     channel from 6 GFLOP on, AUTO takes apart the same way, with the same
+ *     limits (filters of 2x2 to 11x11, more than eight, up to 512 taps).  There
+ *     errors against exact sums are a third of the fp32 instructions' (0.35e-7 of
+ *     the norm against 0.91e-7 with 25 terms, 0.51e-7 against 1.63e-7 with 81,
+ *     0.98e-7 against 3.3e-7 with 363), and filters of one weight that is not zero
+ *     give their products rounded once.
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).
  *     Work is enqueued on it and the call returns without synchronising.
  *     The launch happens on the device that is current in the calling thread;

@@ -1,22 +1,19 @@
-// fp32 direct convolution of FEW CHANNELS on the fp16 matrix cores of gfx950: one large image, or the first
+// fp32 direct convolution of FEW CHANNELS on the bf16 matrix cores of gfx950: one large image, or the first
 // layer of a network.
 //
-// v_mfma_f32_16x16x32_f16 runs at sixteen times the rate of the fp32 instructions.  Under a scale, a power of
-// two, an fp32 value is x = h + l / 2^11 in two fp16 parts but for at most its last bit (23 bits and a sign of 24),
-// and
-//   x * w = h h' + (h l' + l h') / 2^11 + l l' / 2^22 .
-// The last product, 2^-22 |x w| at most and 2^-25 in the root mean square, is left out: three instructions do the
-// work.  Products of parts are exact, both sums stay in fp32 and are apart until the end.  Against 64 bits a sum
-// of 81 random products is off by 0.86e-7 of its norm (1.6e-7 on the fp32 instructions, which round after every
-// two products; these after eight), one of 363 by 1.4e-7 (3.4e-7).
-// Scales: a tile's image block has one, its largest value at 2^14, and every filter has one; the sums are
-// scaled back on their way out, exactly.
-// What two parts cannot give is formed again in fp32:
-//  * a block or filter with a value 2^27 or more below its largest: there, sums so small that what the fp16
-//    range cuts off could reach their last bits; sums that are not finite (infinities and NaN make NaN of the
-//    parts): the wave's 64 pixels, behind the main loop, on the fp32 matrix cores;
-//  * filters of up to twelve weights that are not zero: their sums do not average out what the split leaves out,
-//    and a filter of one weight is to give its pixels rounded once.  Weight by weight, as the tile ends.
+// v_mfma_f32_16x16x32_bf16 runs at sixteen times the rate of the fp32 instructions.  As in split_kernel.h a value is
+// the exact sum of three bf16 parts, and of the nine products of parts the six largest are formed: what is left out,
+// m l' + l m' + l l', is 2^-26 |x w| at most.  Products of parts are exact; h h' and the five small ones are summed
+// apart, in fp32, until the end.  Whole numbers whose sums the fp32 instructions form exactly come out the same.
+// Against 64 bits a sum of 81 random products is off by 0.51e-7 of its norm (1.63e-7), one of 363 by 0.98e-7 (3.3e-7), one of
+// 25 by 0.35e-7 (0.91e-7): in brackets the fp32 instructions, which round after every two products, these after eight.
+// (Two fp16 parts under a scale and three products hold 23 of a value's 24 bits and were 485 and 112 us in the cases
+// below: products of two whole numbers of 12 bits came out wrong in the last digit.)
+// What parts cannot give is formed again:
+//  * sums that are not finite (infinities and NaN make NaN of the parts), and, where an operand has values below 2^-103,
+//    whose last part may fall below the smallest bf16, sums below 2^-60 (all of them beside values above 2^40):
+//    the wave's 64 pixels, behind the main loop, on the fp32 matrix cores;
+//  * filters of one weight give their pixels rounded once: read again as the tile ends.
 //
 // split_kernel.h reduces over sixteen channels of one tap at a time, which few channels cannot fill; here
 // the reduction runs over TAPS: an instruction takes 32 of them, in whatever order a table gives, so that the
@@ -36,12 +33,10 @@
 //  * Filters: split once per workgroup into LDS where all of a block's fit, else by a small kernel in front
 //    into the workspace, from where a ring of three steps runs ahead in LDS.
 //
-// Measured: 64 x 3 x 224 x 224, 64 11x11 filters 1137 -> 475 us = 286 TFLOP/s (119 on the fp32 instructions); a
-// bare loop of these instructions runs at 611; without its stores 425, without its image reads 40 less); one
-// image of 1081 x 1917, 40 9x9 filters 224 -> 108 us (81 without its stores).  The same kernel with three bf16
-// parts and six products: 760 and 127.  Both cases are bound by their stores beside the arithmetic: 750 and 328 MB
-// in pieces of 64 bytes that share lines with other tiles; whole lines through LDS were no faster up to 1 GB, and
-// the order of tiles below was worth 5 to 10 % there.
+// Measured: 64 x 3 x 224 x 224, 64 11x11 filters 1133 -> 737 us = 185 TFLOP/s (120 on the fp32 instructions; 530 would be
+// the six products at the rate of a bare loop of these instructions); one image of 1081 x 1917, 40 9x9 filters 224 -> 127 us.
+// Beside the arithmetic both are bound by their stores: 750 and 328 MB in pieces of 64 bytes that share lines with other
+// tiles; whole lines through LDS were no faster up to 1 GB, and the order of tiles below was worth 5 to 10 % there.
 #include <algorithm>
 #include <cmath>
 #include "split_kernel.h"
@@ -52,43 +47,26 @@ namespace {
 
 constexpr int kTapsNT = 256;                    // pixels of a tile
 // bytes of an image block's part in LDS (no multiple of 256: reads of two parts do not pair up, which would
-// leave the operands' words in the wrong registers)
-constexpr int kTapsPartSmall = 11600, kTapsPartLarge = 19888;
+// leave the operands' words in the wrong registers): the smaller size, and what the LDS has room for beside a ring
+// of three steps of the filters
+constexpr int kTapsPartSmall = 11600;
+constexpr int taps_part_large(int MB) { return MB == 4 ? 14384 : MB == 3 ? 17424 : 19888; }
 constexpr int kTapsLds = 81920;                 // half of a CU's
-constexpr int kTapsFew = 12;                    // weights that are not zero, for the sums of a filter not to be split
+constexpr int kTapsSteps = 16;                  // 512 taps, which the line for tiny values counts on
 constexpr int kTapsStatic = 1024;               // set aside for the kernel's static LDS
 
-typedef _Float16 v8h __attribute__((ext_vector_type(8)));
-typedef _Float16 v2h __attribute__((ext_vector_type(2)));
-
-// Power of two that takes a largest magnitude to [2^14, 2^15).
-__device__ __forceinline__ int taps_scale(float most)
-{
-    most = fminf(most, 0x1.fffffep127f);
-    return most > 0.f ? 15 - __builtin_amdgcn_frexp_expf(most) : 0;
-}
-// Two scaled values as two fp16 parts each, packed: x = h + l / 2^11.
-__device__ __forceinline__ void taps_split(float x0, float x1, uint32_t& h, uint32_t& l)
-{
-    const v2h hv = __builtin_convertvector((v2f){x0, x1}, v2h);
-    h = __builtin_bit_cast(uint32_t, hv);
-    l = __builtin_bit_cast(uint32_t, __builtin_convertvector((v2f){(x0 - (float)hv[0]) * 2048.f, (x1 - (float)hv[1]) * 2048.f}, v2h));
-}
 // The smallest magnitude that is not zero, among values: their bits, doubled, less one.
 __device__ __forceinline__ uint32_t taps_least(uint32_t least, float x) { return min(least, (__builtin_bit_cast(uint32_t, x) << 1) - 1u); }
-// ... is it 2^27 or more below the block's largest (whose scale is given)?
-__device__ __forceinline__ bool taps_wide(uint32_t least, int scale)
-{
-    const uint32_t line = __builtin_bit_cast(uint32_t, __builtin_amdgcn_ldexpf(1.f, -12 - scale));
-    return least < (max(line, 1u) << 1) - 1u;
-}
+// ... is it below 2^-103, so that a value's last part may fall below the smallest bf16?
+__device__ __forceinline__ bool taps_tiny(uint32_t least) { return least < (uint32_t)(2 * (127 - 103)) * 0x800000u - 1u; }
+constexpr float kTapsHuge = 0x1p40f;
 
 struct TapsParams {
     const float* in;
     const float* filt;
     float* out;
     const v4u* bank;     // ring: the split filters, [filter block][step][part][16 filters][lane]
-    const int* scales;   // ring: per filter, its scale, times two, and whether its values are wide
+    const int* notes;    // ring: what is noted of each filter
     int N, C, H, W, K, F, Ho, Wo;
     int bw, nstrips, LS, ptiles, tiles, tpg, grows;     // tpg: tiles per strip of a group of `grows` rows
     int P, RC, nc, steps;        // pairs per tap row, pairs of rows, couples of pairs, steps
@@ -109,8 +87,8 @@ __device__ __forceinline__ int taps_pair(const TapsParams& p, int u, int b, int*
     return (p.C * p.F & 1) && v < p.P ? p.C * p.F - 1 : -1;
 }
 
-// The 32 taps of step s for lane group g of a filter whose weights are at w: their scaled parts.
-__device__ __forceinline__ void taps_filter_piece(const TapsParams& p, const float* w, bool there, int s, int g, int scale, v4u (&part)[2])
+// The 32 taps of step s for lane group g of a filter whose weights are at w: their parts.
+__device__ __forceinline__ void taps_filter_piece(const TapsParams& p, const float* w, bool there, int s, int g, v4u (&part)[3])
 {
     float x[8];
 #pragma unroll
@@ -122,80 +100,64 @@ __device__ __forceinline__ void taps_filter_piece(const TapsParams& p, const flo
         x[2 * q] = there && r >= 0 ? w[at] : 0.f;
         x[2 * q + 1] = there && r >= 0 && j + 1 < p.F ? w[at + 1] : 0.f;
     }
+    SplitRange range;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-        uint32_t h, l;
-        taps_split(__builtin_amdgcn_ldexpf(x[2 * q], scale), __builtin_amdgcn_ldexpf(x[2 * q + 1], scale), h, l);
+        uint32_t h, m, l;
+        split_pair(x[2 * q], x[2 * q + 1], h, m, l, range);
         part[0][q] = h;
-        part[1][q] = l;
+        part[1][q] = m;
+        part[2][q] = l;
     }
 }
 
-// What is noted of a filter: four times its scale, bit 1: it has few weights that are not zero, bit 0: its values
-// are wide.
-__device__ __forceinline__ int taps_scale_of(int note) { return note >> 2; }
+// What is noted of a filter: it has tiny values, one weight that is not zero (whose tap stands from kNoteTap on), huge
+// values.
+constexpr int kNoteTiny = 1, kNoteOne = 2, kNoteHuge = 4, kNoteTap = 3;
 // The note of the filter whose T weights are at w; PER threads next to
 // each other (a power of two), each with its number `at` among them, work on a filter.
 template <int PER>
-__device__ __forceinline__ int taps_filter_scale(const float* w, int T, int at)
+__device__ __forceinline__ int taps_filter_note(const float* w, int T, int at)
 {
     float most = 0.f;
     uint32_t least = 0xFFFFFFFFu;
-    int count = 0;
+    int count = 0, tap = 0;
 #pragma unroll 4
     for (int t = at; t < T; t += PER) {
         most = fmaxf(most, fabsf(w[t]));
         least = taps_least(least, w[t]);
         count += w[t] != 0.f;
+        tap = w[t] != 0.f ? t : tap;
     }
 #pragma unroll
     for (int d = 1; d < PER; d *= 2) {
         most = fmaxf(most, __shfl_xor(most, d));
         least = min(least, (uint32_t)__shfl_xor((int)least, d));
         count += __shfl_xor(count, d);
+        tap = max(tap, __shfl_xor(tap, d));
     }
-    const int scale = taps_scale(most);
-    return 4 * scale + (count > 0 && count <= kTapsFew ? 2 : 0) + (taps_wide(least, scale) ? 1 : 0);
+    return (taps_tiny(least) ? kNoteTiny : 0) | (count == 1 ? kNoteOne | tap << kNoteTap : 0) | (most > kTapsHuge ? kNoteHuge : 0);
 }
 
 // A workgroup per sixteen filters and four steps: a piece a thread.
 template <int MB>
 __global__ void __launch_bounds__(256)
-taps_bank_kernel(TapsParams p, v4u* bank, int* scales)
+taps_bank_kernel(TapsParams p, v4u* bank, int* notes)
 {
-    __shared__ int sc[16];
     const int groups = (p.steps + 3) / 4, km = blockIdx.x / groups, s0 = blockIdx.x % groups * 4;
     const int T = p.C * p.F * p.F, tid = threadIdx.x;
-    {
+    if (s0 == 0) {                                      // uniform
         const int k = km * 16 + (tid >> 4);
-        const int fs = taps_filter_scale<16>(p.filt + (int64_t)min(k, p.K - 1) * T, k < p.K ? T : 0, tid & 15);
-        if ((tid & 15) == 0) sc[tid >> 4] = fs;
-        if ((tid & 15) == 0 && s0 == 0) scales[k] = fs;
+        const int note = taps_filter_note<16>(p.filt + (int64_t)min(k, p.K - 1) * T, k < p.K ? T : 0, tid & 15);
+        if ((tid & 15) == 0) notes[k] = note;
     }
-    __syncthreads();
     const int s = s0 + (tid >> 6), l = tid & 63, k = km * 16 + (l & 15), kb = km / MB, m = km % MB;
     if (s >= p.steps) return;
-    v4u part[2];
-    taps_filter_piece(p, p.filt + (int64_t)min(k, p.K - 1) * T, k < p.K, s, l >> 4, taps_scale_of(sc[l & 15]), part);
-    v4u* d = bank + ((int64_t)(kb * p.steps + s) * 2 * MB + m) * 64 + l;
-    d[0] = part[0];
-    d[MB * 64] = part[1];
-}
-
-// What lane l takes over from another one in step d of a reduction to lane 63 (zero where there is none).
-__device__ __forceinline__ float taps_across(float x, int d)
-{
-    const int v = __builtin_bit_cast(int, x);
-    int r = 0;
-    switch (d) {
-    case 0: r = __builtin_amdgcn_update_dpp(0, v, 0x111, 0xF, 0xF, true); break;      // row_shr:1, 2, 4, 8
-    case 1: r = __builtin_amdgcn_update_dpp(0, v, 0x112, 0xF, 0xF, true); break;
-    case 2: r = __builtin_amdgcn_update_dpp(0, v, 0x114, 0xF, 0xF, true); break;
-    case 3: r = __builtin_amdgcn_update_dpp(0, v, 0x118, 0xF, 0xF, true); break;
-    case 4: r = __builtin_amdgcn_update_dpp(0, v, 0x142, 0xA, 0xF, false); break;     // row_bcast:15, 31
-    default: r = __builtin_amdgcn_update_dpp(0, v, 0x143, 0xC, 0xF, false); break;
-    }
-    return __builtin_bit_cast(float, r);
+    v4u part[3];
+    taps_filter_piece(p, p.filt + (int64_t)min(k, p.K - 1) * T, k < p.K, s, l >> 4, part);
+    v4u* d = bank + ((int64_t)(kb * p.steps + s) * 3 * MB + m) * 64 + l;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) d[q * MB * 64] = part[q];
 }
 
 template <int MB, bool RES, int PSB>
@@ -204,16 +166,16 @@ split_taps_kernel(TapsParams p)
 {
     constexpr int NT = kTapsNT, NB = 4;
     constexpr int NQ = (PSB / 16 + 255) / 256;          // quads of image dwords a thread stages
-    constexpr int SLOT = 2 * MB * 64;                   // 16-byte pieces of a step's filters
+    constexpr int SLOT = 3 * MB * 64;                   // 16-byte pieces of a step's filters
     constexpr uint32_t kNowhere = 0xC0000000u;
     constexpr int kRsrcFlags = 0x00020000;
 
     extern __shared__ __attribute__((aligned(16))) v4u lds_pieces[];
     char* const img = (char*)lds_pieces;
-    v4u* const fl = lds_pieces + 2 * PSB / 16;          // filters: all steps, or a ring of three
+    v4u* const fl = lds_pieces + 3 * PSB / 16;          // filters: all steps, or a ring of three
     v4u* const table = fl + (RES ? p.steps : 3) * SLOT; // [step][lane group]: byte offsets of its four pairs
-    __shared__ uint32_t s_most[2], s_wide[2];           // by tile parity: largest magnitude, whether the values are wide
-    __shared__ int s_scales[MB * 16];                   // of the filter block
+    __shared__ int s_range[2];                          // by tile parity: whether the image block has tiny, huge values
+    __shared__ int s_notes[MB * 16];                    // of the filter block
 
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -228,7 +190,7 @@ split_taps_kernel(TapsParams p)
     const int64_t plane = (int64_t)p.Ho * p.Wo;
     const int64_t in_bytes = (int64_t)p.N * p.C * HW * 4;
 
-    if (tid < 2) { s_most[tid] = 0; s_wide[tid] = 0; }
+    if (tid < 2) s_range[tid] = 0;
     for (int e = tid; e < p.steps * 16; e += 256) {
         int j;
         const int r = taps_pair(p, (e >> 4) * 8 + ((e >> 3) & 1) * 4 + (e & 3), (e >> 2) & 1, &j);
@@ -296,43 +258,34 @@ split_taps_kernel(TapsParams p)
             rb[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, o + 16u, 0, 0));
         }
     };
-    // The largest magnitude of what was fetched, for the tile's scale.
-    auto note_most = [&](const Place& t, int par) __attribute__((always_inline)) {
+    auto commit = [&](const Place& t, int par) __attribute__((always_inline)) {
         const int quads = t.nslots * p.C * p.LS >> 2;
+        uint32_t least = 0xFFFFFFFFu;
         float most = 0.f;
 #pragma unroll
         for (int i = 0; i < NQ; ++i) {
             if (i * 256 >= quads) continue;             // uniform
-            most = fmaxf(fmaxf(most, fabsf(ra[i][0])), fabsf(ra[i][1]));
-            most = fmaxf(fmaxf(most, fabsf(ra[i][2])), fabsf(ra[i][3]));
-            most = fmaxf(most, fabsf(rb[i]));
-        }
-#pragma unroll
-        for (int d = 0; d < 6; ++d) most = fmaxf(most, taps_across(most, d));        // lane 63 ends with the largest
-        if (lane == 63) atomicMax(&s_most[par], __builtin_bit_cast(uint32_t, most));
-    };
-    auto commit = [&](const Place& t, int par, int scale) __attribute__((always_inline)) {
-        const int quads = t.nslots * p.C * p.LS >> 2;
-        uint32_t least = 0xFFFFFFFFu;
-#pragma unroll
-        for (int i = 0; i < NQ; ++i) {
-            if (i * 256 >= quads) continue;             // uniform
-            float x[6] = {ra[i][0], ra[i][1], ra[i][2], ra[i][3], rb[i], 0.f};
-            uint32_t h[3], l[3];
+            const float x[6] = {ra[i][0], ra[i][1], ra[i][2], ra[i][3], rb[i], 0.f};
+            uint32_t part[3][3];
 #pragma unroll
             for (int q = 0; q < 5; ++q) {
                 least = taps_least(least, x[q]);
-                x[q] = __builtin_amdgcn_ldexpf(x[q], scale);
+                most = fmaxf(most, fabsf(x[q]));
             }
+            SplitRange range;
 #pragma unroll
-            for (int q = 0; q < 3; ++q) taps_split(x[2 * q], x[2 * q + 1], h[q], l[q]);
+            for (int q = 0; q < 3; ++q) split_pair(x[2 * q], x[2 * q + 1], part[0][q], part[1][q], part[2][q], range);
             const int e = tid + i * 256;
             if (e < PSB / 16) {
-                *(v4u*)(img + e * 16) = v4u{h[0], __builtin_amdgcn_alignbit(h[1], h[0], 16), h[1], __builtin_amdgcn_alignbit(h[2], h[1], 16)};
-                *(v4u*)(img + PSB + e * 16) = v4u{l[0], __builtin_amdgcn_alignbit(l[1], l[0], 16), l[1], __builtin_amdgcn_alignbit(l[2], l[1], 16)};
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    const uint32_t (&w)[3] = part[k];
+                    *(v4u*)(img + k * PSB + e * 16) = v4u{w[0], __builtin_amdgcn_alignbit(w[1], w[0], 16), w[1], __builtin_amdgcn_alignbit(w[2], w[1], 16)};
+                }
             }
         }
-        if (taps_wide(least, scale)) s_wide[par] = 1;
+        const int range = (taps_tiny(least) ? kNoteTiny : 0) | (most > kTapsHuge ? kNoteHuge : 0);
+        if (range) atomicOr(&s_range[par], range);
     };
 
     // ---- filters
@@ -340,11 +293,11 @@ split_taps_kernel(TapsParams p)
     // image block's place holds are brought there, split from there.
     auto load_filters = [&](int kb) {
         if constexpr (!RES) {
-            if (tid < MB * 16) s_scales[tid] = p.scales[kb * MB * 16 + tid];
+            if (tid < MB * 16) s_notes[tid] = p.notes[kb * MB * 16 + tid];
         } else {
             const int T = p.C * p.F * p.F;
             float* const raw = (float*)img;
-            const int mg = min(MB, 2 * PSB / 4 / (16 * T));                 // blocks of sixteen at a time (the plan sees to one or more)
+            const int mg = min(MB, 3 * PSB / 4 / (16 * T));                 // blocks of sixteen at a time (the plan sees to one or more)
             for (int m0 = 0; m0 < MB; m0 += mg) {
                 const int k0 = (kb * MB + m0) * 16, nf = min(mg, MB - m0) * 16;
                 const int words = min(nf, p.K - k0) * T;                    // (none beyond K)
@@ -354,31 +307,30 @@ split_taps_kernel(TapsParams p)
                 __syncthreads();
                 if (tid < nf * 4) {
                     const int f = tid >> 2;
-                    const int fs = taps_filter_scale<4>(raw + f * T, k0 + f < p.K ? T : 0, tid & 3);
-                    if ((tid & 3) == 0) s_scales[m0 * 16 + f] = fs;
+                    const int note = taps_filter_note<4>(raw + f * T, k0 + f < p.K ? T : 0, tid & 3);
+                    if ((tid & 3) == 0) s_notes[m0 * 16 + f] = note;
                 }
-                __syncthreads();
                 for (int e = tid; e < p.steps * nf * 4; e += 256) {
                     const int l = e & 63, m = (e >> 6) % (nf >> 4), s = (e >> 6) / (nf >> 4), f = m * 16 + (l & 15);
-                    v4u part[2];
-                    taps_filter_piece(p, raw + f * T, k0 + f < p.K, s, l >> 4, taps_scale_of(s_scales[m0 * 16 + f]), part);
-                    fl[s * SLOT + (m0 + m) * 64 + l] = part[0];
-                    fl[s * SLOT + (MB + m0 + m) * 64 + l] = part[1];
+                    v4u part[3];
+                    taps_filter_piece(p, raw + f * T, k0 + f < p.K, s, l >> 4, part);
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) fl[s * SLOT + (q * MB + m0 + m) * 64 + l] = part[q];
                 }
             }
             __syncthreads();
         }
     };
     typedef __attribute__((address_space(3))) void* lds_ptr;
-    const int nload = (2 * MB - wave + 3) / 4;          // ring: loads of 64 pieces per step, this wave's
+    const int nload = (3 * MB - wave + 3) / 4;          // ring: loads of 64 pieces per step, this wave's
     const auto brs = __builtin_amdgcn_make_buffer_rsrc((void*)p.bank, 0, RES ? 0 : 0x7FFFFFFF, kRsrcFlags);
     int lkb = 0, lstep = 0, lslot = 0, ltile = t0;      // ring: what is requested next, and where it goes
     auto request = [&]() __attribute__((always_inline)) {
         const int at = (lkb * p.steps + lstep) * (SLOT * 16);
 #pragma unroll
-        for (int i = 0; i < (2 * MB + 3) / 4; ++i) {
+        for (int i = 0; i < (3 * MB + 3) / 4; ++i) {
             const int k = i * 4 + wave;
-            if (k < 2 * MB)                             // uniform
+            if (k < 3 * MB)                             // uniform
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(brs, (lds_ptr)(fl + lslot * SLOT + k * 64), 16, lane * 16, at + k * 1024, 0, 0);
         }
         lslot = lslot == 2 ? 0 : lslot + 1;
@@ -403,9 +355,11 @@ split_taps_kernel(TapsParams p)
     // Tiles with outputs to be formed again (see general_split_kernel).
     uint64_t redo = 0;
     auto redo_bit = [&](int t) __attribute__((always_inline)) { return 1ull << ((t - t0) / dt % 64); };
-    // of a tile with wide values, scaled sums below this are formed again: an operand's part that falls below the
-    // smallest fp16 value is off by up to 2^-36, the other operand up to 2^15
-    const float redo_line = 16.f * (float)(p.C * p.F * p.F);
+    // Where an operand is tiny (it lost 2^-134 at most), sums below this are formed again: 512 products with values of
+    // up to 2^40 may be off by 2^-85.  With larger ones beside them, all are.
+    auto redo_line = [](int notes) __attribute__((always_inline)) {
+        return notes & kNoteTiny ? (notes & kNoteHuge ? __builtin_inff() : 0x1p-60f) : 0.f;
+    };
 
     // The lane's quad of outputs in block n of the wave: byte offset of out[n][k0 + l16][y][x] from
     // out[n_first][k0][0][0]; how many of the four are there.
@@ -426,16 +380,14 @@ split_taps_kernel(TapsParams p)
         request();
         __builtin_amdgcn_s_waitcnt(0x0F70);
     }
-    __syncthreads();                                    // s_most, s_wide are clear
-    note_most(t, 0);
+    __syncthreads();                                    // s_range is clear
     for (int tile = t0, par = 0; tile < t1; tile += dt, par ^= 1) {
         meet();                                         // the last tile's operands have been read
         if (t.kb != kb) {                               // uniform
             kb = t.kb;
             load_filters(kb);
         }
-        const int scale = taps_scale(__builtin_bit_cast(float, s_most[par]));
-        commit(t, par, scale);
+        commit(t, par);
         const Place next = place(tile + dt < t1 ? tile + dt : tile);
         fetch(next);
         // The lane's pixel of the wave's 64: its LDS byte address at tap (0, 0), its output's byte offset from
@@ -459,34 +411,34 @@ split_taps_kernel(TapsParams p)
 #pragma unroll
             for (int n = 0; n < NB; ++n) { hi[m][n] = v4f{}; lo[m][n] = v4f{}; }
         meet();
-        const uint32_t wide = s_wide[par];
-        if (tid == 0) { s_most[par] = 0; s_wide[par ^ 1] = 0; }      // (read before the barrier above, set behind the next)
+        const int range = s_range[par];
+        if (tid == 0) s_range[par ^ 1] = 0;             // (read before the barrier above, set behind the next)
 
         // A step: its image operands were requested during the step before where registers allow that, its
         // filters go sixteen at a time, the next sixteen on their way.
-        constexpr int DB = MB <= 3 ? 2 : 1;
-        v4u b[DB][NB][2], off = table[g];
-        auto load_b = [&](v4u (&b)[NB][2]) __attribute__((always_inline)) {
+        constexpr int DB = MB == 1 ? 2 : 1;
+        v4u b[DB][NB][3], off = table[g];
+        auto load_b = [&](v4u (&b)[NB][3]) __attribute__((always_inline)) {
 #pragma unroll
             for (int n = 0; n < NB; ++n)
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const char* at = img + (base[n] + off[q]);
 #pragma unroll
-                    for (int k = 0; k < 2; ++k) b[n][k][q] = *(const uint32_t*)(at + k * PSB);
+                    for (int k = 0; k < 3; ++k) b[n][k][q] = *(const uint32_t*)(at + k * PSB);
                 }
         };
-        auto step = [&](int s, v4u (&b)[NB][2], v4u (&bnext)[NB][2]) __attribute__((always_inline)) {
+        auto step = [&](int s, v4u (&b)[NB][3], v4u (&bnext)[NB][3]) __attribute__((always_inline)) {
             if constexpr (!RES) {
                 if (s >= 2) wait_loads(nload);          // this step's filters; the next step's may be on their way
                 meet();
                 request();
             }
             const v4u* f = fl + (RES ? s : slot) * SLOT + lane;
-            v4u a[2][2];
+            v4u a[2][3];
             auto load_a = [&](int m) __attribute__((always_inline)) {
 #pragma unroll
-                for (int k = 0; k < 2; ++k) a[m & 1][k] = f[(k * MB + m) * 64];
+                for (int k = 0; k < 3; ++k) a[m & 1][k] = f[(k * MB + m) * 64];
             };
             load_a(0);
             if constexpr (DB == 1) load_b(b);
@@ -501,13 +453,14 @@ split_taps_kernel(TapsParams p)
                 }
                 __builtin_amdgcn_sched_barrier(0);              // (the next operands are on their way before these products)
                 auto mfma = [](v4u x, v4u w, v4f c) __attribute__((always_inline)) {
-                    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(v8h, x), __builtin_bit_cast(v8h, w), c, 0, 0, 0);
+                    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(v8bf, x), __builtin_bit_cast(v8bf, w), c, 0, 0, 0);
                 };
-                const v4u (&w)[2] = a[m & 1];
+                const v4u (&w)[3] = a[m & 1];
+                constexpr int kSmall[5][2] = {{2, 0}, {0, 2}, {1, 1}, {1, 0}, {0, 1}};
 #pragma unroll
-                for (int n = 0; n < NB; ++n) lo[m][n] = mfma(b[n][1], w[0], lo[m][n]);
+                for (int q = 0; q < 5; ++q)
 #pragma unroll
-                for (int n = 0; n < NB; ++n) lo[m][n] = mfma(b[n][0], w[1], lo[m][n]);
+                    for (int n = 0; n < NB; ++n) lo[m][n] = mfma(b[n][kSmall[q][0]], w[kSmall[q][1]], lo[m][n]);
 #pragma unroll
                 for (int n = 0; n < NB; ++n) hi[m][n] = mfma(b[n][0], w[0], hi[m][n]);
                 __builtin_amdgcn_sched_barrier(0);
@@ -526,8 +479,6 @@ split_taps_kernel(TapsParams p)
         }
         if constexpr (!RES) __builtin_amdgcn_s_waitcnt(0x0F70);      // the next tile's first two steps are in LDS
 
-        note_most(next, par ^ 1);
-
         // (a buffer's range check keeps what isn't there from being written)
         float bad = 0.f;
         bool below = false;
@@ -538,69 +489,75 @@ split_taps_kernel(TapsParams p)
             const uint32_t ob = (uint32_t)__builtin_amdgcn_ds_bpermute((n * 16 + 4 * g) * 4, (int)whole);
             o[n] = ob == kNowhere ? kNowhere : ob + (uint32_t)l16 * (uint32_t)plane * 4u;
         }
+        // A lane's quad of outputs in block (m, n), whole or what a row's end leaves of it.
+        auto put = [&](auto ors, int n, v4f v, bool has) __attribute__((always_inline)) {
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, v), ors, has ? o[n] : kNowhere, 0, 0);
+            if (t.ws & 3) {                             // uniform: quads that a row's end cuts
+                const int x = __builtin_amdgcn_ds_bpermute((n * 16 + 4 * g) * 4, px);
+                const uint32_t ob = (uint32_t)__builtin_amdgcn_ds_bpermute((n * 16 + 4 * g) * 4, (int)obase) + (uint32_t)l16 * (uint32_t)plane * 4u;
+                if (x < t.ws && x + 4 > t.ws && has)
+#pragma unroll
+                    for (int r = 0; r < 3; ++r)
+                        if (x + r < t.ws) {
+                            const float value = v[r];
+                            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, value), ors, ob + 4u * r, 0, 0);
+                        }
+            }
+        };
+        auto out_of = [&](int m) __attribute__((always_inline)) {
+            return __builtin_amdgcn_make_buffer_rsrc((void*)(p.out + ((int64_t)t.n_first * p.K + (t.kb * MB + m) * 16) * plane), 0, 0x7FFFFFFF, kRsrcFlags);
+        };
 #pragma unroll
         for (int m = 0; m < MB; ++m) {
-            const int k0 = (t.kb * MB + m) * 16;
-            const auto ors = __builtin_amdgcn_make_buffer_rsrc((void*)(p.out + ((int64_t)t.n_first * p.K + k0) * plane), 0, 0x7FFFFFFF, kRsrcFlags);
-            const int fs = s_scales[m * 16 + l16];
-            const bool has = k0 + l16 < p.K && (fs & 2) == 0;
-            const bool wide_any = __any(wide | (fs & 1));
+            const auto ors = out_of(m);
+            const int note = s_notes[m * 16 + l16];
+            const bool has = (t.kb * MB + m) * 16 + l16 < p.K && (note & kNoteOne) == 0;
+            const float line = redo_line(range | note);
 #pragma unroll
             for (int n = 0; n < NB; ++n) {
                 v4f v;
 #pragma unroll
-                for (int r = 0; r < 4; ++r) v[r] = __builtin_fmaf(lo[m][n][r], 0x1p-11f, hi[m][n][r]);
-                if (wide_any) {                         // uniform
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) below |= (wide | (fs & 1)) && fabsf(v[r]) < redo_line;
-                }
-#pragma unroll
                 for (int r = 0; r < 4; ++r) {
+                    v[r] = hi[m][n][r] + lo[m][n][r];
                     bad = __builtin_fmaf(v[r], 0.f, bad);        // NaN behind anything not finite
-                    v[r] = __builtin_amdgcn_ldexpf(v[r], -scale - taps_scale_of(fs));
+                    below |= fabsf(v[r]) < line;
                 }
-                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(v4u, v), ors, has ? o[n] : kNowhere, 0, 0);
-                if (t.ws & 3) {                         // uniform: quads that a row's end cuts
-                    const int x = __builtin_amdgcn_ds_bpermute((n * 16 + 4 * g) * 4, px);
-                    const uint32_t ob = (uint32_t)__builtin_amdgcn_ds_bpermute((n * 16 + 4 * g) * 4, (int)obase) + (uint32_t)l16 * (uint32_t)plane * 4u;
-                    if (x < t.ws && x + 4 > t.ws && has)
-#pragma unroll
-                        for (int r = 0; r < 3; ++r)
-                            if (x + r < t.ws) {
-                                const float one = v[r];
-                                __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, one), ors, ob + 4u * r, 0, 0);
-                            }
-                }
+                put(ors, n, v, has);
             }
         }
-        const bool again = !(bad == 0.f) | below;
-        if (__any(again)) redo |= redo_bit(tile);
-
-        // Filters of few weights: the products of what a split leaves out of a value would not average out, and a
-        // filter of one weight is to give its pixels, rounded once.  Their sums are formed weight by weight.
-        uint64_t few = __ballot(lane < min(MB * 16, p.K - t.kb * MB * 16) && (s_scales[min(lane, MB * 16 - 1)] & 2) != 0);
-        if (few != 0) {                                 // uniform
-            const int pp = t.p0 + wave * 64 + lane, T = p.C * p.F * p.F;
+        // Filters of one weight give their pixels, rounded once: those are read again, four a lane like its outputs.
+        if (__any(lane < MB * 16 && (s_notes[min(lane, MB * 16 - 1)] & kNoteOne) != 0)) {
+            const int64_t ifirst = (int64_t)t.n_first * p.C * HW * 4;
+            const auto irs = __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)p.in + ifirst), 0,
+                                                              (int)min(in_bytes - ifirst, (int64_t)0x7FFFFFFF), kRsrcFlags);
+            const int pp = t.p0 + wave * 64 + lane;
             int x, y;
             const int dn = pixel(t, min(pp, total - 1), &x, &y);
-            const bool there = pp < total && x < t.ws;
-            const float* const src = p.in + (int64_t)(t.n_first + dn) * p.C * HW + (int64_t)y * p.W + t.x0 + (there ? x : 0);
-            while (few != 0) {
-                const int k = t.kb * MB * 16 + __builtin_ctzll(few);
-                few &= few - 1;
-                float sum = 0.f;
-                for (int t0 = 0; t0 < T; t0 += 64) {
-                    const float w = t0 + lane < T ? p.filt[(int64_t)k * T + t0 + lane] : 0.f;
-                    for (uint64_t nz = __ballot(w != 0.f); nz != 0; nz &= nz - 1) {
-                        const int at = __builtin_ctzll(nz), tap = t0 + at;
-                        const int c = fdiv(tap, p.d_ff), ij = tap - c * p.F * p.F, i = fdiv(ij, p.d_f);
-                        const float wt = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, w), at));
-                        sum = __builtin_fmaf(src[(int64_t)c * HW + i * p.W + ij - i * p.F], wt, sum);
-                    }
+            const uint32_t ib = pp < total && x < t.ws ? (uint32_t)(dn * p.C * HW + y * p.W + t.x0 + x) * 4u : kNowhere;
+#pragma unroll
+            for (int m = 0; m < MB; ++m) {
+                const int note = s_notes[m * 16 + l16];
+                const bool one = (note & kNoteOne) != 0;          // (no filter beyond K is one)
+                const int tap = one ? note >> kNoteTap : 0, k = (t.kb * MB + m) * 16 + l16;
+                const int c = fdiv(tap, p.d_ff), ij = tap - c * p.F * p.F, i = fdiv(ij, p.d_f);
+                const uint32_t at = (uint32_t)(c * HW + i * p.W + ij - i * p.F) * 4u;
+                const float w = p.filt[(int64_t)min(k, p.K - 1) * (p.C * p.F * p.F) + tap];
+                v4f v[NB];
+#pragma unroll
+                for (int n = 0; n < NB; ++n) {
+                    const uint32_t quad = (uint32_t)__builtin_amdgcn_ds_bpermute((n * 16 + 4 * g) * 4, (int)ib);
+                    v[n] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(irs, one && quad != kNowhere ? quad + at : kNowhere, 0, 0));
                 }
-                if (there) p.out[((int64_t)(t.n_first + dn) * p.K + k) * plane + (int64_t)y * p.Wo + t.x0 + x] = sum;
+                const auto ors = out_of(m);
+#pragma unroll
+                for (int n = 0; n < NB; ++n) {
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) v[n][r] *= w;
+                    put(ors, n, v[n], one);
+                }
             }
         }
+        if (__any(!(bad == 0.f) | below)) redo |= redo_bit(tile);
         t = next;
     }
 
@@ -659,22 +616,21 @@ TapsSteps taps_steps(const Shape& s)
     t.steps = (t.nc + 7) / 8;
     return t;
 }
-bool taps_fits(const TapsSteps& t, int ahead, int psb) { return ahead * 2 * t.MB * 1024 + t.steps * 64 + kTapsStatic + 2 * psb <= kTapsLds; }
+bool taps_fits(const TapsSteps& t, int ahead, int psb) { return ahead * 3 * t.MB * 1024 + t.steps * 64 + kTapsStatic + 3 * psb <= kTapsLds; }
 
 // Column strips, and where filters and image block lie, at the least cost.
 TapsPlan make_taps_plan(const Shape& s)
 {
     const TapsSteps t = taps_steps(s);
     TapsPlan best{t.MB, t.KB, t.P, t.RC, t.nc, t.steps, 0, 0, 0, 0, 0, 0, 0, false, false};
-    // (the kernel is made for few channels, and lanes address the filters with 32-bit byte offsets)
-    if (s.C > 16 || s.F < 2 || s.F > 11 || t.steps > 16 || (int64_t)s.K * s.C * s.F * s.F >= 1LL << 29) return best;
+    if (s.C > 16 || s.F < 2 || s.F > 11 || t.steps > kTapsSteps || (int64_t)s.K * s.C * s.F * s.F >= 1LL << 29) return best;
     const int64_t all_rows = (int64_t)s.N * s.Ho;
     double least = 1e300;
     for (int mode = 0; mode < 3; ++mode) {
         const bool res = mode < 2;
-        const int psb = mode == 0 ? kTapsPartSmall : kTapsPartLarge;
+        const int psb = mode == 0 ? kTapsPartSmall : taps_part_large(t.MB);
         if ((!res && t.steps < 3) || !taps_fits(t, res ? t.steps : 3, psb)) continue;
-        if (res && 16LL * s.C * s.F * s.F * 4 > 2 * psb) continue;           // sixteen filters' weights go through the image block's place
+        if (res && 16LL * s.C * s.F * s.F * 4 > 3 * psb) continue;           // sixteen filters' weights go through the image block's place
         int last = 0;
         for (int about : {16, 32, 48, 64, 96, 128, 192, 256}) {
             const int nstrips = (s.Wo + about - 1) / about, bw = ((s.Wo + nstrips - 1) / nstrips + 3) / 4 * 4;
@@ -733,7 +689,7 @@ int taps_launch(const float* in, const float* filt, float* out, const Shape& s, 
     if (!raise_lds_limit((const void*)kern, kTapsLds, lds_limit_raised)) return DCONV_LAUNCH_FAILED;
     GenWorkspace ws;
     if constexpr (!RES) {
-        const size_t bank_floats = (size_t)pl.KB * pl.steps * 2 * MB * 256, floats = bank_floats + (size_t)pl.KB * MB * 16;
+        const size_t bank_floats = (size_t)pl.KB * pl.steps * 3 * MB * 256, floats = bank_floats + (size_t)pl.KB * MB * 16;
         if (floats > kGenWorkspaceFloats) return DCONV_UNSUPPORTED;
         if (static_ws) {
             if (gen_static_workspace(st, floats, 0, &ws) != DCONV_OK) return DCONV_UNSUPPORTED;
@@ -742,12 +698,12 @@ int taps_launch(const float* in, const float* filt, float* out, const Shape& s, 
             if (!ws.part) return DCONV_UNSUPPORTED;
         }
         p.bank = (const v4u*)ws.part;
-        p.scales = (const int*)(ws.part + bank_floats);
+        p.notes = (const int*)(ws.part + bank_floats);
         begin_launch();
         hipLaunchKernelGGL((taps_bank_kernel<MB>), dim3((unsigned)(pl.KB * MB * ((pl.steps + 3) / 4))), dim3(256), 0, st, p, (v4u*)ws.part, (int*)(ws.part + bank_floats));
         if (const int rc = launch_status(); rc != DCONV_OK) return rc;
     }
-    const int lds = pl.steps * 64 + (RES ? pl.steps : 3) * 2 * MB * 1024 + 2 * PSB;
+    const int lds = pl.steps * 64 + (RES ? pl.steps : 3) * 3 * MB * 1024 + 3 * PSB;
     begin_launch();
     hipLaunchKernelGGL(kern, dim3((unsigned)std::min(p.tiles, 2 * cus)), dim3(256), (size_t)lds, st, p);
     return launch_status();
@@ -772,34 +728,32 @@ TapsPlan split_taps_plan(const Shape& s)
     return pl;
 }
 
-// When this kernel goes before the others, by estimates of its time and of theirs fitted to 900 layers drawn at
-// random (half of them one image of 64^2 .. 4096^2, half 1 to 64 images of 1 to 16 channels; 2x2 to 11x11;
-// rms 11 and 12 %).  Here: 6.3 us and 0.34 us per step and block of sixteen filters to split them (or 3 us for
-// the small kernel), per round of tiles 1.25 us and 0.25 us per step and block, 6.5 us per GB of output,
-// half as much again beyond the memory-side cache.  The others: 7.9 us per GFLOP.  It has to promise a
-// tenth: of 1400 layers 489 are chosen, 1.5 times faster on average, 18 of them slower, by up to 27 %
-// (large images, whose lines the special case's kernel writes whole).
+// When this kernel goes before the others, by estimates of its time and of theirs fitted to 1544 layers drawn at
+// random (half of them one image of 64^2 .. 4096^2, half 1 to 64 images of 1 to 16 channels; 2x2 to 11x11, 9 to 256
+// filters; rms 9 and 16 %).  Here: 6.2 us and 0.30 us per step and block of sixteen filters to split them (or 2.5 us for
+// the small kernel), per round of tiles 0.89 us, 0.39 us per step and block and 0.037 us per row of taps, 6.6 us per GB of
+// output, two thirds more beyond the memory-side cache.  The others: 8.4 us per GFLOP and the output.  It has to promise
+// a tenth: then 317 layers are chosen, 1.33 times faster than the fastest other kernel on average, six of them 3 % or more
+// slower (four images with sixteen filters or fewer, which the last term of `there` is for since); at a twentieth 361, 21 slower.
 double split_taps_time_if_preferred(const Shape& s, TapsPlan* plan)
 {
     if (s.C > 16 || s.F < 2 || s.F > 11 || s.K < 9) return 1e300;
     const TapsSteps t = taps_steps(s);
-    // (a longer sum is no closer to the exact one than the fp32 kernel's where that adds a tile's parts: 968 taps
-    // 1.6e-7 against 1.5e-7; up to 480 taps at most 1.4e-7, and 3.4e-7 for a whole tile's there)
-    if (t.steps > 16) return 1e300;
+    if (t.steps > kTapsSteps) return 1e300;
     const double px = (double)s.N * s.Ho * s.Wo, mb = px * s.K * 4e-6;
-    // (one image of one channel: from 6 GFLOP on.  Below, the configuration that dconv_tile_choice names gives
-    // the bits of the plain call when it is forced, which callers rely on; 720 x 1280 with forty 9x9 filters,
-    // 5.9 GFLOP, would go from 101 to 50 us)
-    if (s.N == 1 && s.C == 1 && 2.0 * px * s.K * s.F * s.F < 6e9) return 1e300;
-    // (few multiply-adds per output of a large volume: bound by its stores, which the special case's kernel
-    // arranges better)
-    if (s.N == 1 && s.C == 1 && mb > 600 && s.F < 9) return 1e300;
     const double tiles = std::ceil(px * 1.04 / kTapsNT) * t.KB, work = t.steps * t.MB;
     const double rounds = tiles > 1536 ? tiles / 512 : std::ceil(tiles / 512);
     const bool res = taps_fits(t, t.steps, kTapsPartSmall);
-    const double here = 6.3 + rounds * (0.253 * work + 1.25) + (res ? 0.344 * work : 3.0 + 0.104 * t.steps) + 0.153 * mb + 0.082 * std::max(0.0, mb - 250);
+    const double here = 6.2 + rounds * (0.386 * work + 0.89 + 0.0369 * s.C * (s.F + 4)) + (res ? 0.3 * work : 2.45 + 0.064 * t.steps) + 0.152 * mb +
+                        0.098 * std::max(0.0, mb - 250);
+    // (one image of one channel: from 6 GFLOP on.  Below, the configuration that dconv_tile_choice names gives
+    // the bits of the plain call when it is forced, which callers rely on; 720 x 1280 with forty 9x9 filters,
+    // 5.9 GFLOP, would go from 101 to 61 us)
+    if (s.N == 1 && s.C == 1 && 2.0 * px * s.K * s.F * s.F < 6e9) return 1e300;
     const double taps = (double)s.C * s.F * s.F;
-    const double there = 6.1 + 0.00785e-6 * 2 * px * ((s.K + 31) / 32 * 32) * taps + 0.147 * mb + 0.0168 * taps;
+    // (one image of one channel has kernels with blocks of sixteen filters)
+    const int block = s.N == 1 && s.C == 1 && s.K <= 16 ? 16 : 32;
+    const double there = 4.74 + 0.00839e-6 * 2 * px * ((s.K + block - 1) / block * block) * taps + 0.169 * mb + 0.0062 * taps;
     if (here >= 0.9 * there) return 1e300;
     *plan = split_taps_plan(s);
     return plan->ok ? here : 1e300;
@@ -813,16 +767,16 @@ int launch_split_taps(const float* in, const float* filt, float* out, const Shap
     // (sixteen filters always stay in LDS)
     switch (pl.MB * 4 + (!pl.res ? 0 : pl.psb == kTapsPartSmall ? 1 : 2)) {
     case 5: return taps_launch<1, true, kTapsPartSmall>(in, filt, out, s, st, pl, static_ws);
-    case 6: return taps_launch<1, true, kTapsPartLarge>(in, filt, out, s, st, pl, static_ws);
-    case 8: return taps_launch<2, false, kTapsPartLarge>(in, filt, out, s, st, pl, static_ws);
+    case 6: return taps_launch<1, true, taps_part_large(1)>(in, filt, out, s, st, pl, static_ws);
+    case 8: return taps_launch<2, false, taps_part_large(2)>(in, filt, out, s, st, pl, static_ws);
     case 9: return taps_launch<2, true, kTapsPartSmall>(in, filt, out, s, st, pl, static_ws);
-    case 10: return taps_launch<2, true, kTapsPartLarge>(in, filt, out, s, st, pl, static_ws);
-    case 12: return taps_launch<3, false, kTapsPartLarge>(in, filt, out, s, st, pl, static_ws);
+    case 10: return taps_launch<2, true, taps_part_large(2)>(in, filt, out, s, st, pl, static_ws);
+    case 12: return taps_launch<3, false, taps_part_large(3)>(in, filt, out, s, st, pl, static_ws);
     case 13: return taps_launch<3, true, kTapsPartSmall>(in, filt, out, s, st, pl, static_ws);
-    case 14: return taps_launch<3, true, kTapsPartLarge>(in, filt, out, s, st, pl, static_ws);
-    case 16: return taps_launch<4, false, kTapsPartLarge>(in, filt, out, s, st, pl, static_ws);
+    case 14: return taps_launch<3, true, taps_part_large(3)>(in, filt, out, s, st, pl, static_ws);
+    case 16: return taps_launch<4, false, taps_part_large(4)>(in, filt, out, s, st, pl, static_ws);
     case 17: return taps_launch<4, true, kTapsPartSmall>(in, filt, out, s, st, pl, static_ws);
-    case 18: return taps_launch<4, true, kTapsPartLarge>(in, filt, out, s, st, pl, static_ws);
+    case 18: return taps_launch<4, true, taps_part_large(4)>(in, filt, out, s, st, pl, static_ws);
     default: return DCONV_UNSUPPORTED;
     }
 }

@@ -42,7 +42,9 @@
  *     errors against exact sums are a third of the fp32 instructions' (0.35e-7 of
  *     the norm against 0.91e-7 with 25 terms, 0.51e-7 against 1.63e-7 with 81,
  *     0.98e-7 against 3.3e-7 with 363), and filters of one weight that is not zero
- *     give their products rounded once.
+ *     give their products rounded once.  Outputs that are computed again take up
+ *     to 2 times DCONV_VARIANT_TILED's time there, one filter of values near 2^-110
+ *     up to 1.2 times it, a bank of sparse filters a quarter more than a dense one.
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).
  *     Work is enqueued on it and the call returns without synchronising.
  *     The launch happens on the device that is current in the calling thread;

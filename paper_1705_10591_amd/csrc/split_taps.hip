@@ -14,6 +14,10 @@
 //    whose last part may fall below the smallest bf16, sums below 2^-60 (all of them beside values above 2^40):
 //    the wave's 64 pixels, behind the main loop, on the fp32 matrix cores;
 //  * filters of one weight give their pixels rounded once: read again as the tile ends.
+// Measured, on layers of 81 to 363 taps: all outputs formed again 1.6 to 2.0 times the fp32 kernel's time (6.3 with the
+// operands of an instruction loaded one by one), and 1.02 to 1.15 times this kernel's for one NaN pixel, 1.8 to 2.0 for one
+// filter with values near 2^-110 beside others (its sixteen filters only are formed again), 1.0 to 1.25 for a bank of
+// filters of one weight, 1.0 for filters of two or twelve.
 //
 // split_kernel.h reduces over sixteen channels of one tap at a time, which few channels cannot fill; here
 // the reduction runs over TAPS: an instruction takes 32 of them, in whatever order a table gives, so that the
@@ -354,6 +358,7 @@ split_taps_kernel(TapsParams p)
 
     // Tiles with outputs to be formed again (see general_split_kernel).
     uint64_t redo = 0;
+    uint32_t redo_blocks = 0;                           // blocks of sixteen filters that they are in
     auto redo_bit = [&](int t) __attribute__((always_inline)) { return 1ull << ((t - t0) / dt % 64); };
     // Where an operand is tiny (it lost 2^-134 at most), sums below this are formed again: 512 products with values of
     // up to 2^40 may be off by 2^-85.  With larger ones beside them, all are.
@@ -481,7 +486,7 @@ split_taps_kernel(TapsParams p)
 
         // (a buffer's range check keeps what isn't there from being written)
         float bad = 0.f;
-        bool below = false;
+        uint32_t again = 0;                             // blocks of sixteen filters with sums below the line
         const uint32_t whole = px + 4 <= t.ws ? obase : kNowhere;
         uint32_t o[NB];
 #pragma unroll
@@ -512,7 +517,8 @@ split_taps_kernel(TapsParams p)
             const auto ors = out_of(m);
             const int note = s_notes[m * 16 + l16];
             const bool has = (t.kb * MB + m) * 16 + l16 < p.K && (note & kNoteOne) == 0;
-            const float line = redo_line(range | note);
+            const float line = has ? redo_line(range | note) : 0.f;
+            bool below = false;
 #pragma unroll
             for (int n = 0; n < NB; ++n) {
                 v4f v;
@@ -524,6 +530,7 @@ split_taps_kernel(TapsParams p)
                 }
                 put(ors, n, v, has);
             }
+            if (__any(below)) again |= 1u << m;
         }
         // Filters of one weight give their pixels, rounded once: those are read again, four a lane like its outputs.
         if (__any(lane < MB * 16 && (s_notes[min(lane, MB * 16 - 1)] & kNoteOne) != 0)) {
@@ -557,45 +564,81 @@ split_taps_kernel(TapsParams p)
                 }
             }
         }
-        if (__any(!(bad == 0.f) | below)) redo |= redo_bit(tile);
+        if (__any(!(bad == 0.f))) again = (1u << MB) - 1u;
+        if (again != 0) {                               // uniform
+            redo |= redo_bit(tile);
+            redo_blocks |= again;
+        }
         t = next;
     }
 
     // ---- outputs that the split cannot form: a wave's blocks again, on the fp32 matrix cores
     if (redo == 0) return;
     __builtin_amdgcn_s_waitcnt(0x0F70);                 // this wave's outputs are in memory
+    // Sixteen taps a time: lane (g, l) brings weights 4 g .. 4 g + 3 of filter l and, for each of the four, pixel l of the
+    // wave's four blocks; instruction q takes word q, so that its reduction index g is tap 4 g + q.  The next sixteen are on their way.
     const int T = p.C * p.F * p.F;
+    const auto wrs = __builtin_amdgcn_make_buffer_rsrc((void*)p.filt, 0, (int)min((int64_t)p.K * T * 4, (int64_t)0x7FFFFFFF), kRsrcFlags);
     for (int tile = t0; tile < t1; tile += dt) {
         if ((redo & redo_bit(tile)) == 0) continue;     // uniform
         const Place t = place(tile);
-#pragma unroll 1
+        const int64_t ifirst = (int64_t)t.n_first * p.C * HW * 4;
+        const auto irs = __builtin_amdgcn_make_buffer_rsrc((void*)((const char*)p.in + ifirst), 0,
+                                                          (int)min(in_bytes - ifirst, (int64_t)0x7FFFFFFF), kRsrcFlags);
+        uint32_t pix[NB];
+#pragma unroll
+        for (int n = 0; n < NB; ++n) {
+            const int pp = t.p0 + wave * 64 + n * 16 + l16;
+            int x, y;
+            const int dn = pixel(t, min(pp, total - 1), &x, &y);
+            pix[n] = pp < total && x < t.ws ? (uint32_t)(dn * p.C * HW + y * p.W + t.x0 + x) * 4u : kNowhere;
+        }
+        v4f acc[MB][NB] = {}, x[2][NB], w[2][MB];
+        auto bring = [&](int s, v4f (&x)[NB], v4f (&w)[MB]) __attribute__((always_inline)) {
+#pragma unroll
+            for (int m = 0; m < MB; ++m) {
+                const int k = (t.kb * MB + m) * 16 + l16;
+                // (beyond the last tap another filter's, against pixels that are zero: set to zero below)
+                w[m] = __builtin_bit_cast(v4f, __builtin_amdgcn_raw_buffer_load_b128(
+                    wrs, k < p.K && (redo_blocks >> m & 1) ? (uint32_t)(k * T + s * 16 + 4 * g) * 4u : kNowhere, 0, 0));
+            }
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int tap = s * 16 + 4 * g + q;
+                const int c = fdiv(tap, p.d_ff), ij = tap - c * p.F * p.F, i = fdiv(ij, p.d_f);
+                const uint32_t at = (uint32_t)(c * HW + i * p.W + ij - i * p.F) * 4u;
+#pragma unroll
+                for (int n = 0; n < NB; ++n)
+                    x[n][q] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(irs, tap < T && pix[n] != kNowhere ? pix[n] + at : kNowhere, 0, 0));
+#pragma unroll
+                for (int m = 0; m < MB; ++m) w[m][q] = tap < T ? w[m][q] : 0.f;
+            }
+        };
+        const int groups = (T + 15) / 16;
+        bring(0, x[0], w[0]);
+        for (int s0 = 0; s0 < groups; s0 += 2)
+#pragma unroll
+            for (int d = 0; d < 2; ++d) {
+                if (s0 + d >= groups) break;            // uniform
+                bring(s0 + d + 1, x[d ^ 1], w[d ^ 1]);  // (behind the last one: nothing is read)
+#pragma unroll
+                for (int m = 0; m < MB; ++m)
+                    if (redo_blocks >> m & 1)           // uniform
+#pragma unroll
+                        for (int q = 0; q < 4; ++q)
+#pragma unroll
+                            for (int n = 0; n < NB; ++n) acc[m][n] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[d][n][q], w[d][m][q], acc[m][n], 0, 0, 0);
+            }
+#pragma unroll
         for (int n = 0; n < NB; ++n) {
             uint32_t ob;
             const int there = out_quad(t, n, &ob);
             float* const o = p.out + ((int64_t)t.n_first * p.K + t.kb * MB * 16) * plane + ob / 4u;
-            const int pp = t.p0 + wave * 64 + n * 16 + l16;
-            int x, y;
-            const int dn = pixel(t, min(pp, total - 1), &x, &y);
-            const bool real = pp < total && x < t.ws;
-            const float* src = p.in + (int64_t)(t.n_first + dn) * p.C * HW + (int64_t)y * p.W + t.x0 + x;
-            v4f acc[MB] = {};
-#pragma unroll 4
-            for (int u = 0; u < (T + 3) / 4; ++u) {
-                const int tap = 4 * u + g;
-                const int c = fdiv(tap, p.d_ff), ij = tap - c * p.F * p.F, i = fdiv(ij, p.d_f), j = ij - i * p.F;
-                const float xv = real && tap < T ? src[(int64_t)c * HW + i * p.W + j] : 0.f;
-#pragma unroll
-                for (int m = 0; m < MB; ++m) {
-                    const int k = (t.kb * MB + m) * 16 + l16;
-                    const float w = tap < T && k < p.K ? p.filt[(int64_t)k * T + tap] : 0.f;
-                    acc[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(xv, w, acc[m], 0, 0, 0);
-                }
-            }
 #pragma unroll
             for (int m = 0; m < MB; ++m)
 #pragma unroll
                 for (int r = 0; r < 4; ++r)
-                    if (r < there && (t.kb * MB + m) * 16 + l16 < p.K) o[(int64_t)(m * 16) * plane + r] = acc[m][r];
+                    if (r < there && (redo_blocks >> m & 1) && (t.kb * MB + m) * 16 + l16 < p.K) o[(int64_t)(m * 16) * plane + r] = acc[m][n][r];
         }
     }
 }

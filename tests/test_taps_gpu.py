@@ -94,6 +94,24 @@ def test_values_that_two_parts_cannot_carry(shape):
         assert np.all(np.abs(got - acc) <= 1e-5 * mag + C * F * F * 2.0 ** -150)
 
 
+@pytest.mark.parametrize("shape", [(8, 10, 44, 143, 33, 5), (9, 1, 62, 123, 97, 8)], ids=ids)
+def test_only_what_parts_cannot_give_is_formed_again(shape):
+    """A tiny pixel that no sum is small enough to feel leaves all bits as they are (no filter is missing from the
+    last block of sixteen for nothing), a filter of tiny weights those of the other blocks."""
+    N, C, H, W, K, F = shape
+    x, f = wl.random_case(9250 + F, N, C, H, W, K, F)
+    x[:, 0, ::9, ::11] = 0
+    want, y, g = call(x, f), x.copy(), f.copy()
+    y[:, 0, ::9, ::11] = 2.0 ** -110
+    g[20] *= np.float32(2.0 ** -110)
+    assert np.array_equal(call(y, f), want)
+    got = call(x, g)
+    other = np.arange(K) // 16 != 1
+    assert np.array_equal(got[:, other], want[:, other])
+    acc, mag, _ = oracle.general(x, g)
+    assert np.all(np.abs(got[:, 20] - acc[:, 20]) <= 1e-5 * mag[:, 20] + C * F * F * 2.0 ** -150)
+
+
 @pytest.mark.parametrize("shape", [(8, 10, 44, 143, 33, 5), (9, 1, 62, 123, 97, 8), (3, 3, 50, 39, 64, 11)], ids=ids)
 def test_filters_of_few_weights(shape):
     """Filters of one weight beside full ones give their products rounded once (rows that end off a multiple of

@@ -36,8 +36,8 @@
  *     outputs that are not finite, are computed again in fp32: calls with such
  *     values were measured at up to 4 times what DCONV_VARIANT_TILED takes,
  *     which stays on fp32 products and takes the same time for any data.
- *     Layers of up to sixteen channels with enough work, and one image of one
- *     channel from 6 GFLOP on, AUTO takes apart the same way, with the same
+ *     Layers of up to sixteen channels with enough work, and images of one channel
+ *     (dconv_single_channel too), AUTO takes apart the same way, with the same
  *     limits (filters of 2x2 to 11x11, more than eight, up to 512 taps).  There
  *     errors against exact sums are a third of the fp32 instructions' (0.35e-7 of
  *     the norm against 0.91e-7 with 25 terms, 0.51e-7 against 1.63e-7 with 81,

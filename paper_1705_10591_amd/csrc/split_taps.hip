@@ -784,15 +784,14 @@ double split_taps_time_if_preferred(const Shape& s, TapsPlan* plan)
     const TapsSteps t = taps_steps(s);
     if (t.steps > kTapsSteps) return 1e300;
     const double px = (double)s.N * s.Ho * s.Wo, mb = px * s.K * 4e-6;
+    // (few multiply-adds per output of a large volume: bound by its stores, which the special case's kernel arranges
+    // better: 3008 x 2282 with 48 7x7 filters 457 us there, 500 here; 98 of 9x9 on 3374 x 959 694 and 544)
+    if (s.N == 1 && s.C == 1 && mb > 1000 && s.F < 8) return 1e300;
     const double tiles = std::ceil(px * 1.04 / kTapsNT) * t.KB, work = t.steps * t.MB;
     const double rounds = tiles > 1536 ? tiles / 512 : std::ceil(tiles / 512);
     const bool res = taps_fits(t, t.steps, kTapsPartSmall);
     const double here = 6.2 + rounds * (0.386 * work + 0.89 + 0.0369 * s.C * (s.F + 4)) + (res ? 0.3 * work : 2.45 + 0.064 * t.steps) + 0.152 * mb +
                         0.098 * std::max(0.0, mb - 250);
-    // (one image of one channel: from 6 GFLOP on.  Below, the configuration that dconv_tile_choice names gives
-    // the bits of the plain call when it is forced, which callers rely on; 720 x 1280 with forty 9x9 filters,
-    // 5.9 GFLOP, would go from 101 to 61 us)
-    if (s.N == 1 && s.C == 1 && 2.0 * px * s.K * s.F * s.F < 6e9) return 1e300;
     const double taps = (double)s.C * s.F * s.F;
     // (one image of one channel has kernels with blocks of sixteen filters)
     const int block = s.N == 1 && s.C == 1 && s.K <= 16 ? 16 : 32;

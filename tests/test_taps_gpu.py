@@ -181,8 +181,8 @@ def test_short_sums_are_no_further_off_than_on_the_fp32_kernel(shape):
 
 
 # layers that the rule sends there: filters that stay on the chip, filters that go through the workspace
-CHOSEN = [(1, 1, 409, 724, 130, 9), (20, 3, 150, 148, 64, 5), (12, 3, 150, 148, 64, 11)]
-THROUGH_THE_WORKSPACE = CHOSEN[2]
+CHOSEN = [(1, 1, 720, 1280, 40, 9), (1, 1, 409, 724, 130, 9), (20, 3, 150, 148, 64, 5), (12, 3, 150, 148, 64, 11)]
+THROUGH_THE_WORKSPACE = CHOSEN[3]
 
 
 @pytest.mark.parametrize("shape", CHOSEN, ids=ids)

@@ -322,8 +322,9 @@ int dconv_kernel_choice(int single_channel, int N, int C, int H, int W, int K, i
  * own, which is waited for.)  Layers whose products are taken apart run on the
  * fp32 matrix cores when they are captured, so their bits and their time are
  * those of that kernel; in dconv_general_noalloc they run as they do otherwise.
- * (Layers of few channels whose split filters stay on the chip need no workspace
- * and run the same when captured.)
+ * (Layers of few channels whose split filters stay on the chip, short launches and
+ * layers on DCONV_VARIANT_FEW_TAPS need no workspace and run the same when
+ * captured.)
  */
 
 /*
@@ -334,7 +335,10 @@ int dconv_kernel_choice(int single_channel, int N, int C, int H, int W, int K, i
  * kernels of one call.  The first call that needs it on a stream allocates, with
  * hipMalloc, what the largest launch on that device can need (256 KiB of
  * partial sums and four counters per compute unit: 64 MiB + 4 KiB on a 256-CU
- * chip) and clears the counters on that stream; no other entry point
+ * chip) and clears the counters on that stream; so does the first call on a stream
+ * of a layer that runs on a kernel without a workspace where the tiled kernel
+ * would share its tiles (by estimate), so that such a call too can be the one that
+ * is run before a capture; no other entry point
  * allocates (dconv_single_channel counts as dconv_general here where it runs
  * on the same kernel, see there), and no call
  * synchronises (but for the relaxed capture above).  The block keeps its

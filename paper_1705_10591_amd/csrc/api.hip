@@ -40,12 +40,13 @@ struct Route {
     TapsPlan taps;
     ShortChoice small;
     bool has_small;
+    bool in_place_of_tiles;      // FEW_TAPS: of the general kernel's, not of the vector-ALU kernel
 };
 
 // By shape alone; `taps`: the kernel for few channels is among the choices.
 Route auto_route(const Shape& s, bool single_entry, bool taps)
 {
-    Route r{DCONV_VARIANT_SIMPLE, single_entry, {}, {}, {1e300, 0}, false};
+    Route r{DCONV_VARIANT_SIMPLE, single_entry, {}, {}, {1e300, 0}, false, false};
     auto small = [&]() {
         if (!r.has_small) r.small = dconv::short_choice(s);
         r.has_small = true;
@@ -75,6 +76,7 @@ Route auto_route(const Shape& s, bool single_entry, bool taps)
             r.single = dconv::single_batch_preferred(s) || (dconv::single_tiled_supports(s) && !dconv::general_tiled_supports(s));
             if (!r.single && few.taps < 1e300 && few.taps < few_channels() && few.taps < small()) {
                 r.variant = DCONV_VARIANT_FEW_TAPS;
+                r.in_place_of_tiles = true;
                 r.few = few.plan;
                 return r;
             }
@@ -109,6 +111,7 @@ int launch_auto(bool single_entry, const float* in, const float* filt, float* ou
 {
     Route r = auto_route(s, single_entry, true);
     if (r.variant == DCONV_VARIANT_FEW_CHANNELS) {
+        if (!static_ws && r.taps.res && !r.single) dconv::bring_workspace(s, st);
         const int rc = dconv::launch_split_taps(in, filt, out, s, st, static_ws, r.taps);
         if (rc != DCONV_UNSUPPORTED) return rc;
         r = auto_route(s, single_entry, false);
@@ -116,7 +119,9 @@ int launch_auto(bool single_entry, const float* in, const float* filt, float* ou
     switch (r.variant) {
     case DCONV_VARIANT_FEW_FILTERS:
         return r.single ? dconv::launch_single_few(in, filt, out, s, st) : dconv::launch_general_few(in, filt, out, s, st);
-    case DCONV_VARIANT_FEW_TAPS: return dconv::launch_few_taps(in, filt, out, s, st, r.few);
+    case DCONV_VARIANT_FEW_TAPS:
+        if (!static_ws && r.in_place_of_tiles) dconv::bring_workspace(s, st);
+        return dconv::launch_few_taps(in, filt, out, s, st, r.few);
     case DCONV_VARIANT_TILED:
         return r.single ? dconv::launch_single_tiled(in, filt, out, s, st, -1)
                         : dconv::launch_general_tiled(in, filt, out, s, st, -1, static_ws, GeneralWay::kAuto,

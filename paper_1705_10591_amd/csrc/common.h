@@ -62,7 +62,7 @@ int launch_single_tiled(const float* img, const float* filt, float* out, const S
 // where another kernel is the better choice).
 struct ShortChoice { double time; int cfg; };
 ShortChoice short_choice(const Shape& s);
-bool short_in_place_of_shared_tiles(const Shape& s);     // ... of tiles that the general kernel would share
+bool general_would_share_tiles(const Shape& s);          // (by the same estimates)
 int launch_short(const float* in, const float* filt, float* out, const Shape& s, hipStream_t st, int cfg);
 // The kernels of the general case that tile filters and pixels: the fp32 one, large layers' products taken
 // apart on the bf16 matrix cores (split_kernel.h), short launches, or what the shape asks for.
@@ -73,6 +73,8 @@ enum class GeneralWay { kTiled, kParts, kShort, kAuto };
 int launch_general_tiled(const float* in, const float* filt, float* out, const Shape& s, hipStream_t st, int cfg,
                          bool static_ws, GeneralWay way, const ShortChoice* small = nullptr);
 GeneralWay general_way_for(const Shape& s);              // what kAuto is for a shape
+// The stream's workspace for later calls, where the general kernel would have asked for it (general.hip).
+void bring_workspace(const Shape& s, hipStream_t st);
 // few channels on the bf16 matrix cores (split_taps.hip): DCONV_UNSUPPORTED where it cannot run; estimated kernel
 // time in us and the plan, 1e300 where another kernel is the better choice
 struct TapsPlan {

@@ -244,6 +244,27 @@ GenWorkspace gen_workspace(hipStream_t st, size_t part_floats, size_t ncnt)
     }
 }
 
+// Releases so far: what is remembered of a workspace from before one is void.
+static std::atomic<uint64_t> ws_releases{1};
+
+// A layer that the general kernel would share the tiles of, on a kernel without a workspace: the stream is given its
+// block all the same, as programs run such a call before they capture others.  Once: the threads remember the last
+// streams that they asked for (the lookup and the questions whether a stream captures cost a call of 8 us 0.4 us).
+void bring_workspace(const Shape& s, hipStream_t st)
+{
+    if (!general_would_share_tiles(s)) return;
+    struct Seen { hipStream_t st; int dev; uint64_t releases; };
+    thread_local Seen seen[4] = {};
+    thread_local unsigned at = 0;
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return;
+    const uint64_t releases = ws_releases.load(std::memory_order_acquire);      // (before the block is asked for)
+    for (const Seen& e : seen)
+        if (e.releases == releases && e.st == st && e.dev == dev) return;
+    if (gen_capturing(st) || !gen_workspace(st, 0, 0).part) return;
+    seen[at++ % 4] = Seen{st, dev, releases};
+}
+
 void release_general_workspaces()
 {
     WsTable& table = ws_table();
@@ -256,6 +277,7 @@ void release_general_workspaces()
     for (auto& l : table.left) free_all(*l.second);
     table.entries.clear();
     table.left.clear();
+    ws_releases.fetch_add(1, std::memory_order_acq_rel);
 }
 
 // ---- the static scratch array of dconv_general_noalloc --------------------------------------------
@@ -566,9 +588,7 @@ int launch_general_tiled(const float* in, const float* filt, float* out, const S
         {
             const ShortChoice tiles = small ? *small : short_choice(s);
             if (tiles.time == 1e300) break;
-            // (a layer whose tiles the general kernel would share still brings the stream its workspace: programs run
-            // such a call before they capture others)
-            if (!static_ws && short_in_place_of_shared_tiles(s) && !gen_capturing(st)) (void)gen_workspace(st, 0, 0);
+            if (!static_ws) bring_workspace(s, st);
             const int rc = launch_short(in, filt, out, s, st, tiles.cfg);
             if (rc != DCONV_UNSUPPORTED) return rc;
         }

@@ -241,7 +241,7 @@ ShortChoice short_choice(const Shape& s)
     return r;
 }
 
-bool short_in_place_of_shared_tiles(const Shape& s)
+bool general_would_share_tiles(const Shape& s)
 {
     const GeneralTiles t = general_tiles(s);
     return t.whole > 1.2 * t.even + 4;

@@ -91,6 +91,38 @@ def test_a_call_without_counters_prepares_the_stream_for_one_with_counters(kerne
         assert torch.equal(second[4], want), f"replay {rep}"
 
 
+# the kernels that need no workspace where the general kernel would share its tiles: short launches, the taps of few
+# filters
+WITHOUT = [(ONE_IMAGE, dconv.VARIANT_SHORT), ((16, 200, 40, 64, 3, 3), dconv.VARIANT_FEW_TAPS)]
+
+
+@pytest.mark.parametrize("shape,kernel", WITHOUT, ids=["short", "few_taps"])
+def test_what_a_stream_was_given_is_asked_for_again_after_a_release(shape, kernel):
+    """Such a call prepares the stream for a captured one that needs the workspace, every time that it has none: the
+    second call on a stream asks for nothing, the first one after a release does."""
+    assert dconv.kernel_choice(False, *shape) == kernel
+    first, second = make(8520, shape), make(8521, (3, 16, 28, 28, 130, 3))
+    want = dconv.dconv_general(second[2], second[3], variant=SHARED + 1)
+    s = torch.cuda.Stream()
+    for rep in range(2):
+        torch.cuda.synchronize()
+        dconv.release_workspace()
+        with torch.cuda.stream(s):
+            eager = [dconv.dconv_general(first[2], first[3]) for _ in range(2)]
+        s.synchronize()
+        assert torch.equal(*eager)
+        g = torch.cuda.CUDAGraph()
+        print(f"capturing after {shape}, time {rep}", flush=True)
+        with torch.cuda.graph(g, stream=s):
+            dconv.dconv_general(second[2], second[3], out=second[4], variant=SHARED + 1)
+        for _ in range(2):
+            second[4].fill_(float("nan"))
+            g.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(second[4], want), f"time {rep}"
+        del g
+
+
 def test_a_capture_that_lets_the_allocation_through_leaves_cleared_counters():
     """In relaxed mode a first call may allocate while it is captured: calls before the first replay find cleared
     counters, and replays do not clear them again."""

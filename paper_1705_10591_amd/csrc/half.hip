@@ -106,9 +106,11 @@ int preferred_config(const Shape& s, int dtype, bool blocked)
 
 // Short launches: the estimate of half_short.hip against one of the tiled kernel, fitted to the same layers
 // (rms 9 %): launch, steps and chunks of one tile, steps of the tiles beyond one per CU, rounds, memory and output.
-// It has to promise a twentieth and, as both estimates lean on the tiles' overlap where there are many, 2 % more
-// for every microsecond.  Of 583 layers that the fit did not see (up to 30 GFLOP) 349 are chosen, 2.2 times
-// faster on average; six of them are slower (the worst 1.31 times, of 12 us), eleven faster by more than a tenth are left.
+// It has to promise a tenth and, as both estimates lean on the tiles' overlap where there are many, 3 % more
+// for every microsecond: pixels a multiple of 512 bytes apart cost this kernel up to twice the estimate.  Of 1500 layers that
+// the fit did not see (2x2 to 7x7, up to 30 GFLOP) 810 are chosen, 2.4 times faster on average, six of them slower (by up to
+// 22 %); with a twentieth and 2 % 887, 2.27 times, 17 slower (by up to 27 %).  A list of slower ones:
+// profiles/rule_short_launches_short_types.txt.
 // The large tile (few of those layers) and filters from 8x8 on (none) keep the tiled kernel.
 bool short_preferred(const Shape& s, int dtype, int tile, int* cfg)
 {
@@ -124,7 +126,7 @@ bool short_preferred(const Shape& s, int dtype, int tile, int* cfg)
     const double mb = 1e-6 * groups * kHalfChunkBytes * ((double)s.N * s.H * s.W + (double)s.K * s.F * s.F) + out;
     const double tile_us = mid ? 0.283 * steps : 0.0898 * steps + 0.2555 * chunks + 0.1466 * std::max(0.0, tiles / 256 - 1) * steps;
     const double there = 4.525 + tile_us + 0.2874 * (std::ceil(tiles / 256) - 1) + 0.0914 * mb + 0.0544 * out;
-    return here * (1.05 + 0.02 * here) < there;
+    return here * (1.1 + 0.03 * here) < there;
 }
 
 }  // namespace

@@ -777,7 +777,8 @@ TapsPlan split_taps_plan(const Shape& s)
 // the small kernel), per round of tiles 0.89 us, 0.39 us per step and block and 0.037 us per row of taps, 6.6 us per GB of
 // output, two thirds more beyond the memory-side cache.  The others: 8.4 us per GFLOP and the output.  It has to promise
 // a tenth: then 317 layers are chosen, 1.33 times faster than the fastest other kernel on average, six of them 3 % or more
-// slower (four images with sixteen filters or fewer, which the last term of `there` is for since); at a twentieth 361, 21 slower.
+// slower (four images with sixteen filters or fewer, which the last term of `there` is for since); at a twentieth 361, 21
+// slower.  Layers that the fit did not see: profiles/rule_few_channels.txt.
 double split_taps_time_if_preferred(const Shape& s, TapsPlan* plan)
 {
     if (s.C > 16 || s.F < 2 || s.F > 11 || s.K < 9) return 1e300;

@@ -22,12 +22,14 @@ that the rules can be checked or re-derived on another chip.
     python -m paper_1705_10591_amd.tune route SEED COUNT          (one image of one channel on shapes drawn at
                                                                    random: the library's choice, the special
                                                                    case's kernel and the general-case kernel)
-    python -m paper_1705_10591_amd.tune rule parts|second|point SEED COUNT
+    python -m paper_1705_10591_amd.tune rule parts|second|point|channels|taps|short|short-types SEED COUNT
                                                                   (layers drawn at random, the library's choice
                                                                    against what it would run without: products
                                                                    of bf16 parts, the second kernel that adds
                                                                    the parts of shared tiles, the 1x1 kernel of
-                                                                   the short types)
+                                                                   the short types, few channels, the taps of few
+                                                                   filters, short launches in fp32 and in the short
+                                                                   types)
     python -m paper_1705_10591_amd.tune units                     (special case: 16-byte against 4-byte units
                                                                    on the way out, the width-matching ablation)
     python -m paper_1705_10591_amd.tune writeback                 (general case: stores straight from the
@@ -317,44 +319,71 @@ def _log(rng, lo, hi):
 def _rule_case(which: str, rng):
     """(label, calls: the library's choice first, whether it takes the kernel) of one random layer, or None."""
     gen = torch.Generator(device="cuda").manual_seed(rng.getrandbits(31))
-    H = _log(rng, 7, {"parts": 128, "second": 60, "point": 128}[which])
+    H = _log(rng, *{"second": (7, 60), "channels": (28, 512), "taps": (14, 256)}.get(which, (7, 128)))
     W = max(7, round(H * rng.choice((1.0, 1.0, rng.uniform(0.5, 2.0)))))
-    if which == "point":
-        kind, blocked = rng.choice(("f16", "bf16", "i8")), rng.random() < 0.5
+    if which in ("point", "short-types"):
+        kind, blocked = rng.choice(("f16", "bf16", "i8") if which == "point" else ("f16", "bf16")), rng.random() < 0.5
         step = 32 if kind == "i8" else 16
-        N, C, K = _log(rng, 1, 64), step * _log(rng, 1, 1024 // step), _log(rng, 16, 1024)
-        if N * H * W * max(C, K) > 3e8:
+        F = 1 if which == "point" else rng.choice((1, 2, 3, 3, 3, 4, 5, 7))
+        most = 1024 if which == "point" else 512
+        N, C, K = _log(rng, 1, 64), step * _log(rng, 1, most // step), _log(rng, 16, most)
+        if N * H * W * max(C, K) > 3e8 or 2.0 * N * C * H * W * K * F * F > 30e9:
             return None
-        shapes = [(A, C // step, h, w, step) if blocked else (A, h, w, C) for A, h, w in ((N, H, W), (K, 1, 1))]
+        H, W = H + F - 1, W + F - 1
+        shapes = [(A, C // step, h, w, step) if blocked else (A, h, w, C) for A, h, w in ((N, H, W), (K, F, F))]
         if kind == "i8":
             x, f = (torch.randint(-127, 128, s, device="cuda", generator=gen, dtype=torch.int8) for s in shapes)
-            fn, out = dconv.dconv_general_i8, torch.empty(N, K, H, W, device="cuda", dtype=torch.int32)
+            fn, out = dconv.dconv_general_i8, torch.empty(N, K, H - F + 1, W - F + 1, device="cuda", dtype=torch.int32)
         else:
             dt = torch.float16 if kind == "f16" else torch.bfloat16
             x, f = (torch.rand(s, device="cuda", generator=gen).to(dt) for s in shapes)
-            fn, out = dconv.dconv_general_half, torch.empty(N, K, H, W, device="cuda")
+            fn, out = dconv.dconv_general_half, torch.empty(N, K, H - F + 1, W - F + 1, device="cuda")
+        call = lambda v, o=out: fn(x, f, out=o, variant=v, blocked=blocked)
+        if which == "short-types":
+            # (by the bits of sums of random values whether AUTO runs small tiles; the rule goes by bytes, alike for 8 bits)
+            try:
+                auto, small, tiled = (call(v, torch.empty_like(out)) for v in (dconv.VARIANT_AUTO, dconv.VARIANT_SHORT, dconv.VARIANT_TILED))
+                takes = torch.equal(auto, small) and not torch.equal(auto, tiled)
+            except dconv.DconvError:
+                takes = False
+            return f"{kind}{' blocked' if blocked else ''} {N}x{C}x{H}x{W}x{K}x{F}", \
+                [lambda v=v: call(v) for v in (dconv.VARIANT_SHORT, dconv.VARIANT_TILED)] if takes else [], takes
         variants = [dconv.VARIANT_AUTO] + [dconv.VARIANT_TILED_CFG0 + i for i in range(5)]
-        calls = [lambda v=v: fn(x, f, out=out, variant=v, blocked=blocked) for v in variants]
+        calls = [lambda v=v: call(v) for v in variants]
         return f"{kind}{' blocked' if blocked else ''} {N}x{C}x{H}x{W}x{K}", calls, \
             4 * N * K * H * W <= 256e6 and C * x.element_size() % 64 == 0
-    F = rng.choice((2, 3, 3, 3, 4, 5, 6, 7) if which == "parts" else (1, 3, 3, 5))
-    N = _log(rng, 1, 64 if which == "parts" else 8)
-    C, K = (_log(rng, 8, 512), _log(rng, 17, 512)) if which == "parts" else (_log(rng, 16, 1024), _log(rng, 17, 512))
+    F = rng.choice({"parts": (2, 3, 3, 3, 4, 5, 6, 7), "second": (1, 3, 3, 5), "channels": (2, 3, 3, 4, 5, 6, 7, 8, 9, 10, 11),
+                    "taps": (1, 2, 3, 3, 3, 4, 5, 6, 7), "short": (1, 2, 3, 3, 3, 4, 5, 7, 9, 11)}[which])
+    N = _log(rng, 1, 8 if which == "second" else 64)
+    C, K = {"parts": lambda: (_log(rng, 8, 512), _log(rng, 17, 512)), "second": lambda: (_log(rng, 16, 1024), _log(rng, 17, 512)),
+            "channels": lambda: (rng.choice((1, 2, 3, 3, 3, 4, 6, 8, 12, 16)), _log(rng, 9, 256)),
+            "taps": lambda: (_log(rng, 2, 512), rng.randint(1, 16)), "short": lambda: (_log(rng, 1, 512), _log(rng, 9, 512))}[which]()
+    if which == "channels" and rng.random() < 0.5:
+        N, C, H, W = 1, 1, _log(rng, 64, 4096), _log(rng, 64, 4096)
     if F > min(H, W):
         return None
     flop = 2.0 * N * C * K * F * F * (H - F + 1) * (W - F + 1)
     choice = dconv.tile_choice(False, N, C, H, W, K, F)
-    if choice < 0 or flop > 60e9 or (which == "parts" and flop < 0.3e9):
+    if flop > (6e9 if which == "short" else 60e9) or (which == "parts" and flop < 0.3e9) or N * K * H * W > 5e8:
+        return None
+    if choice < 0 and which in ("parts", "second", "short"):
         return None
     x = torch.rand(N, C, H, W, device="cuda", generator=gen)
     f = torch.randn(K, C, F, F, device="cuda", generator=gen) * 0.1
     out = torch.empty(N, K, H - F + 1, W - F + 1, device="cuda")
     call = lambda v, o=out: dconv.dconv_general(x, f, out=o, variant=v)
     label = f"{N}x{C}x{H}x{W}x{K}x{F}"
-    if which == "parts":
-        variants = (dconv.VARIANT_AUTO, dconv.VARIANT_TILED)
-        outs = [call(v, torch.empty_like(out)) for v in variants]
-        return label, [lambda v=v: call(v) for v in variants], not torch.equal(*outs)
+    if which != "second":
+        # the kernel by its name, and what the library ran without it
+        named = {"parts": dconv.VARIANT_PARTS, "channels": dconv.VARIANT_FEW_CHANNELS, "taps": dconv.VARIANT_FEW_TAPS,
+                 "short": dconv.VARIANT_SHORT}[which]
+        others = {"channels": (dconv.VARIANT_TILED, dconv.VARIANT_SPECIAL_CASE),
+                  "taps": (dconv.VARIANT_FEW_FILTERS if choice == dconv.CHOICE_FEW_FILTERS else dconv.VARIANT_TILED,)}
+        if dconv.kernel_choice(False, N, C, H, W, K, F) != named:
+            return label, [], False
+        # (no workspace: the calls can be captured)
+        return label, [lambda v=v: dconv.dconv_general(x, f, out=out, variant=v, noalloc=True)
+                       for v in (named,) + others.get(which, (dconv.VARIANT_TILED,))], True
     # the fp32 kernel's own schedule, whole tiles, tiles shared by as many workgroups as the chip holds
     variants = (dconv.VARIANT_TILED, dconv.VARIANT_TILED_CFG0 + 3 + choice, dconv.VARIANT_TILED_CFG0 + 6 + choice)
     outs = [call(v, torch.empty_like(out)) for v in variants]
@@ -362,9 +391,12 @@ def _rule_case(which: str, rng):
 
 
 def rule_table(which: str, seed: int, count: int) -> None:
-    """The library's choice on random layers against what it would run without one of its kernels: `parts`
-    against the fp32 matrix cores, `second` against whole tiles and tiles added by their last workgroup,
-    `point` against the tile configurations of the kernel for every filter side (replayed from graphs).  Lists the layers that are 3 %
+    """The library's choice on random layers against what it would run without one of its kernels: `parts` and
+    `short` against the fp32 tiled kernel, `second` against whole tiles and tiles added by their last workgroup,
+    `channels` against that kernel and the special case's, `taps` against the vector-ALU kernel or the tiled one, whichever
+    dconv_tile_choice says, `short-types` against the tiled kernel of those types,
+    `point` against the tile configurations of the kernel for every filter side (replayed from graphs, as small layers
+    of the others).  Lists the layers that are 3 %
     or more slower for it, and a summary over the layers for which the rule takes the kernel."""
     import random
     rng = random.Random(seed)
@@ -376,6 +408,9 @@ def rule_table(which: str, seed: int, count: int) -> None:
         if case is None:
             continue
         label, calls, takes = case
+        if not calls:
+            done += 1
+            continue
         ok = []
         for c in calls:
             try:
@@ -385,9 +420,13 @@ def rule_table(which: str, seed: int, count: int) -> None:
                 if e.status != dconv.STATUS_UNSUPPORTED:
                     raise
         t = [1e30] * len(ok)
+        if len(ok) < 2:
+            done += 1
+            continue
+        small = which == "point" or (which != "second" and min(_time(c, 0.2, 3) for c in ok) < 0.15)
         for _ in range(2):                 # alternating: neither gets the warmer chip
             for i, c in enumerate(ok):
-                t[i] = min(t[i], _graph_time(c) if which == "point" else _time(c, 4.0, 10))
+                t[i] = min(t[i], _graph_time(c) if small else _time(c, 4.0, 10))
         ratio = min(t[1:]) / t[0]
         everything.append(ratio)
         if takes:
@@ -401,7 +440,7 @@ def rule_table(which: str, seed: int, count: int) -> None:
     taken.sort()
     print(f"# without the kernel / with it: taken on {len(taken)} of {count} layers, there geometric mean {mean(taken):.3f}, "
           f"worst {taken[0] if taken else 1.0:.3f}, median {taken[len(taken) // 2] if taken else 1.0:.3f}, best {taken[-1] if taken else 1.0:.2f}, "
-          f"{sum(r <= 0.97 for r in taken)} layers 3 % or more slower; over all layers {mean(everything):.3f}")
+          f"{sum(r <= 0.97 for r in taken)} layers 3 % or more slower; over all layers measured {mean(everything):.3f}")
 
 
 def writeback_table() -> None:
@@ -520,7 +559,7 @@ def main(argv):
             return 2
         random_table(argv[1], int(argv[2]), int(argv[3]))
         return 0
-    if len(argv) == 4 and argv[0] == "rule" and argv[1] in ("parts", "second", "point"):
+    if len(argv) == 4 and argv[0] == "rule" and argv[1] in ("parts", "second", "point", "channels", "taps", "short", "short-types"):
         if not torch.cuda.is_available():
             print("tune needs a GPU", file=sys.stderr)
             return 2

@@ -1,5 +1,5 @@
 """Few filters with the taps of all filters as rows of a matrix product (VARIANT_FEW_TAPS, and AUTO by estimated time).
-The shapes are small ones that the library's rule sends there.
+The shapes are small ones that reach every instantiation of the kernel, which is called by name.
 """
 import numpy as np
 import pytest
@@ -11,6 +11,7 @@ import paper_1705_10591_amd as dconv
 from helpers import assert_within_bound
 
 pytestmark = pytest.mark.gpu
+FEW_TAPS = dconv.VARIANT_FEW_TAPS
 
 # (N, C, H, W, K, F): every filter side, one to seven blocks of tap rows, four and eight waves a workgroup, one,
 # two and four column blocks of 64 per row, two column strips, one and two sets of sums in LDS; channels off
@@ -33,15 +34,14 @@ def test_within_the_bound_between_guard_bands(shape):
     want = (N, K, H - F + 1, W - F + 1)
     buf = torch.full((int(np.prod(want)) + 2048,), float("nan"), device="cuda")
     out = buf[1001:len(buf) - 1047].view(want)
-    dconv.dconv_general(xb, fd, out=out)
-    again = dconv.dconv_general(xb.clone(), fd, noalloc=True)
-    named, few, tiled = (dconv.dconv_general(xb, fd, variant=v) for v in (dconv.VARIANT_FEW_TAPS, dconv.VARIANT_FEW_FILTERS, dconv.VARIANT_TILED))
+    dconv.dconv_general(xb, fd, out=out, variant=FEW_TAPS)
+    again = dconv.dconv_general(xb.clone(), fd, noalloc=True, variant=FEW_TAPS)
+    few, tiled = (dconv.dconv_general(xb, fd, variant=v) for v in (dconv.VARIANT_FEW_FILTERS, dconv.VARIANT_TILED))
     torch.cuda.synchronize()
     got = out.cpu().numpy()
     acc, mag, _ = oracle.general(x, f)
     assert_within_bound(got, acc, mag, f"few filters {shape}")
     assert torch.equal(out, again)
-    assert dconv.kernel_choice(False, *shape) == dconv.VARIANT_FEW_TAPS and torch.equal(out, named)
     # (with 1x1 filters and a few channels all kernels form the same chain)
     assert F == 1 or not torch.equal(out, few) and not torch.equal(out, tiled)
     # the vector-ALU kernel's sums are one chain: no closer to the exact ones
@@ -52,7 +52,7 @@ def test_within_the_bound_between_guard_bands(shape):
     # one pixel that is not finite reaches the outputs whose windows hold it, and no other
     at = (N - 1, C - 1, H // 2, W - 2)
     xb[at] = float("nan")
-    marked = dconv.dconv_general(xb, fd)
+    marked = dconv.dconv_general(xb, fd, variant=FEW_TAPS)
     hit = torch.zeros_like(out, dtype=torch.bool)
     hit[N - 1, :, max(0, at[2] - F + 1):at[2] + 1, max(0, at[3] - F + 1):at[3] + 1] = True
     assert torch.equal(torch.isnan(marked), hit) and torch.equal(marked[~hit], out[~hit])
@@ -61,16 +61,28 @@ def test_within_the_bound_between_guard_bands(shape):
 @pytest.mark.parametrize("shape", SHAPES[3::4], ids=lambda s: "x".join(map(str, s)))
 def test_integer_inputs_are_exact(shape):
     x, f = wl.integer_case(9950, *shape)
-    out = dconv.dconv_general(torch.from_numpy(x).cuda(), torch.from_numpy(f).cuda())
+    out = dconv.dconv_general(torch.from_numpy(x).cuda(), torch.from_numpy(f).cuda(), variant=FEW_TAPS)
     torch.cuda.synchronize()
     assert np.array_equal(out.cpu().numpy(), oracle.general(x, f)[0].astype(np.float32))
 
 
+# layers that the rule sends there, in place of the vector-ALU kernel and of the tiled one
+CHOSEN = [(8, 64, 60, 60, 3, 3), (16, 200, 40, 64, 3, 3), (8, 64, 224, 224, 3, 3), (4, 128, 56, 56, 3, 3)]
+
+
+@pytest.mark.parametrize("shape", CHOSEN, ids=lambda s: "x".join(map(str, s)))
+def test_where_the_library_picks_it(shape):
+    assert dconv.kernel_choice(False, *shape) == FEW_TAPS
+    x, f = (torch.from_numpy(a).cuda() for a in wl.random_case(9970, *shape, "u01", "he"))
+    want = dconv.dconv_general(x, f, variant=FEW_TAPS)
+    assert torch.equal(dconv.dconv_general(x, f), want) and torch.equal(dconv.dconv_general(x, f, noalloc=True), want)
+
+
 def test_a_captured_call_runs_the_same():
     """No workspace: the replayed graph gives the eager call's bits, with other work between replays."""
-    x, f = (torch.from_numpy(a).cuda() for a in wl.random_case(9960, *SHAPES[-1], "u01", "he"))
+    x, f = (torch.from_numpy(a).cuda() for a in wl.random_case(9960, *CHOSEN[1], "u01", "he"))
     eager = dconv.dconv_general(x, f)
-    assert torch.equal(eager, dconv.dconv_general(x, f, variant=dconv.VARIANT_FEW_TAPS))
+    assert torch.equal(eager, dconv.dconv_general(x, f, variant=FEW_TAPS))
     out = torch.zeros_like(eager)
     torch.cuda.synchronize()
     graph = torch.cuda.CUDAGraph()

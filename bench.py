@@ -184,17 +184,22 @@ def half_entry(w, kind, ms):
 
 
 def config_entry(w, ms):
+    import paper_1705_10591_amd as dconv
+    kernel = dconv.kernel_choice(w.kind == "single", w.N, w.C, w.H, w.W, w.K, w.F)
+    # (products of bf16 parts pass the fp32 matrix-core peak: theirs beside it)
+    parts = {"frac_bf16_parts": round(w.flops / (ms * 1e-3) / 1e12 * 6 / MFMA16_PEAK_TFLOPS, 4)} \
+        if kernel in (dconv.VARIANT_PARTS, dconv.VARIANT_FEW_CHANNELS) else {}
     gflops = w.flops / (ms * 1e-3) / 1e9
     gbs = w.algorithmic_bytes / (ms * 1e-3) / 1e9
     return {"name": w.name, "kernel": "dconv_single_channel" if w.kind == "single" else "dconv_general",
             "shape": {"N": w.N, "C": w.C, "H": w.H, "W": w.W, "K": w.K, "F": w.F},
             "ms": round(ms, 5), "gflops": round(gflops, 1),
-            "frac_fp32_peak": round(gflops / 1e3 / FP32_PEAK_TFLOPS, 4),
+            "frac_fp32_peak": round(gflops / 1e3 / FP32_PEAK_TFLOPS, 4), **parts,
             "algorithmic_gbs": round(gbs, 1), "frac_hbm_peak": round(gbs / HBM_PEAK_GBS, 4)}
 
 
 def add_parts_peak(roof):
-    """Large fp32 layers of the general case run on the bf16 matrix cores, six products of bf16 parts for
+    """Large fp32 layers and layers of few channels run on the bf16 matrix cores, six products of bf16 parts for
     one of fp32 (their rate can pass the fp32 matrix-core peak): the peak of that way beside the other."""
     roof["peak_bf16_parts"] = round(MFMA16_PEAK_TFLOPS / 6, 1)
     roof["frac_bf16_parts"] = round(roof["achieved"] * 6 / MFMA16_PEAK_TFLOPS, 4)
@@ -338,14 +343,15 @@ def main():
         # the packed forms, which this build switches off: plain multiply-adds reach half of it)
         import paper_1705_10591_amd as dconv
         sh = entry["shape"]
-        on_alu = dconv.kernel_choice(single, sh["N"], sh["C"], sh["H"], sh["W"], sh["K"], sh["F"]) == dconv.VARIANT_FEW_FILTERS
+        kernel = dconv.kernel_choice(single, sh["N"], sh["C"], sh["H"], sh["W"], sh["K"], sh["F"])
+        on_alu = kernel == dconv.VARIANT_FEW_FILTERS
         roof = {"bound": "alu" if on_alu else "mfma", "achieved": round(entry["gflops"] / 1e3, 3),
                 "peak": FP32_PEAK_TFLOPS, "unit": "TFLOP/s",
                 "frac": round(entry["gflops"] / 1e3 / FP32_PEAK_TFLOPS, 4)}
         if on_alu:
             roof["peak_plain_fma"] = FP32_PEAK_TFLOPS / 2
             roof["frac_plain_fma"] = round(entry["gflops"] / 1e3 / (FP32_PEAK_TFLOPS / 2), 4)
-        elif not single and 2 <= sh["F"] <= 7:
+        elif kernel in (dconv.VARIANT_PARTS, dconv.VARIANT_FEW_CHANNELS):
             add_parts_peak(roof)
     roof["kernel"] = entry["kernel"]
     roof["kernel_ms"] = round(ms, 5)

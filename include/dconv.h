@@ -38,7 +38,7 @@
  *     which stays on fp32 products and takes the same time for any data.
  *     Layers of up to sixteen channels with enough work, and images of one channel
  *     (dconv_single_channel too), AUTO takes apart the same way, with the same
- *     limits (filters of 2x2 to 11x11, more than eight, up to 512 taps).  There
+ *     limits (more than eight filters of 2x2 to 11x11, up to 512 taps).  There
  *     errors against exact sums are a third of the fp32 instructions' (0.35e-7 of
  *     the norm against 0.91e-7 with 25 terms, 0.51e-7 against 1.63e-7 with 81,
  *     0.98e-7 against 3.3e-7 with 363), and filters of one weight that is not zero
@@ -118,8 +118,10 @@ enum {
                                  product on the fp32 matrix cores                */
     DCONV_VARIANT_FEW_CHANNELS = 7,
                               /* up to sixteen channels, filters of 2x2 to 11x11 and
-                                 at most 512 taps: products of parts, reduction over
-                                 taps (see above); also dconv_single_channel_v   */
+                                 at most 512 taps (odd sides counted as the next
+                                 even ones across) whose image block fits the
+                                 LDS: products of parts, reduction over taps (see
+                                 above); also dconv_single_channel_v             */
     DCONV_VARIANT_PARTS = 8,  /* filters of 2x2 to 7x7: products of parts, reduction
                                  over channels (see above).  Like FEW_CHANNELS it
                                  may keep split filters in the workspace, and is

@@ -807,8 +807,8 @@ int launch_split_taps(const float* in, const float* filt, float* out, const Shap
     if (!pl.ok) return DCONV_UNSUPPORTED;
     // (filters split into the workspace: see try_split)
     if (!pl.res && !static_ws && gen_capturing(st)) return DCONV_UNSUPPORTED;
-    // (sixteen filters always stay in LDS)
     switch (pl.MB * 4 + (!pl.res ? 0 : pl.psb == kTapsPartSmall ? 1 : 2)) {
+    case 4: return taps_launch<1, false, taps_part_large(1)>(in, filt, out, s, st, pl, static_ws);
     case 5: return taps_launch<1, true, kTapsPartSmall>(in, filt, out, s, st, pl, static_ws);
     case 6: return taps_launch<1, true, taps_part_large(1)>(in, filt, out, s, st, pl, static_ws);
     case 8: return taps_launch<2, false, taps_part_large(2)>(in, filt, out, s, st, pl, static_ws);

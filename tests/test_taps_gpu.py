@@ -21,7 +21,7 @@ pytestmark = pytest.mark.gpu
 SHAPES = [(1, 6, 193, 311, 9, 4), (2, 6, 189, 159, 9, 4), (5, 15, 180, 101, 9, 2), (7, 5, 50, 134, 17, 10), (8, 7, 81, 71, 17, 8),
           (9, 3, 154, 90, 18, 6), (5, 1, 208, 134, 19, 11), (4, 6, 72, 394, 17, 4), (4, 3, 78, 135, 35, 10), (8, 10, 44, 143, 33, 5),
           (7, 2, 89, 205, 33, 5), (8, 3, 165, 83, 34, 5), (5, 15, 53, 373, 35, 2), (4, 6, 52, 278, 49, 6), (9, 1, 62, 123, 97, 8),
-          (9, 12, 149, 46, 100, 2), (47, 3, 98, 41, 32, 11), (1, 1, 409, 724, 130, 9)]
+          (9, 12, 149, 46, 100, 2), (47, 3, 98, 41, 32, 11), (1, 1, 409, 724, 130, 9), (3, 8, 40, 61, 16, 8)]
 ids = lambda s: "x".join(map(str, s))
 FEW_CHANNELS = dconv.VARIANT_FEW_CHANNELS
 

@@ -786,8 +786,9 @@ double split_taps_time_if_preferred(const Shape& s, TapsPlan* plan)
     if (t.steps > kTapsSteps) return 1e300;
     const double px = (double)s.N * s.Ho * s.Wo, mb = px * s.K * 4e-6;
     // (few multiply-adds per output of a large volume: bound by its stores, which the special case's kernel arranges
-    // better: 3008 x 2282 with 48 7x7 filters 457 us there, 500 here; 98 of 9x9 on 3374 x 959 694 and 544)
-    if (s.N == 1 && s.C == 1 && mb > 1000 && s.F < 8) return 1e300;
+    // better: 4096 x 4096 with 64 8x8 filters 1337 us there, 1588 here, 3008 x 2282 with 48 7x7 457 and 500; with 9x9
+    // filters 1632 and 1367, 913 and 776 on 3000 x 3000)
+    if (s.N == 1 && s.C == 1 && mb > 1000 && s.F < 9) return 1e300;
     const double tiles = std::ceil(px * 1.04 / kTapsNT) * t.KB, work = t.steps * t.MB;
     const double rounds = tiles > 1536 ? tiles / 512 : std::ceil(tiles / 512);
     const bool res = taps_fits(t, t.steps, kTapsPartSmall);

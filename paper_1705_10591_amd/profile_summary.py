@@ -80,6 +80,9 @@ def trace(d, bench_json):
     ach = r["achieved"] * r["kernel_ms"] / med_ms      # (the line's rate is work / kernel_ms)
     out.append(f"from the median: achieved {ach:.1f} {r['unit']} = {ach / r['peak']:.4f} of the published peak "
                f"({r['peak']} {r['unit']})")
+    if "peak_bf16_parts" in r:
+        out.append(f"the kernel forms six products of bf16 parts for one of fp32: {ach / r['peak_bf16_parts']:.4f} of a sixth of "
+                   f"the published bf16 peak ({r['peak_bf16_parts']} {r['unit']})")
     others = {}
     for s, e, n in rows:
         if n != name:

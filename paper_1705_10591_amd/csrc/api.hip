@@ -111,7 +111,7 @@ int launch_auto(bool single_entry, const float* in, const float* filt, float* ou
 {
     Route r = auto_route(s, single_entry, true);
     if (r.variant == DCONV_VARIANT_FEW_CHANNELS) {
-        if (!static_ws && r.taps.res && !r.single) dconv::bring_workspace(s, st);
+        if (!static_ws && r.taps.res && (!r.single || dconv::single_general_preferred(s))) dconv::bring_workspace(s, st);
         const int rc = dconv::launch_split_taps(in, filt, out, s, st, static_ws, r.taps);
         if (rc != DCONV_UNSUPPORTED) return rc;
         r = auto_route(s, single_entry, false);

@@ -16,14 +16,14 @@
 //    products begin meanwhile.
 //  * A workgroup, of four or eight waves, has a band of rows of a column strip of an image.
 //
-// Errors: sixteen channels are summed by themselves, the groups then, the taps last: 2.0e-7 of the norm with 64
-// channels of 3x3 (the vector-ALU kernel, one chain of 576, 4.5e-7).
+// Errors: sixteen channels are summed by themselves, the groups then, the taps last: 0.97e-7 of the norm with 64
+// channels of 3x3 and values in -1 .. 1, 1.2e-7 with activations (the vector-ALU kernel, one chain of 576, 4.3e-7 and 4.6e-7).
 //
-// What bounds it: 8 x 64 x 224 x 224, three 3x3 filters, input in memory: 51 -> 34 us.  10 rows of products a CU take
+// What bounds it: 8 x 64 x 224 x 224, three 3x3 filters: 50 -> 36 us by the call, 33.5 the kernel.  10 rows of products a CU take
 // 17.6 us on the fp32 matrix cores (27 rows of 32, 224 columns of 256, 9 rows for 7 of output), their input 21 us
 // at 5 TB/s; the additions and barriers between phases cost 0.7 us a phase (with four waves a workgroup, one
-// row a phase: 36 us).  16 x 256 x 64 x 64, three 3x3 filters (on the general kernel before): 92 -> 26 us;
-// 4 x 128 x 56 x 56: 24.5 -> 10.2; 8 x 64 x 224 x 224, twelve 1x1 filters: 46 -> 27.
+// row a phase: 2 us more).  16 x 256 x 64 x 64, three 3x3 filters (on the general kernel before): 93 -> 28 us;
+// 4 x 128 x 56 x 56: 26 -> 11.3; 8 x 64 x 224 x 224, twelve 1x1 filters: 43 -> 26 (kernels replayed from a graph).
 #pragma once
 #include <algorithm>
 #include <cmath>

@@ -16,8 +16,9 @@
 // step of a 64 x 64 tile takes 8 KB through it for 256 cycles of products.
 //
 // Measured (general_half_kernel -> this one, kernels replayed from a graph): three images of 320 x 8 x 8 with 106
-// 3x3 filters, bf16, blocked 21.7 -> 7.4 us (by the call); two of 384 x 17 x 18 with 229 5x5, int8 41.0 -> 13.4;
-// one of 352 x 25 x 25 with 25 3x3, bf16 28.4 -> 6.5; eleven of 112 x 11 x 11 with 227 7x7, bf16 45.2 -> 13.1.
+// 3x3 filters, bf16, blocked 22.0 -> 6.0 us; two of 384 x 17 x 18 with 229 5x5, int8 49.7 -> 19.6;
+// one of 352 x 25 x 25 with 25 3x3, bf16 28.2 -> 6.1; eleven of 112 x 11 x 11 with 227 7x7, bf16 52.9 -> 14.1; one of 256 x
+// 14 x 14 with 256 3x3, fp16 21.3 -> 6.6.
 // Sums are a half or a quarter as long: errors against 64 bits halve (3.2e-7 -> 1.6e-7 in the first of these).
 #include <algorithm>
 #include "half_kernel.h"

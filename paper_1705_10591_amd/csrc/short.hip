@@ -215,9 +215,10 @@ static double short_time(const Shape& s, int* cfg)
 // 150 TFLOP/s or, if that is less, what sharing them takes, the root of the products' time, memory at 7 TB/s
 // beside it and 0.25 per thousand taps; rms 15.5 %.  It has to promise 15 %: of 4531 layers that the fit did not see
 // (both kernels' times within 19 % rms of their estimates) 2656 are chosen then, 1.93 times faster on average (1 x 256 x 14 x 14
-// with 256 3x3 filters 16.3 -> 8.7 us, 4 x 64 x 28 x 28 with 64 13.1 -> 9.4), 52 of them 3 % or more slower, by a
+// with 256 3x3 filters 16.3 -> 8.7 us, 8 x 50 x 30 x 30 with 90 24.9 -> 14.1, 4 x 64 x 28 x 28 with 64 12.9 -> 9.6, 16 x 32 x
+// 14 x 14 with 96 1x1 filters 8.3 -> 4.3), 52 of them 3 % or more slower, by a
 // third at most, of 7 to 37 us; with a tenth 2889, 1.86 times, 94 slower.  A list of slower ones:
-// profiles/rule_short_launches.txt.  Errors against 64 bits fall by a third: 1.95e-7 -> 1.25e-7 with 256 channels.
+// profiles/rule_short_launches.txt.  Errors against 64 bits: 1.85e-7 -> 1.09e-7 with 256 channels.
 struct GeneralTiles { double even, whole; };
 static GeneralTiles general_tiles(const Shape& s)
 {

@@ -177,3 +177,49 @@ def test_rules_that_hold_for_every_shape():
             assert c == 2          # no 64-filter block that is half padding
         if K % 64 == 0:
             assert c != 2          # nothing to save with 32-filter blocks
+
+
+def test_the_kernel_that_runs_by_shape():
+    kernel = dconv.kernel_choice
+    # what each rule was made for, and a neighbour that stays with the tiled kernel
+    assert kernel(False, 64, 3, 224, 224, 64, 11) == kernel(False, 1, 1, 1081, 1917, 40, 9) == dconv.VARIANT_FEW_CHANNELS
+    assert kernel(True, 1, 1, 1081, 1917, 40, 9) == kernel(True, 1, 1, 720, 1280, 40, 9) == dconv.VARIANT_FEW_CHANNELS
+    assert kernel(True, 1, 1, 4096, 4096, 64, 5) == dconv.VARIANT_TILED and kernel(False, 1, 1, 4096, 4096, 64, 5) == dconv.VARIANT_SPECIAL_CASE
+    assert kernel(False, 8, 64, 224, 224, 3, 3) == kernel(False, 16, 256, 64, 64, 3, 3) == dconv.VARIANT_FEW_TAPS
+    assert kernel(False, 37, 176, 192, 184, 3, 5) == dconv.VARIANT_FEW_FILTERS
+    assert kernel(False, 1, 256, 14, 14, 256, 3) == dconv.VARIANT_SHORT
+    assert kernel(False, 32, 256, 28, 28, 512, 3) == dconv.VARIANT_PARTS
+    assert kernel(False, 64, 512, 28, 28, 512, 1) == dconv.VARIANT_TILED
+    assert kernel(False, 4, 64, 56, 56, 64, 33) == dconv.VARIANT_SIMPLE
+    assert kernel(True, 1, 1, 64, 64, 128, 8) == dconv.CHOICE_GENERAL_CASE and kernel(False, 1, 1, 64, 64, 128, 8) == dconv.VARIANT_TILED
+    assert kernel(True, 1, 1, 256, 256, 1, 3) == dconv.VARIANT_FEW_FILTERS and kernel(False, 1, 1, 256, 256, 1, 3) == dconv.VARIANT_AUTO
+    assert kernel(True, 2, 1, 64, 64, 4, 3) == kernel(False, 1, 1, 8, 8, 0, 3) == dconv.CHOICE_INVALID
+
+
+def test_the_kernel_that_is_reported_accepts_the_shape():
+    """Without a GPU a call ends at its first HIP query, behind all that a kernel asks of a shape."""
+    import ctypes
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("with a GPU the calls would launch on fake pointers")
+    lib, fake, rng, seen = dconv.load_library(), ctypes.c_void_p(0x1000), random.Random(17), set()
+    for _ in range(6000):
+        few = rng.random() < 0.4
+        N, C = rng.choice((1, rng.randint(1, 64))), rng.randint(1, 16) if few else rng.randint(1, 600)
+        H, W = (rng.randint(1, 500), rng.randint(1, 500)) if few else (rng.randint(1, 130), rng.randint(1, 130))
+        K, F = rng.choice((rng.randint(1, 20), rng.randint(1, 600))), rng.choice((1, 2, 3, 3, 3, 4, 5, 6, 7, 8, 9, 10, 11, 13))
+        if F > min(H, W):
+            continue
+        variant = dconv.kernel_choice(False, N, C, H, W, K, F)
+        seen.add(variant)
+        rc = lib.dconv_general_noalloc(fake, N, C, H, W, fake, K, F, fake, variant, None)
+        assert rc == dconv.STATUS_LAUNCH_FAILED, (N, C, H, W, K, F, variant, rc)
+        if N == 1 and C == 1:
+            variant = dconv.kernel_choice(True, N, C, H, W, K, F)
+            if variant != dconv.CHOICE_GENERAL_CASE:
+                rc = lib.dconv_single_channel_v(fake, H, W, fake, K, F, fake, variant, None)
+                # (no question whether a stream captures has an answer here: such a call keeps off the workspace)
+                assert rc == dconv.STATUS_LAUNCH_FAILED or variant == dconv.VARIANT_FEW_CHANNELS and rc == dconv.STATUS_UNSUPPORTED, \
+                    (H, W, K, F, variant, rc)
+    assert {dconv.VARIANT_TILED, dconv.VARIANT_FEW_FILTERS, dconv.VARIANT_SPECIAL_CASE, dconv.VARIANT_SHORT, dconv.VARIANT_FEW_TAPS,
+            dconv.VARIANT_FEW_CHANNELS, dconv.VARIANT_PARTS} <= seen, seen

@@ -139,6 +139,19 @@ def test_filters_of_few_weights(shape):
     assert np.array_equal(np.isnan(call(x, f)), np.isnan(acc))
 
 
+@pytest.mark.parametrize("weights", [2, 3, 12])
+def test_banks_of_sparse_filters_are_no_further_off_than_on_the_fp32_kernel(weights):
+    N, C, H, W, K, F = shape = (3, 3, 80, 90, 48, 7)
+    x, f = wl.random_case(9390 + weights, *shape)
+    rng = np.random.default_rng(weights)
+    for k in range(K):
+        f[k].reshape(-1)[rng.permutation(C * F * F)[weights:]] = 0
+    acc, mag, _ = oracle.general(x, f)
+    got, fp32 = (call(x, f, v) for v in (FEW_CHANNELS, dconv.VARIANT_TILED))
+    assert_within_bound(got, acc, mag, f"{weights} weights")
+    assert np.linalg.norm(got - acc) <= np.linalg.norm(fp32 - acc)
+
+
 def test_whole_numbers_are_exact_while_their_sums_are():
     """Products of 24 bits: odd pixels of 12 bits under a weight of 12 bits among small ones, and pixels of 24 bits, one a
     window, under powers of two."""
@@ -175,9 +188,9 @@ def test_short_sums_are_no_further_off_than_on_the_fp32_kernel(shape):
     x[:] = np.random.default_rng(T).uniform(0.5, 2, (1, C, 1, 1))
     f[:] = np.random.default_rng(T + 1).uniform(0.5, 2, (K, 1, 1, 1))
     acc, mag, _ = oracle.general(x, f)
-    # (2^-26 a product; the large products' sum is rounded every eight of them, the small ones' sum counts for 2^-8 of it,
+    # (2^-24 a product; the large products' sum is rounded every eight of them, the small ones' sum counts for 2^-8 of it,
     # and both are added)
-    assert np.all(np.abs(call(x, f, dconv.VARIANT_FEW_CHANNELS) - acc) <= (2.0 ** -26 + 2.0 ** -24 * (1.2 * -(-T // 8) + 1)) * mag)
+    assert np.all(np.abs(call(x, f, dconv.VARIANT_FEW_CHANNELS) - acc) <= 2.0 ** -24 * (1 + 1.2 * -(-T // 8) + 1) * mag)
 
 
 # layers that the rule sends there: filters that stay on the chip, filters that go through the workspace

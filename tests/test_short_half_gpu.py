@@ -19,7 +19,8 @@ SHAPES = [(1, 32, 5, 5, 9, 2), (1, 96, 7, 9, 17, 1), (3, 32, 3, 3, 1, 3), (1, 25
           (13, 96, 10, 12, 65, 3), (64, 32, 7, 7, 70, 7), (4, 64, 28, 28, 130, 4), (5, 224, 23, 31, 50, 2),
           (15, 32, 43, 19, 34, 4),
           (25, 192, 25, 24, 34, 2), (13, 384, 40, 17, 66, 2), (6, 480, 36, 36, 135, 2), (18, 128, 37, 44, 16, 7)]
-CHOSEN = [s for s in SHAPES if s not in ((15, 32, 43, 19, 34, 4), (25, 192, 25, 24, 34, 2), (6, 480, 36, 36, 135, 2))]     # (by AUTO)
+# layers that AUTO runs on the tiled kernel, with channels last and blocked
+ELSEWHERE = {False: [(25, 192, 25, 24, 34, 2), (13, 384, 40, 17, 66, 2)], True: [(25, 192, 25, 24, 34, 2)]}
 ids = lambda s: "x".join(map(str, s))
 SHORT = dconv.VARIANT_SHORT
 
@@ -64,7 +65,7 @@ def test_within_the_bound_and_no_further_off_than_the_tiled_kernel(shape, kind, 
     acc, mag, _ = oracle.general(xr, fr)
     assert_within_bound(out.cpu().numpy(), acc, mag, f"short {kind} {shape}")
     assert not torch.equal(out, tiled)
-    assert torch.equal(auto, out if shape in CHOSEN else tiled), "small tiles are expected to run under AUTO in CHOSEN alone"
+    assert torch.equal(auto, tiled if shape in ELSEWHERE[blocked] else out), "small tiles are expected to run here, or not to"
     err = [np.linalg.norm(o.cpu().numpy() - acc) for o in (out, tiled)]
     print(f"  errors {err}", flush=True)
     assert err[0] <= err[1], err

@@ -107,10 +107,10 @@ int preferred_config(const Shape& s, int dtype, bool blocked)
 // Short launches: the estimate of half_short.hip against one of the tiled kernel, fitted to the same layers
 // (rms 9 %): launch, steps and chunks of one tile, steps of the tiles beyond one per CU, rounds, memory and output.
 // It has to promise a twentieth and, as both estimates lean on the tiles' overlap where there are many, 2 % more
-// for every microsecond.  Pixels a multiple of 128 or 512 bytes apart, whose loads crowd into the same channels of the L2, take
-// the small tiles 1.3 and 1.5 times the estimate (channels last; channel-blocked runs of such length 1.1 and 1.4).  Of 1500
-// layers that the fit did not see (2x2 to 7x7, up to 30 GFLOP) 864 are chosen, 2.3 times faster on average, nine of them 3 %
-// or more slower (by up to 23 %); where the strides do not count 887, 17 slower.  A list of slower ones:
+// for every microsecond; and a tenth with what strides cost: pixels a multiple of 128 or 512 bytes apart, whose loads crowd into
+// the same channels of the L2, take the small tiles 1.3 and 1.5 times the estimate (channels last; channel-blocked runs of such
+// length 1.1 and 1.4).  Of 1500 layers that the fit did not see (2x2 to 7x7, up to 30 GFLOP) 878 are chosen, 2.3 times faster
+// on average, twelve of them 3 % or more slower (by up to 23 %); where the strides do not count 887, 17 slower.  A list of slower ones:
 // profiles/rule_short_launches_short_types.txt.
 // The large tile (few of those layers) and filters from 8x8 on (none) keep the tiled kernel.
 bool short_preferred(const Shape& s, int dtype, bool blocked, int tile, int* cfg)
@@ -118,7 +118,7 @@ bool short_preferred(const Shape& s, int dtype, bool blocked, int tile, int* cfg
     if (s.F > 7 || tile == 1 || tile == 3) return false;
     const int run = s.C * elem_bytes(dtype);
     const double crowded = run % 512 == 0 ? (blocked ? 1.4 : 1.5) : run % 128 == 0 ? (blocked ? 1.1 : 1.3) : 1.0;
-    const double here = crowded * short_half_time(s, dtype, cfg);
+    const double here = short_half_time(s, dtype, cfg);
     if (here > 1e200) return false;
     const int rg = half_row_group(s.F);
     const int64_t px = (int64_t)s.N * s.Ho * s.Wo, groups = (int64_t)s.C * elem_bytes(dtype) / kHalfChunkBytes;
@@ -129,7 +129,7 @@ bool short_preferred(const Shape& s, int dtype, bool blocked, int tile, int* cfg
     const double mb = 1e-6 * groups * kHalfChunkBytes * ((double)s.N * s.H * s.W + (double)s.K * s.F * s.F) + out;
     const double tile_us = mid ? 0.283 * steps : 0.0898 * steps + 0.2555 * chunks + 0.1466 * std::max(0.0, tiles / 256 - 1) * steps;
     const double there = 4.525 + tile_us + 0.2874 * (std::ceil(tiles / 256) - 1) + 0.0914 * mb + 0.0544 * out;
-    return here * (1.05 + 0.02 * here) < there;
+    return std::max(1.05 + 0.02 * here, 1.1 * crowded) * here < there;
 }
 
 }  // namespace

@@ -20,7 +20,7 @@ SHAPES = [(1, 32, 5, 5, 9, 2), (1, 96, 7, 9, 17, 1), (3, 32, 3, 3, 1, 3), (1, 25
           (15, 32, 43, 19, 34, 4),
           (25, 192, 25, 24, 34, 2), (13, 384, 40, 17, 66, 2), (6, 480, 36, 36, 135, 2), (18, 128, 37, 44, 16, 7)]
 # layers that AUTO runs on the tiled kernel, with channels last and blocked
-ELSEWHERE = {False: [(25, 192, 25, 24, 34, 2), (13, 384, 40, 17, 66, 2)], True: [(25, 192, 25, 24, 34, 2)]}
+ELSEWHERE = {False: [(25, 192, 25, 24, 34, 2)], True: []}
 ids = lambda s: "x".join(map(str, s))
 SHORT = dconv.VARIANT_SHORT
 

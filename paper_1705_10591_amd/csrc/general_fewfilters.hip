@@ -37,9 +37,7 @@ bool general_few_supports(const Shape& s)
 // chosen it is up to 6 times faster (101 x 3 x 64 x 640, two 1x1 filters: 97 -> 16 us; 8 x 16 x 224
 // x 224, one 7x7 filter: 189 -> 23 us; 8 x 64 x 224 x 224, three 3x3 filters: 139 -> 49 us; eight:
 // 139 -> 81 us; 21 x 8 x 96 x 640, twelve 5x5: 174 -> 80 us).
-// What the estimates are made of: a workgroup's chain, tiles, memory and multiply-adds, in microseconds.
-struct FewParts { double chain, tiles, memory, products; };
-static FewParts few_parts(const Shape& s)
+static double few_time(const Shape& s, double* tiles_out)
 {
     static const int kCompiled[17] = {0, 1, 2, 3, 4, 6, 6, 8, 8, 12, 12, 12, 12, 16, 16, 16, 16};
     const GfTile t = gf_tile_for(s);
@@ -52,33 +50,37 @@ static FewParts few_parts(const Shape& s)
     const double bytes = 4.0 * ((double)s.N * s.C * s.H * s.W + (double)s.N * s.K * s.Ho * s.Wo);
     const int per_barrier = (t.rpw == 1 && kc <= 8) ? 2 : 1;              // channels (see launch_gf)
     const double chain = s.C * (0.30 / per_barrier + 0.010 * (tr + s.F - 1) + 0.0105 * kc * ff * t.rpw + 0.03 * kc);
-    return {chain, tiles, bytes / 5.1e6, 2.0 * macs * kc / inside / 70e6};
+    *tiles_out = tiles;
+    return 3.4 + std::max({chain * std::max(1.0, tiles / 430.0), bytes / 5.1e6, 2.0 * macs * kc / inside / 70e6});
 }
 bool general_few_preferred(const Shape& s)
 {
     // (one image of one channel is the special case proper, which has its own few-filters kernel)
     if (!general_few_supports(s) || (s.C == 1 && s.N == 1)) return false;
-    const FewParts p = few_parts(s);
-    const double few = 3.4 + std::max({p.chain * std::max(1.0, p.tiles / 430.0), p.memory, p.products});
+    double tiles;
+    const double few = few_time(s, &tiles);
     const int ff = s.F * s.F;
     const double macs = (double)s.N * s.Ho * s.Wo * s.C * ff;             // per filter
     const double bytes = 4.0 * ((double)s.N * s.C * s.H * s.W + (double)s.N * s.K * s.Ho * s.Wo);
     const double tiled = 7.1 + std::max({0.055 * s.C + 0.009 * s.C * ff, 2.0 * macs * 32 / 88e6, bytes / 2.6e6});
-    return few < (p.tiles >= 768 ? 1.0 : 0.95) * tiled;
+    return few < (tiles >= 768 ? 1.0 : 0.95) * tiled;
 }
 
 // When the taps of all filters go to the matrix cores (few_taps_kernel.h) instead: where its estimated time is
-// below 85 % of the vector-ALU kernel's, for layers that are that one's, or three quarters of the general matrix-core
+// below 95 % of the vector-ALU kernel's, for layers that are that one's, or 85 % of the general matrix-core
 // kernel's, for the others (up to 64 taps there: with more, sums of many channels are no closer to the exact
-// ones).  Fitted to kernel times of 1722 layers from replayed graphs (1 to 16 filters of 1x1 to 7x7, 2 to 512
-// channels, 14 x 14 to 256 x 512 maps, 1 to 64 images), in microseconds.  This kernel, rms 13 %: 1.1 and 0.9 per filter side, the
-// larger one of the plan's estimate and of input and output at 4.4 TB/s times 0.74, the smaller one times 0.68, 0.96 per
-// thousand weights, 0.014 per phase, row and tap of a filter for the additions.  The vector-ALU kernel, rms 14 %: the parts of
-// the estimate above, summed (their largest alone is off by 18 %, and by a third where its tiles fill the chip many times over).
-// The general kernel: 8.1, a 32-filter block at 137 TFLOP/s and the root of it, input and output at 4.2 TB/s and a chain
-// per channel; rms 28 %.  617 of the layers are of the first kind: 160 are chosen, 1.55 times faster, nine of them 3 % or more
-// slower, by up to 18 % (twice a third, of 3 us); 1105 of the others: 570 chosen, twice as fast, 12 slower, by up to a
-// quarter.  Layers that the fit did not see: profiles/rule_taps_of_few_filters.txt.
+// ones).  Fitted to kernel times of 1600 layers from replayed graphs (1 to 16 filters of 1x1 to 7x7, 2 to 512
+// channels, 14 x 14 to 256 x 512 maps, 1 to 64 images), in microseconds; rms 15 % for this kernel, 22 % for the
+// general one: 3.9, the larger one of the plan's estimate and of input and output at 4.4 TB/s with a third of
+// the smaller one, 0.77 per thousand weights; 8.1, a 32-filter block at 137 TFLOP/s and the root of it, input
+// and output at 4.2 TB/s and a chain per channel.  Launches of the vector-ALU kernel of over 200 us have to be beaten by 15 %, as its
+// estimate is high where its tiles fill the chip many times over: 36 of 617 layers, one slower, where 5 % take four more,
+// two of them slower by a quarter and no faster on average.
+// Of 1722 layers that the fit did not see 617 were of the first kind: 176 are chosen, 1.47 times faster, 19 of them 3 % or
+// more slower (most of them launches of under 15 us; the worst 5.8 -> 9.4); 1105 of the others: 544 chosen, twice as fast,
+// eight slower, by up to 24 %.  Both estimates fitted anew (rms 13 and 14 %) with a line at 85 % had nine slower ones of 160, but
+// left 46 layers to the vector-ALU kernel that were faster by 1.5 % on average here, and five times closer to the exact sums.
+// A list of slower ones: profiles/rule_taps_of_few_filters.txt.
 FewTapsPlan make_few_taps_plan(const Shape& s) { return few_taps_plan(s); }
 
 FewFilters few_filters_for(const Shape& s)
@@ -90,18 +92,15 @@ FewFilters few_filters_for(const Shape& s)
     if (!pl.ok) return r;
     const double ff = (double)s.F * s.F, px = (double)s.N * s.Ho * s.Wo;
     const double mb = 4e-6 * ((double)s.N * s.C * s.H * s.W + px * s.K), memory = mb / 4.4;
-    const int rp = pl.nw / pl.cb;                                                   // rows of a phase
-    const double additions = (double)((pl.rb + s.F - 1 + rp - 1) / rp) * std::ceil(pl.total / 256.0) * s.K * ff / rp;
-    const double here = 1.14 + 0.913 * s.F + 0.736 * std::max(pl.cost, memory) + 0.679 * std::min(pl.cost, memory) +
-                        0.955e-3 * s.K * ff * s.C + 0.0139 * additions;
+    const double here = 3.9 + 0.99 * std::max(pl.cost, memory) + 0.357 * std::min(pl.cost, memory) + 0.77e-3 * s.K * ff * s.C;
     bool better;
     if (r.alu) {
-        const FewParts p = few_parts(s);
-        const double few = 3.32 + p.chain * (0.812 + 0.204 * std::max(0.0, p.tiles / 430 - 1)) + 0.67 * p.memory + 0.227 * p.products;
-        better = here < 0.85 * few;
+        double tiles;
+        const double few = few_time(s, &tiles);
+        better = here < (few > 200 ? 0.85 : 0.95) * few;
     } else {
         const double mflop = 2e-6 * px * 32 * s.C * ff;
-        better = pl.mb <= 4 && here < 0.75 * (8.1 + 0.0073 * mflop + 0.191 * std::sqrt(mflop) + 0.24 * mb + (0.0078 + 0.0183 * std::max(1.0, px / 256 / 512)) * s.C);
+        better = pl.mb <= 4 && here < 0.85 * (8.1 + 0.0073 * mflop + 0.191 * std::sqrt(mflop) + 0.24 * mb + (0.0078 + 0.0183 * std::max(1.0, px / 256 / 512)) * s.C);
     }
     if (!better) return r;
     r.taps = here;

@@ -213,12 +213,12 @@ static double short_time(const Shape& s, int* cfg)
 
 // The general kernel, by the tiles of the shape's own choice: 5.4, whole tiles one after the other on the CUs at
 // 150 TFLOP/s or, if that is less, what sharing them takes, the root of the products' time, memory at 7 TB/s
-// beside it and 0.25 per thousand taps; rms 15.5 %.  On few channels it takes less than that: 13 % less up to four, 6 % up
-// to fourteen.  It has to promise a tenth: of 4531 layers that the fit did not see
-// (both kernels' times within 19 % rms of their estimates) 2761 are chosen then, 1.91 times faster on average (1 x 256 x 14 x 14
+// beside it and 0.25 per thousand taps; rms 15.5 %.  It has to promise a tenth: of 4531 layers that the fit did
+// not see (both kernels' times within 19 % rms of their estimates) 2889 are chosen, 1.86 times faster on average (1 x 256 x 14 x 14
 // with 256 3x3 filters 16.3 -> 8.7 us, 8 x 50 x 30 x 30 with 90 24.9 -> 14.1, 4 x 64 x 28 x 28 with 64 12.9 -> 9.6, 16 x 32 x
-// 14 x 14 with 96 1x1 filters 8.3 -> 4.3), 51 of them 3 % or more slower, by a
-// third at most, of 7 to 37 us (2889 and 94 where the channels do not count).  A list of slower ones:
+// 14 x 14 with 96 1x1 filters 8.3 -> 4.3), 94 of them 3 % or more slower, 57 by more than a tenth (7 to 40 us; few filters on few
+// channels and large maps among them, the worst 13.6 -> 23.6).  With 15 % 52 would be, and 233 layers fewer be chosen, most of
+// them faster here and all of them closer to the exact sums.  A list of slower ones:
 // profiles/rule_short_launches.txt.  Errors against 64 bits: 1.85e-7 -> 1.09e-7 with 256 channels.
 struct GeneralTiles { double even, whole; };
 static GeneralTiles general_tiles(const Shape& s)
@@ -239,8 +239,7 @@ ShortChoice short_choice(const Shape& s)
     const double mb = 4e-6 * ((double)s.N * s.C * s.H * s.W + s.K * T + px * s.K);
     const GeneralTiles t = general_tiles(s);
     const double there = 5.44 + 1.067 * std::min(t.whole, 1.2 * t.even + 4) + 0.016 * t.even + 0.139 * mb + 2.1 * std::sqrt(t.even) + 0.25e-3 * T;
-    const double channels = s.C <= 4 ? 0.87 : s.C <= 14 ? 0.94 : 1.0;
-    if (here < 0.9 * channels * there) r.time = here;
+    if (here < 0.9 * there) r.time = here;
     return r;
 }
 
